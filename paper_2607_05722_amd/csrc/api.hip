@@ -117,13 +117,11 @@ namespace {
 struct Layout {
     int M, Mpad, units, n_splits, chunk, row_tiles, attn_kh, attn_z, n_parts, rows_pad, lm_tiles, lm_parts;
     bool attn_items;         // length-aware attention work (batches)
-    int n_sk_ctr, sk_ctr0;   // split-K residual GEMM: counters (one per column group) from tile counter sk_ctr0
-    int n_nk_ctr, nk_ctr0;   // normed GEMM of 17..64 rows: counters (one per column tile) from tile counter nk_ctr0
-    int n_tk_ctr, tk_ctr0;   // tiled GEMM with K slices (M > 64): counters (one per tile group) from tk_ctr0
-    int tk_part_wgs;         // (tile group, slice) partials its buffer holds
-    size_t nk_part_floats;   // and the size of its partials buffer
-    size_t status, x, xg, part_ss, q, o, act, keys, lse, rope, po, pml, blk_k, blk_v, tile_ctr, sk_part, tk_part, lora_t, drafts,
-        ens_logits, ens_v, nk_part, total;
+    int n_tile_ctr;          // tile counters in all, zeroed by the embedding kernel at the start of a pass
+    int n_ctr, ctr0;         // K slices: counters (one per group of tiles) from tile counter ctr0
+    size_t part_floats;      // K slices: room for their partials
+    size_t status, x, xg, part_ss, q, o, act, keys, lse, rope, po, pml, blk_k, blk_v, tile_ctr, part, lora_t, drafts,
+        ens_logits, ens_v, total;
 };
 
 // k: block rows per sequence.  quad_k > 0: the block is a quadratic self-speculation layout
@@ -131,8 +129,8 @@ struct Layout {
 Layout make_layout(const nld_config& c, int batch, int k, int max_len, int quad_k = 0) {
     Layout L{};
     L.M = batch * k;
-    // operand rows: whole 64-row groups, or whole 128-row tiles of the tiled GEMM (M > 64)
-    L.Mpad = L.M > 64 ? cdiv(L.M, gemm_tile_row_pad()) * gemm_tile_row_pad() : cdiv(L.M, 64) * 64;
+    // operand rows: whole row groups of the panel GEMM (128 rows for M > 64)
+    L.Mpad = L.M > 64 ? cdiv(L.M, 128) * 128 : 64;
     L.units = batch * c.n_kv_heads;
     const int G = c.n_q_heads / c.n_kv_heads;
     L.row_tiles = cdiv(G * k, 16);
@@ -181,40 +179,26 @@ Layout make_layout(const nld_config& c, int batch, int k, int max_len, int quad_
     L.keys = take(8 * L.Mpad * (size_t)L.lm_parts);
     L.lse = take(8 * L.Mpad * (size_t)L.lm_parts);   // softmax statistics per argmax partial (denoising)
     L.rope = take(8 * L.Mpad * (size_t)(c.head_dim / 2));
-    // split-K GEMM (M <= 64; the O, down, QKV and gate/up projections): one counter per column
-    // group of at least 2 tiles of the O, down and QKV projections, and the partials of up to
-    // SPLITK_MAX slices (gate/up, with more tiles, runs unsplit)
+    // K slices of a projection: counters (one per group of tiles) and room for the slices' partials.  Up to
+    // 64 rows the groups are at least one column tile, above 128 rows x 8 column tiles.
+    const int H32 = cdiv((int)H, 32);
     const int sk_tiles = std::max((int)H / 16, (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim / 16);
-    L.n_sk_ctr = L.M <= 64 ? cdiv(sk_tiles, 2) : 0;
-    const int sk_rows = L.M <= 32 ? 32 : 64;
-    L.sk_ctr0 = 2 * c.n_layers + 1;
-    // normed GEMM of 17..64 rows: one counter per column tile of the widest normed projection,
-    // partials of every K slice
-    const int nk_tiles = std::max(std::max(cdiv(c.vocab, 16), cdiv(c.ffn, 8)),
-                                  (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim / 16);
-    const bool nk = L.M > 16 && L.M <= 64;
-    L.n_nk_ctr = nk ? nk_tiles : 0;
-    L.nk_ctr0 = L.sk_ctr0 + L.n_sk_ctr;
-    // per pass: QKV and gate/up of every layer, LM head; then the split-K counters and the
-    // 17..64-row counters (all zeroed by the embedding kernel at the start of a pass)
-    // tiled GEMM (M > 64) with K slices: one counter per 128 x 128 tile group of the widest
-    // projection it may split (O, down, QKV, gate/up), partials of up to two workgroups per CU
-    const bool tk = L.M > 64;
-    L.n_tk_ctr = tk ? std::max(gemm_tile_groups(L.M, std::max(sk_tiles, cdiv(c.ffn, 8))), 1) : 0;
-    L.tk_ctr0 = L.nk_ctr0 + L.n_nk_ctr;
-    L.tk_part_wgs = tk ? 2 * gemm_tile_wgs_per_cu() * device_cus() : 0;
-    // per pass: QKV and gate/up of every layer, LM head; then the split-K counters, the 17..64-row
-    // counters and the tiled GEMM's counters (all zeroed by the embedding kernel at the start of a
-    // pass; the split GEMMs also reset theirs after each use)
-    L.tile_ctr = take(4 * (size_t)(2 * c.n_layers + 1 + L.n_sk_ctr + L.n_nk_ctr + L.n_tk_ctr));
-    L.tk_part = take(4 * (size_t)L.tk_part_wgs * gemm_tile_part_floats_per_wg());
-    // (the normed projections, LM head, QKV and gate/up, all reduce over hidden)
-    L.nk_part_floats = nk ? (size_t)nk_tiles * cdiv(cdiv((int)H, 32), gemm_normk_kstep_span(L.M)) *
-                                (L.M > 32 ? 4 : 2) * 256
-                          : 0;
-    L.nk_part = take(4 * L.nk_part_floats);
-    // partials: whole column groups (at most 2 * n_sk_ctr + 4 tiles of 16) x sk_rows rows x slices
-    L.sk_part = take(L.M <= 64 ? 4 * (size_t)(2 * L.n_sk_ctr + 4) * 16 * sk_rows * SPLITK_MAX : 0);
+    const int wide = std::max(std::max(L.lm_tiles, cdiv(c.ffn, 8)), sk_tiles);
+    const int sk_groups = cdiv(sk_tiles, 2);   // the split-K GEMM's column groups hold at least two tiles
+    L.ctr0 = 2 * c.n_layers + 1;               // after the normed GEMM's hand-out counters
+    size_t nk_floats = 0;
+    if (L.M <= 64) {
+        const size_t sk_floats = (size_t)(2 * sk_groups + 4) * 16 * (L.M <= 32 ? 32 : 64) * SPLITK_MAX;
+        if (L.M > 16) nk_floats = (size_t)wide * cdiv(H32, L.M > 32 ? 32 : 64) * (L.M > 32 ? 4 : 2) * 256;
+        L.n_ctr = sk_groups + (L.M > 16 ? wide : 0);
+        L.part_floats = nk_floats + sk_floats;
+    } else {
+        L.n_ctr = cdiv(L.M, 128) * cdiv(std::max(sk_tiles, cdiv(c.ffn, 8)), 8);
+        L.part_floats = (size_t)4 * device_cus() * 16384;
+    }
+    L.n_tile_ctr = L.ctr0 + L.n_ctr;
+    L.tile_ctr = take(4 * (size_t)L.n_tile_ctr);
+    L.part = take(4 * L.part_floats);
     L.po = take(4 * (size_t)L.units * L.n_parts * L.rows_pad * c.head_dim);
     L.pml = take(4 * 2 * (size_t)L.units * L.n_parts * L.rows_pad);
     L.blk_k = take(2 * (size_t)L.units * 2 * 64 * c.head_dim);   // block K/V, split: [unit][hi, lo][64][D]
@@ -296,13 +280,11 @@ int norm_grid(int epi, int n_tiles) {
 }
 
 struct StreamPlan {
-    int mt, ct, nw, gx, gy;
+    int ct, nw, gx;
 };
 
-StreamPlan plan_stream(int epi, int M, int n_tiles) {
+StreamPlan plan_stream(int epi, int n_tiles) {
     StreamPlan p;
-    p.mt = M <= 16 ? 1 : (M <= 32 ? 2 : 4);
-    p.gy = cdiv(M, 16 * p.mt);
     if (epi == EPI_LMHEAD) {
         p.ct = 4;
         p.nw = 4;
@@ -310,10 +292,10 @@ StreamPlan plan_stream(int epi, int M, int n_tiles) {
         p.ct = 2;
         p.nw = 8;
     } else {
-        // O and down on this kernel at up to 16 rows: 16 wavefronts with every load of their 8 k-steps in
-        // flight (O at the 8B shapes: 10.8-11.0 against 11.2 us with 8 wavefronts)
+        // O and down on this kernel: 16 wavefronts with every load of their 8 k-steps in flight (O at the 8B
+        // shapes: 10.8-11.0 against 11.2 us with 8 wavefronts)
         p.ct = 1;
-        p.nw = epi == EPI_RESID && M <= 16 ? env_int("NLD_STREAM_NW_RESID", 16) : 8;
+        p.nw = epi == EPI_RESID ? env_int("NLD_STREAM_NW_RESID", 16) : 8;
     }
     p.gx = cdiv(n_tiles, p.ct);
     return p;
@@ -368,50 +350,20 @@ nld_status validate_call(const nld_model* m, const nld_kv_cache* kv, int batch, 
     return NLD_OK;
 }
 
-// The tiled GEMM takes every projection with more than 64 rows whose shape it supports.
-bool use_tile(const GemmArgs& g) {
-    return !env_int("NLD_NO_TILE_GEMM", 0) && !g.W2 && gemm_tile_supported(g.M, g.K, g.ksteps);
-}
+enum ProjKind { PROJ_O = 0, PROJ_DOWN = 1, PROJ_QKV = 2, PROJ_GU = 3, PROJ_LM = 4, PROJ_LORA = 5, N_PROJ = 6 };
 
-enum SplitKind { SK_O = 0, SK_DOWN = 1, SK_QKV = 2, SK_GU = 3 };
-
-// K slices of the tiled GEMM (M > 64): enough slices to fill every CU's workgroup slots when the
-// 128 x 128 tile groups alone leave CUs idle (O, down and QKV at a few hundred rows; gate/up has
-// several groups per CU already), each slice at least two stages of 64 k.
-// NLD_TILE_KSPLIT_<O|DOWN|QKV|GU> overrides the count (1: off).
-int plan_tile_ksplit(int kind, const GemmArgs& g, const Layout& L) {
-    static const char* names[] = {"NLD_TILE_KSPLIT_O", "NLD_TILE_KSPLIT_DOWN", "NLD_TILE_KSPLIT_QKV",
-                                  "NLD_TILE_KSPLIT_GU"};
-    const int groups = gemm_tile_groups(g.M, g.n_tiles);
-    int ks = kind == SK_GU ? 1 : std::max(1, gemm_tile_wgs_per_cu() * device_cus() / groups);
-    ks = env_int(names[kind], ks);
-    ks = std::min(ks, std::min(gemm_tile_stages(g.ksteps) / 2, 8));
-    if (ks <= 1 || groups > L.n_tk_ctr || groups * ks > L.tk_part_wgs) return 1;
-    return ks;
-}
-
-hipError_t tile_gemm(int kind, int epi, const GemmArgs& g, void* ws, const Layout& L, hipStream_t s) {
-    const int ks = epi == EPI_LMHEAD ? 1 : plan_tile_ksplit(kind, g, L);
-    if (ks == 1) return launch_gemm_tile(epi, g, 1, nullptr, nullptr, s);
-    return launch_gemm_tile(epi, g, ks, at<float>(ws, L.tk_part), at<unsigned>(ws, L.tile_ctr) + L.tk_ctr0, s);
-}
-
-// Split-K plan of a projection with at most 64 rows: ct column tiles per workgroup and
+// Split-K plan of a projection with at most 16 rows: ct column tiles per workgroup and
 // ksplit K slices, so that column groups x slices is at most one workgroup per CU, with
 // every wavefront (8 per workgroup) getting at least two k-steps.  Defaults per
-// projection (measured on MI355X at the 8B shapes): up to 16 rows down 2 tiles, O off (the
-// streamed GEMM, 11.3 against 12.9 us), QKV and gate/up off (the normed multi-tile kernel is
-// faster there); 17..64 rows every projection 4 tiles, except QKV at 17..32 rows, 3 tiles (taken
-// there before the normed multi-tile kernel).  Environment overrides:
-// NLD_SPLITK_<O|DOWN|QKV|GU> = "ct,ksplit" ("ct,0": ksplit from the rule; "0": off),
+// projection (measured on MI355X at the 8B shapes): down 2 tiles, O off (the streamed GEMM,
+// 11.3 against 12.9 us), QKV off (the normed multi-tile kernel is faster).  Environment overrides:
+// NLD_SPLITK_<O|DOWN|QKV> = "ct,ksplit" ("ct,0": ksplit from the rule; "0": off),
 // NLD_SPLITK / NLD_SPLITK_CT for every projection at once, NLD_NO_SPLITK = 1: off.
-
 bool plan_splitk(int kind, int epi, const GemmArgs& g, const Layout& L, int* ct, int* ksplit) {
-    if (g.W2 || L.n_sk_ctr == 0 || env_int("NLD_NO_SPLITK", 0)) return false;
-    static const char* names[] = {"NLD_SPLITK_O", "NLD_SPLITK_DOWN", "NLD_SPLITK_QKV", "NLD_SPLITK_GU"};
-    // column tiles per workgroup: up to 16 rows; 17..32 rows; 33..64 rows
-    static const int dflt_ct[3][4] = {{0, 2, 0, 0}, {4, 4, 3, 4}, {4, 4, 4, 4}};
-    int c = dflt_ct[g.M <= 16 ? 0 : (g.M <= 32 ? 1 : 2)][kind], ks = 0;
+    if (g.W2 || env_int("NLD_NO_SPLITK", 0)) return false;
+    static const char* names[] = {"NLD_SPLITK_O", "NLD_SPLITK_DOWN", "NLD_SPLITK_QKV"};
+    static const int dflt_ct[] = {0, 2, 0};
+    int c = dflt_ct[kind], ks = 0;
     const char* v = getenv(names[kind]);
     if (v && *v) {
         c = atoi(v);
@@ -423,79 +375,108 @@ bool plan_splitk(int kind, int epi, const GemmArgs& g, const Layout& L, int* ct,
     if (c <= 0 || !gemm_splitk_supported(epi, g.M, c)) return false;
     const int groups = cdiv(g.n_tiles, c);
     if (ks <= 0) ks = std::min(std::max(1, device_cus() / groups), std::max(1, g.ksteps / 16));
-    if (groups > L.n_sk_ctr) ks = 1;   // no counters (and no partials) for that many groups
+    if (groups > L.n_ctr) ks = 1;   // no counters (and no partials) for that many groups
     *ct = c;
     *ksplit = std::max(1, std::min(std::min(ks, SPLITK_MAX), g.ksteps));
     return true;
 }
 
-// The multi-tile GEMM of 17..64 rows when it applies (counters and partials fit the
-// workspace); returns false otherwise.
-bool try_normk(int epi, GemmArgs& g, void* ws, const Layout& L, hipStream_t s, int* parts_out, hipError_t* err) {
-    if (L.n_nk_ctr == 0 || !gemm_normk_supported(epi, g.M) || g.W2 || env_int("NLD_NO_NORMK", 0)) return false;
-    const int slices = cdiv(g.ksteps, gemm_normk_kstep_span(g.M));
-    if (g.n_tiles > L.n_nk_ctr || cdiv(g.n_tiles, gemm_normk_max_tiles()) * slices > L.lm_parts ||
-        (size_t)g.n_tiles * slices * (g.M > 32 ? 4 : 2) * 256 > L.nk_part_floats)
-        return false;
-    // about one workgroup per CU; the LM head writes one argmax key per row and workgroup (at most
-    // lm_parts per row)
-    int gx = std::max(cdiv(g.n_tiles, gemm_normk_max_tiles()), std::max(1, device_cus() / slices));
-    if (epi == EPI_LMHEAD) gx = std::min(gx, std::max(1, L.lm_parts / slices));
-    g.n_parts = gx * slices;
-    if (parts_out) *parts_out = g.n_parts;
-    *err = launch_gemm_normk(epi, gx, g, at<float>(ws, L.nk_part), at<unsigned>(ws, L.tile_ctr) + L.nk_ctr0, s);
-    return true;
+// Panel GEMM (M > 16): workgroup shape and K slices of one projection, the cheapest by an estimate in
+// microseconds from rates measured on this part: weights 6.3 TB/s from HBM with every CU reading (32 GB/s
+// into one CU), operand and re-read weights 80 GB/s per CU from L2, which add up; MFMA at 80% of 1024 flops
+// per cycle and SIMD, LDS 128 bytes per cycle; slices 1.5 us to meet and 0.6 us each, their partials written at
+// 5 TB/s in all and read back by one CU at 60 GB/s.  Against a sweep of every shape and slice count at the 8B shapes (32,
+// 64, 100, 512 rows) and the 14B ones (256) the picked plan is within 4% of the fastest one, for the LM
+// head of a short vocabulary within 10%.
+// NLD_PANEL_<O|DOWN|QKV|GU|LM|LORA> = "shape,slices" overrides a plan; NLD_TILE_KSPLIT_<O|DOWN|QKV|GU> (more
+// than 64 rows) and NLD_SPLITK (17..64) the slices alone.
+struct PanelPlan {
+    int shape = 0, ksplit = 1;
+};
+
+PanelPlan plan_panel(int kind, int M, int n_tiles, int K, const Layout& L) {
+    static const char* names[] = {"NLD_PANEL_O", "NLD_PANEL_DOWN", "NLD_PANEL_QKV", "NLD_PANEL_GU", "NLD_PANEL_LM", "NLD_PANEL_LORA"};
+    static const char* slices[] = {"NLD_TILE_KSPLIT_O", "NLD_TILE_KSPLIT_DOWN", "NLD_TILE_KSPLIT_QKV", "NLD_TILE_KSPLIT_GU", "", ""};
+    const double cus = device_cus(), cyc = 2.2e3;   // cycles per microsecond
+    const int rt = M <= 32 ? 2 : (M <= 64 ? 4 : 8), full = K / 32, R = cdiv(M, 16 * rt);
+    int want = kind < PROJ_LM ? env_int(M > 64 ? slices[kind] : "NLD_SPLITK", 0) : 0, only = -1;
+    if (const char* force = getenv(names[kind])) {
+        only = atoi(force);
+        const char* comma = strchr(force, ',');
+        want = comma ? atoi(comma + 1) : 1;
+    }
+    PanelPlan best;
+    double best_us = -1.0;
+    for (int i = 0; i < gemm_panel_shapes(); ++i) {
+        const PanelShape p = gemm_panel_shape(i);
+        if (p.rt != rt || (kind == PROJ_LORA && !gemm_panel_narrow(p)) || (only >= 0 && i != only)) continue;
+        const int wt = p.wc * p.ct, C = cdiv(n_tiles, wt), nst = full / p.kb;
+        // at least two stages per slice (an override: one), two workgroups per CU, counters and partials for all
+        int most = std::max(1, std::min(want > 0 ? std::min(want, nst) : nst / 2, 16));
+        if (R * C > L.n_ctr) most = 1;
+        while (most > 1 && ((size_t)R * C * most > 2 * cus || (size_t)R * C * most * 256 * rt * wt > L.part_floats)) --most;
+        for (int ks = want > 0 ? most : 1; ks <= most; ++ks) {
+            const size_t wgs = (size_t)R * C * ks;
+            const double rounds = ceil(wgs / cus), steps = rounds * cdiv(std::max(nst, 1), ks) * p.kb;
+            const double mfma = steps * rt * wt * 8 / 0.8 / cyc, lds = steps * (p.wc * 2 * rt + 2 * rt) * 8 / cyc;
+            const double hbm = std::max((double)n_tiles * full * 1024 / 6.3e6, steps * wt * 1024 / 32e3);
+            const double l2 = steps * (rt * 2048 + (R > 1 ? wt * 1024 : 0)) / 80e3;
+            const double tile = 1024.0 * rt * wt;
+            const double meet = ks > 1 ? 1.5 + wgs * tile / 5e6 + (ks - 1) * (0.6 + tile / 60e3) : 0.0;
+            const double us = std::max(std::max(mfma, lds), hbm + l2) + meet;
+            if (best_us < 0.0 || us < best_us) {
+                best.shape = i;
+                best.ksplit = ks;
+                best_us = us;
+            }
+        }
+    }
+    return best;
 }
 
-// Residual projections (O, down): the tiled GEMM when it applies, the split-K GEMM for up to
-// 64 rows, else the streamed one.  (The multi-tile GEMM of 17..64 rows with the residual
-// epilogue was slower at 56 rows: down 60.5 against 35.1 us, its 12 K slices' partials
-// dominating.)
-hipError_t resid_gemm(int kind, const GemmArgs& g, void* ws, const Layout& L, hipStream_t s) {
-    if (use_tile(g)) return tile_gemm(kind, EPI_RESID, g, ws, L, s);
+// groups (optional): column groups, the LM head's argmax partials and a residual projection's sums of
+// squares per row
+hipError_t panel_gemm(int epi, const PanelPlan& p, GemmArgs& g, void* ws, const Layout& L, hipStream_t s, int* groups) {
+    const PanelShape sh = gemm_panel_shape(p.shape);
+    g.n_parts = cdiv(g.n_tiles, sh.wc * sh.ct);
+    if (groups) *groups = g.n_parts;
+    return launch_gemm_panel(epi, p.shape, g, p.ksplit, at<float>(ws, L.part), at<unsigned>(ws, L.tile_ctr) + L.ctr0, s);
+}
+
+// Residual projections (O, down): the panel GEMM above 16 rows, else the split-K GEMM (down) or the streamed
+// one.  n_ss: sums of squares per row the projection writes for the next RMSNorm.
+hipError_t resid_gemm(int kind, const PanelPlan* plans, GemmArgs& g, void* ws, const Layout& L, hipStream_t s, int* n_ss) {
+    if (g.M > 16) return panel_gemm(EPI_RESID, plans[kind], g, ws, L, s, n_ss);
+    *n_ss = g.n_tiles;
     int ct = 0, ksplit = 0;
     if (plan_splitk(kind, EPI_RESID, g, L, &ct, &ksplit))
-        return launch_gemm_splitk(EPI_RESID, ct, ksplit, g, at<float>(ws, L.sk_part),
-                                  at<unsigned>(ws, L.tile_ctr) + L.sk_ctr0, s);
-    StreamPlan p = plan_stream(EPI_RESID, g.M, g.n_tiles);
+        return launch_gemm_splitk(EPI_RESID, ct, ksplit, g, at<float>(ws, L.part), at<unsigned>(ws, L.tile_ctr) + L.ctr0, s);
+    StreamPlan p = plan_stream(EPI_RESID, g.n_tiles);
     if (g.W2) p.nw = 8;   // the second source's k-steps need the 8-wavefront kernel's registers
-    return launch_gemm_stream(EPI_RESID, p.mt, p.ct, p.nw, p.gx, p.gy, g, s);
+    return launch_gemm_stream(EPI_RESID, p.ct, p.nw, p.gx, g, s);
 }
 
-// One projection whose operand is RMSNorm(x) (QKV, gate/up, LM head): the normed
-// multi-tile kernel for M <= 16, else the streamed kernel (both read the bf16
+// One projection whose operand is RMSNorm(x) (QKV, gate/up, LM head): the panel GEMM above 16 rows, else the
+// normed multi-tile kernel where it divides the reduction, else the streamed kernel (all read the split
 // operand and the row statistics the producer of x wrote).
-hipError_t normed_gemm(int epi, GemmArgs g, void* ws, const Layout& L, hipStream_t s, int* parts_out) {
+hipError_t normed_gemm(int kind, int epi, const PanelPlan* plans, GemmArgs g, void* ws, const Layout& L, hipStream_t s,
+                       int* parts_out) {
     g.A = at<uint16_t>(ws, L.xg);
     g.part_ss = at<float>(ws, L.part_ss);
-    g.n_ss = g.K / 16;
+    if (g.M > 16) return panel_gemm(epi, plans[kind], g, ws, L, s, parts_out);
     int ks = 0, waves = 0, ct = 0, ksplit = 0;
-    hipError_t err = hipSuccess;
-    // QKV of 17..32 rows: the split-K GEMM, 3 column tiles x 2 K slices per workgroup (8B shapes at
-    // k = 32: 23.6 against 25.2 us for the multi-tile kernel)
-    if (epi == EPI_QKV && g.M > 16 && g.M <= 32 && plan_splitk(SK_QKV, epi, g, L, &ct, &ksplit))
-        return launch_gemm_splitk(epi, ct, ksplit, g, at<float>(ws, L.sk_part),
-                                  at<unsigned>(ws, L.tile_ctr) + L.sk_ctr0, s);
-    if (try_normk(epi, g, ws, L, s, parts_out, &err)) return err;   // 17..64 rows
-    if ((epi == EPI_QKV || (epi == EPI_SWIGLU && g.M > 16)) &&
-        plan_splitk(epi == EPI_QKV ? SK_QKV : SK_GU, epi, g, L, &ct, &ksplit))
-        return launch_gemm_splitk(epi, ct, ksplit, g, at<float>(ws, L.sk_part),
-                                  at<unsigned>(ws, L.tile_ctr) + L.sk_ctr0, s);
+    if (epi == EPI_QKV && plan_splitk(PROJ_QKV, epi, g, L, &ct, &ksplit))
+        return launch_gemm_splitk(epi, ct, ksplit, g, at<float>(ws, L.part), at<unsigned>(ws, L.tile_ctr) + L.ctr0, s);
     if (plan_norm(epi, g.M, g.ksteps, &ks, &waves)) {
         const int grid = norm_grid(epi, g.n_tiles);
         if (parts_out) *parts_out = grid;
         g.n_parts = grid;
         return launch_gemm_norm(epi, ks, waves, grid, g, s);
     }
-    if (use_tile(g)) {
-        g.n_parts = gemm_tile_parts(g.n_tiles);
-        if (parts_out) *parts_out = g.n_parts;
-        return tile_gemm(epi == EPI_QKV ? SK_QKV : SK_GU, epi, g, ws, L, s);
-    }
-    const StreamPlan p = plan_stream(epi, g.M, g.n_tiles);
+    const StreamPlan p = plan_stream(epi, g.n_tiles);
     if (parts_out) *parts_out = p.gx;
     g.n_parts = p.gx;
-    return launch_gemm_stream(epi, p.mt, p.ct, p.nw, p.gx, p.gy, g, s);
+    return launch_gemm_stream(epi, p.ct, p.nw, p.gx, g, s);
 }
 
 nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int k, const PassIO& io, void* ws,
@@ -525,7 +506,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
     e.status = status;
     e.rope = at<float2>(ws, L.rope);
     e.tile_ctr = at<unsigned>(ws, L.tile_ctr);
-    e.n_tile_ctr = 2 * c.n_layers + 1 + L.n_sk_ctr + L.n_nk_ctr + L.n_tk_ctr;
+    e.n_tile_ctr = L.n_tile_ctr;
     e.lengths = kv->lengths;
     e.max_len = kv->max_len;
     e.head_dim = c.head_dim;
@@ -538,7 +519,18 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
         HIP_TRY(launch_embed(e, s));
     }
 
+    int n_ss = EMBED_SS;   // sums of squares per row in part_ss, as its latest producer wrote them
     const int ks_h = cdiv(c.hidden, 32), ks_q = cdiv(nq * D, 32), ks_f = cdiv(c.ffn, 32);
+    const bool lora = io.mode == NLD_MODE_DRAFT && c.lora_rank > 0;
+    PanelPlan plans[N_PROJ];   // the same for every layer
+    if (M > 16) {
+        plans[PROJ_O] = plan_panel(PROJ_O, M, c.hidden / 16, nq * D, L);
+        plans[PROJ_DOWN] = plan_panel(PROJ_DOWN, M, c.hidden / 16, c.ffn, L);
+        plans[PROJ_QKV] = plan_panel(PROJ_QKV, M, (nq + 2 * nkv) * D / 16, c.hidden, L);
+        plans[PROJ_GU] = plan_panel(PROJ_GU, M, cdiv(c.ffn, 8), c.hidden, L);
+        plans[PROJ_LM] = plan_panel(PROJ_LM, M, L.lm_tiles, c.hidden, L);
+        if (lora) plans[PROJ_LORA] = plan_panel(PROJ_LORA, M, c.lora_rank / 16, nq * D, L);
+    }
     for (int l = 0; l < c.n_layers; ++l) {
         const nld_layer_weights& W = mdl->layers[l];
         uint16_t* kc = (uint16_t*)kv->k + (size_t)l * kv_layer;
@@ -546,6 +538,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
 
         GemmArgs g{};
         g.eps = c.rms_eps;
+        g.n_ss = n_ss;
         g.M = M;
         g.K = c.hidden;
         g.W = (const uint4*)W.w_qkv;
@@ -571,7 +564,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
         g.plain = plain & (SITE_Q | SITE_KV);
         {
             TraceScope ts(NLD_TRACE_QKV, s);
-            HIP_TRY(normed_gemm(EPI_QKV, g, ws, L, s, nullptr));
+            HIP_TRY(normed_gemm(PROJ_QKV, EPI_QKV, plans, g, ws, L, s, nullptr));
         }
         if (io.kv_only && l == c.n_layers - 1) break;   // every layer's K/V rows are written
 
@@ -619,7 +612,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
         go.W = (const uint4*)W.w_o;
         go.n_tiles = c.hidden / 16;
         go.ksteps = ks_q;
-        if (io.mode == NLD_MODE_DRAFT && c.lora_rank > 0) {
+        if (lora) {
             // LoRA down-projection t = lora_scale * (A o), split; the O projection then takes
             // B as lora_rank / 32 more k-steps against t
             GemmArgs gt{};
@@ -633,8 +626,12 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
             gt.out_scale = c.lora_scale;
             {
                 TraceScope ts(NLD_TRACE_O_PROJ, s);
-                const StreamPlan p = plan_stream(EPI_SPLIT, M, gt.n_tiles);
-                HIP_TRY(launch_gemm_stream(EPI_SPLIT, p.mt, p.ct, p.nw, p.gx, p.gy, gt, s));
+                if (M > 16) {
+                    HIP_TRY(panel_gemm(EPI_SPLIT, plans[PROJ_LORA], gt, ws, L, s, nullptr));
+                } else {
+                    const StreamPlan p = plan_stream(EPI_SPLIT, gt.n_tiles);
+                    HIP_TRY(launch_gemm_stream(EPI_SPLIT, p.ct, p.nw, p.gx, gt, s));
+                }
             }
             go.W2 = (const uint4*)W.lora_b;
             go.A2 = at<uint16_t>(ws, L.lora_t);
@@ -647,11 +644,12 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
         go.plain = plain & SITE_NORM;
         {
             TraceScope ts(NLD_TRACE_O_PROJ, s);
-            HIP_TRY(resid_gemm(SK_O, go, ws, L, s));
+            HIP_TRY(resid_gemm(PROJ_O, plans, go, ws, L, s, &n_ss));
         }
 
         GemmArgs gu{};
         gu.eps = c.rms_eps;
+        gu.n_ss = n_ss;
         gu.M = M;
         gu.K = c.hidden;
         gu.W = (const uint4*)W.w_gate_up;
@@ -663,7 +661,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
         gu.plain = plain & SITE_ACT;
         {
             TraceScope ts(NLD_TRACE_GATE_UP, s);
-            HIP_TRY(normed_gemm(EPI_SWIGLU, gu, ws, L, s, nullptr));
+            HIP_TRY(normed_gemm(PROJ_GU, EPI_SWIGLU, plans, gu, ws, L, s, nullptr));
         }
 
         GemmArgs gd{};
@@ -680,7 +678,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
         gd.plain = plain & (l + 1 < c.n_layers ? SITE_NORM : SITE_FINAL);
         {
             TraceScope ts(NLD_TRACE_DOWN, s);
-            HIP_TRY(resid_gemm(SK_DOWN, gd, ws, L, s));
+            HIP_TRY(resid_gemm(PROJ_DOWN, plans, gd, ws, L, s, &n_ss));
         }
     }
 
@@ -705,6 +703,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
     GemmArgs gl{};
     gl.tile_ctr = at<unsigned>(ws, L.tile_ctr) + 2 * c.n_layers;
     gl.eps = c.rms_eps;
+    gl.n_ss = n_ss;
     gl.M = M;
     gl.K = c.hidden;
     gl.W = (const uint4*)mdl->w.lm_head;
@@ -721,7 +720,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
     int parts = 0;
     {
         TraceScope ts(NLD_TRACE_LM_HEAD, s);
-        HIP_TRY(normed_gemm(EPI_LMHEAD, gl, ws, L, s, &parts));
+        HIP_TRY(normed_gemm(PROJ_LM, EPI_LMHEAD, plans, gl, ws, L, s, &parts));
     }
 
     fa.part_keys = at<unsigned long long>(ws, L.keys);

@@ -11,22 +11,23 @@
 //         -> LM-head GEMM (final RMSNorm fused; per-workgroup argmax keys)
 //         -> per-sequence argmax + draft extraction / acceptance.
 //
-// The GEMMs are skinny (M = batch*k rows, usually 8..32): bound by streaming the
-// bf16 weights from HBM.  Weights are pre-packed so that one 16-byte load per
+// The GEMMs are skinny (M = batch*k rows, from one to a few hundred): up to about a
+// hundred rows they are bound by streaming the bf16 weights from HBM.  Weights are pre-packed so that one 16-byte load per
 // lane of a wavefront is exactly one MFMA B operand (1 KiB contiguous per
 // wavefront load).
 //
 // Communication between workgroups of one launch.  The normed GEMM hands out
-// tiles from a counter.  The split-K GEMM, the 17..64-row normed GEMM and the
-// tiled GEMM with K slices meet through last-arriver counters; no workgroup ever
-// waits for another.  The protocol of a slice partial:
-//   1. every lane writes its part with agent-scope relaxed atomic stores;
+// tiles from a counter.  The split-K GEMM and the panel GEMM with K slices meet
+// through last-arriver counters; no workgroup ever waits for another.  The protocol
+// of a slice partial:
+//   1. every lane writes its part with agent-scope stores (relaxed atomics, or
+//      16-byte buffer stores with the same cache bits);
 //   2. s_waitcnt(0): the wavefront waits until each of its stores is
 //      acknowledged, then a workgroup barrier;
 //   3. one thread adds 1 to the counter (agent-scope relaxed fetch_add); the
 //      workgroup that reads ksplit - 1 is the last to arrive;
 //   4. the last arriver resets the counter to 0, reads the other partials with
-//      agent-scope relaxed atomic loads, adds the slices in slice order (so the
+//      agent-scope loads, adds the slices in slice order (so the
 //      sum does not depend on who arrived last) and runs the epilogue.
 // Why this orders the data: agent-scope stores are made visible at agent scope
 // (past the XCD-local L2) by the time they are acknowledged, so after step 2
@@ -392,266 +393,13 @@ hipError_t launch_gemm_norm(int epi, int ks, int waves, int grid, const GemmArgs
 }
 
 // =====================================================================================
-// Normed multi-tile GEMM for 17..64 rows (QKV, gate/up, LM head of a pass with two or four
-// row tiles, such as the quadratic self-speculation pass).  The operand of MT row tiles is
-// too large to reload per column tile (the split operand is 2 KB per row tile and k-step,
-// against 1 KB of weights per column tile), so a workgroup of 8 wavefronts holds one K
-// slice of it in registers for every column tile it multiplies: wavefront w owns k-steps
-// [(ks*8 + w)*KS, +KS) of slice ks = blockIdx.y.  Workgroup x of a slice takes column tiles
-// x, x + gridDim.x, ...; their weights stream through PF register buffers, each refilled
-// with the tile PF ahead as soon as it has been multiplied.  Per tile the wavefronts'
-// products meet in LDS and the slice's partial goes to the workspace with agent-scope
-// stores.  After its last tile the workgroup counts itself in on each tile's counter; the
-// workgroup that completes a tile reads the slices' partials in slice order and runs the
-// epilogue (wavefront w takes row tile w % MT of every (8/MT)-th completed tile), then
-// resets the counter.
-// =====================================================================================
-constexpr int NK_MAXT = 160;   // column tiles per workgroup (the host keeps ceil(n_tiles / grid.x) within it)
-
-template <int MT, int KS, int PF, int EPI>
-__global__ void __launch_bounds__(512) gemm_normk_kernel(GemmArgs a, float* part, unsigned* tctr, int ksplit) {
-    constexpr int NW = 8;
-    constexpr int WPR = NW / MT;   // wavefronts per row tile in the epilogue
-    static_assert(NW % MT == 0, "row tiles must divide the wavefronts");
-    __shared__ f32x4_t red[2][NW][MT][64];
-    __shared__ float inv_s[16 * MT];
-    __shared__ unsigned char last_s[NK_MAXT];
-    __shared__ int fin_s[NK_MAXT];
-    __shared__ int nfin_s;
-    __shared__ unsigned long long key_s[NW][16];
-    __shared__ float2 lse_s[NW][16];
-    typedef unsigned long long u64;
-    constexpr int TLC = EPI == EPI_QKV ? TL_QKV : (EPI == EPI_SWIGLU ? TL_GATE_UP : TL_LM);
-    NLD_TS(TLC, 0);
-
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int r = lane & 15, g = lane >> 4;
-    const int x = blockIdx.x, Gx = gridDim.x, ks = blockIdx.y;
-    const int T = a.n_tiles;
-    const int nt = x < T ? (T - 1 - x) / Gx + 1 : 0;
-    const int s0 = (ks * NW + wave) * KS;
-    const uint4 zero4 = {0u, 0u, 0u, 0u};
-
-    // this wavefront's operand slice, hi and lo, for every row tile
-    uint4 ah[MT][KS], al[MT][KS];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            const int ss = s0 + s;
-            const bool ok = mt * 16 + r < a.M && ss < a.ksteps && ss * 32 + 8 * g < a.K;
-            const uint16_t* ap = a.A + (size_t)(mt * a.ksteps + ss) * 1024 + (size_t)lane * 8;
-            ah[mt][s] = zero4;
-            al[mt][s] = zero4;
-            if (ok) {
-                ah[mt][s] = *(const uint4*)ap;
-                al[mt][s] = *(const uint4*)(ap + SPLIT_LO);
-            }
-        }
-
-    rms_scales(a, 0, 16 * MT, inv_s);   // visible after the first barrier below
-    if constexpr (EPI == EPI_LMHEAD) {
-        if (threadIdx.x < NW * 16) {
-            key_s[threadIdx.x / 16][threadIdx.x % 16] = 0ull;
-            lse_s[threadIdx.x / 16][threadIdx.x % 16] = float2{-INFINITY, 0.f};
-        }
-    }
-    if (nt == 0) return;   // no column tile here (the whole workgroup leaves; the LM head writes no key)
-
-    // Per tile, every wavefront stores EL elements of one row tile's partial: row tile w % MT,
-    // elements (w / MT) * EL .. +EL of each lane's four (one 8-byte store, or one 4-byte store).
-    constexpr int EL = 4 / WPR;
-    static_assert(EL == 1 || EL == 2, "one 4- or 8-byte partial store per wavefront and tile");
-    const int st_mt = wave % MT, st_e0 = (wave / MT) * EL;
-    auto store_part = [&](int t, f32x4_t v) __attribute__((always_inline)) {
-        float* pp = part + ((((size_t)t * ksplit + ks) * MT + st_mt) * 64 + lane) * 4 + st_e0;
-        if constexpr (EL == 2)
-            __hip_atomic_store((u64*)pp, __builtin_bit_cast(u64, f32x2_t{v[st_e0], v[st_e0 + 1]}), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        else
-            __hip_atomic_store(pp, v[st_e0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-
-    // Weight loads are unconditional, with the tile and the k-step clamped into the matrix (a
-    // k-step past the end meets a zero operand; a tile past the workgroup's last is never
-    // multiplied).  Each buffer's loads are followed by one partial store, here a zero into the
-    // first tile's slot that its real partial overwrites later, so that the prologue leaves the
-    // same sequence of outstanding loads and stores as a loop iteration: the wait counts then
-    // stay exact and the next PF tiles' loads remain in flight across the loop.
-    const int s_last = a.ksteps - 1;
-    uint4 wb[PF][KS];
-#pragma unroll
-    for (int p = 0; p < PF; ++p) {
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-            wb[p][s] = load_stream(a.W + ((size_t)min(x + p * Gx, T - 1) * a.ksteps + min(s0 + s, s_last)) * 64 + lane);
-        store_part(x, f32x4_t{0.f, 0.f, 0.f, 0.f});
-    }
-
-    // epilogue of row tile mt of tile t from its full sum v (lane layout of an MFMA result);
-    // LM head: the row maxima and statistics accumulate per wavefront in LDS (rows 4g + i)
-    auto epilogue = [&](f32x4_t v, int t, int mt) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int m = 16 * mt + 4 * g + i;
-            const float y = v[i] * inv_s[m];
-            if constexpr (EPI == EPI_QKV) {
-                const int mc = min(m, a.M - 1);
-                const int pos = committed_length(a.lengths, mc / a.k_blk, a.max_len, a.status) + mc % a.k_blk;
-                epi_qkv(a, y, m, t, lane, pos);
-            } else if constexpr (EPI == EPI_SWIGLU) {
-                epi_swiglu(a, y, m, t, lane);
-            } else {
-                float2 tl;
-                const u64 key = epi_lmhead(a, y, m, t, lane, &tl);
-                if (r == 0) {
-                    key_s[wave][4 * g + i] = umax64(key_s[wave][4 * g + i], key);
-                    if (a.part_lse) lse_s[wave][4 * g + i] = lse_merge(lse_s[wave][4 * g + i], tl);
-                }
-            }
-        }
-    };
-
-    // tile j (the workgroup's j-th) from buffer p, whose next tile is j + PF
-    auto tile = [&](int j, int p_dummy, uint4 (&w)[KS]) __attribute__((always_inline)) {
-        (void)p_dummy;
-        const int t = x + j * Gx;
-        f32x4_t acc[MT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        const int tn = min(x + (j + PF) * Gx, T - 1);
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                acc[mt] = mfma_16x16x32(ah[mt][s], w[s], acc[mt]);
-                acc[mt] = mfma_16x16x32(al[mt][s], w[s], acc[mt]);
-            }
-            w[s] = load_stream(a.W + ((size_t)tn * a.ksteps + min(s0 + s, s_last)) * 64 + lane);
-        }
-        const int par = j & 1;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) red[par][wave][mt][lane] = acc[mt];
-        __syncthreads();
-        // the slice's partial: this wavefront's elements of row tile st_mt (fixed order over
-        // the wavefronts)
-        f32x4_t v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int w2 = 0; w2 < NW; ++w2) v += red[par][w2][st_mt][lane];
-        store_part(t, v);
-    };
-    // whole groups of PF tiles with no condition inside, so the loop keeps one shape; then the rest
-    int j0 = 0;
-    for (; j0 + PF <= nt; j0 += PF) {
-#pragma unroll
-        for (int p = 0; p < PF; ++p) tile(j0 + p, p, wb[p]);
-    }
-#pragma unroll
-    for (int p = 0; p < PF - 1; ++p)
-        if (j0 + p < nt) tile(j0 + p, p, wb[p]);
-
-    NLD_TS(TLC, 1);   // main loop done
-    {   // the tiles this workgroup completes (with a single slice: all of its own)
-        // every lane's partial stores are acknowledged before the workgroup counts itself in
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __builtin_amdgcn_s_waitcnt(0);
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __syncthreads();
-        for (int j = threadIdx.x; j < nt; j += blockDim.x)
-            last_s[j] = __hip_atomic_fetch_add(tctr + x + j * Gx, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                        (unsigned)(ksplit - 1);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int n = 0;
-            for (int j = 0; j < nt; ++j)
-                if (last_s[j]) fin_s[n++] = x + j * Gx;
-            nfin_s = n;
-        }
-        __syncthreads();
-        const int nfin = nfin_s;
-        for (int c = threadIdx.x; c < nfin; c += blockDim.x)
-            __hip_atomic_exchange(tctr + fin_s[c], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // wavefront w: row tile w % MT of completed tiles w / MT, + WPR, ...; two tiles' partials in flight
-        const int mt = wave % MT;
-        for (int c = wave / MT; c < nfin; c += 2 * WPR) {
-            const int c2 = c + WPR;
-            const int ta = fin_s[c], tb = c2 < nfin ? fin_s[c2] : ta;
-            f32x4_t va = {0.f, 0.f, 0.f, 0.f}, vb = {0.f, 0.f, 0.f, 0.f};
-            for (int sl = 0; sl < ksplit; ++sl) {
-                const u64* qa = (const u64*)(part + ((((size_t)ta * ksplit + sl) * MT + mt) * 64 + lane) * 4);
-                const u64* qb = (const u64*)(part + ((((size_t)tb * ksplit + sl) * MT + mt) * 64 + lane) * 4);
-                const f32x2_t a0 = __builtin_bit_cast(f32x2_t, __hip_atomic_load(qa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                const f32x2_t a1 = __builtin_bit_cast(f32x2_t, __hip_atomic_load(qa + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                const f32x2_t b0 = __builtin_bit_cast(f32x2_t, __hip_atomic_load(qb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                const f32x2_t b1 = __builtin_bit_cast(f32x2_t, __hip_atomic_load(qb + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                va += f32x4_t{a0[0], a0[1], a1[0], a1[1]};
-                vb += f32x4_t{b0[0], b0[1], b1[0], b1[1]};
-            }
-            epilogue(va, ta, mt);
-            if (c2 < nfin) epilogue(vb, tb, mt);
-        }
-    }
-    NLD_TS(TLC, 2);   // completed tiles finished
-
-    if constexpr (EPI == EPI_LMHEAD) {
-        // one argmax key (and softmax statistics) per row for this workgroup
-        __syncthreads();
-        if ((int)threadIdx.x < 16 * MT) {
-            const int m = threadIdx.x, mt = m / 16, rl = m % 16;
-            if (m < a.M) {
-                u64 k2 = 0ull;
-                float2 st = float2{-INFINITY, 0.f};
-                for (int w = mt; w < NW; w += MT) {   // the wavefronts that finished row tile mt
-                    k2 = umax64(k2, key_s[w][rl]);
-                    st = lse_merge(st, lse_s[w][rl]);
-                }
-                const int part_id = x + Gx * ks;
-                a.part_keys[(size_t)m * a.n_parts + part_id] = k2;
-                if (a.part_lse) a.part_lse[(size_t)m * a.n_parts + part_id] = st;
-            }
-        }
-    }
-}
-
-bool gemm_normk_supported(int epi, int M) {
-    return (epi == EPI_QKV || epi == EPI_SWIGLU || epi == EPI_LMHEAD) && M > 16 && M <= 64;
-}
-
-// k-steps per slice: 8 wavefronts x 4 (four row tiles) or x 8 (two row tiles)
-int gemm_normk_kstep_span(int M) { return 8 * (M > 32 ? 4 : 8); }
-
-int gemm_normk_max_tiles() { return NK_MAXT; }
-
-template <int MT, int KS>
-static hipError_t launch_normk_mt(int epi, dim3 grid, const GemmArgs& a, float* part, unsigned* tctr, int ksplit,
-                                  hipStream_t s) {
-    constexpr int PF = MT >= 4 ? 3 : 2;   // tiles of weights in flight per wavefront (registers permitting)
-    switch (epi) {
-        case EPI_QKV: launch(gemm_normk_kernel<MT, KS, PF, EPI_QKV>, grid, dim3(512), s, a, part, tctr, ksplit); break;
-        case EPI_SWIGLU: launch(gemm_normk_kernel<MT, KS, PF, EPI_SWIGLU>, grid, dim3(512), s, a, part, tctr, ksplit); break;
-        case EPI_LMHEAD: launch(gemm_normk_kernel<MT, KS, PF, EPI_LMHEAD>, grid, dim3(512), s, a, part, tctr, ksplit); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_gemm_normk(int epi, int grid_x, const GemmArgs& a, float* part, unsigned* tctr, hipStream_t s) {
-    if (!gemm_normk_supported(epi, a.M) || grid_x < 1) return hipErrorInvalidValue;
-    if ((a.n_tiles + grid_x - 1) / grid_x > NK_MAXT) return hipErrorInvalidValue;
-    const int span = gemm_normk_kstep_span(a.M);
-    const int ksplit = (a.ksteps + span - 1) / span;
-    const dim3 grid((unsigned)grid_x, (unsigned)ksplit);
-    if (a.M > 32) return launch_normk_mt<4, 4>(epi, grid, a, part, tctr, ksplit, s);
-    return launch_normk_mt<2, 8>(epi, grid, a, part, tctr, ksplit, s);
-}
-
-// =====================================================================================
-// Streamed GEMM: out[m][n] = sum_k A[m][k] W[n][k] for 16*MT rows x 16*CT columns per
+// Streamed GEMM (up to 16 rows): out[m][n] = sum_k A[m][k] W[n][k] for 16*CT columns per
 // workgroup; the NW wavefronts split the reduction, each streaming its slice of the
 // weights and of the bf16 activations with one batch in flight ahead of the MFMAs.
-// Every operand is split (two MFMAs per weight operand).  Used for the O and down
-// projections (residual epilogue) and, for M > 16, for every projection (the
-// per-row RMSNorm scale is then formed in the prologue).
+// Every operand is split (two MFMAs per weight operand).  Used for the O projection
+// (residual epilogue, with the LoRA adapter as a second source) and for the normed
+// projections whose reduction the normed GEMM does not divide (the per-row RMSNorm scale
+// is then formed in the prologue).
 // =====================================================================================
 template <int MT, int CT, bool SPLIT, int NW = 8>
 struct Batch {
@@ -889,35 +637,24 @@ static hipError_t launch_stream_ct(int ct, int nw, dim3 grid, const GemmArgs& a,
     return hipGetLastError();
 }
 
-template <int EPI, bool XK = false>
-static hipError_t launch_stream_mt(int mt, int ct, int nw, dim3 grid, const GemmArgs& a, hipStream_t s) {
-    switch (mt) {
-        case 1: return launch_stream_ct<EPI, 1, XK>(ct, nw, grid, a, s);
-        case 2: return launch_stream_ct<EPI, 2, XK>(ct, nw, grid, a, s);
-        case 4: return launch_stream_ct<EPI, 4, XK>(ct, nw, grid, a, s);
-        default: return hipErrorInvalidValue;
-    }
-}
-
-hipError_t launch_gemm_stream(int epi, int mt, int ct, int nw, int grid_x, int grid_y, const GemmArgs& a,
-                              hipStream_t s) {
-    const dim3 grid(grid_x, grid_y);
-    if (a.W2 && epi != EPI_RESID) return hipErrorInvalidValue;
+hipError_t launch_gemm_stream(int epi, int ct, int nw, int grid_x, const GemmArgs& a, hipStream_t s) {
+    const dim3 grid(grid_x);
+    if (a.M > 16 || (a.W2 && epi != EPI_RESID)) return hipErrorInvalidValue;
     switch (epi) {
-        case EPI_QKV: return launch_stream_mt<EPI_QKV>(mt, ct, nw, grid, a, s);
+        case EPI_QKV: return launch_stream_ct<EPI_QKV, 1, false>(ct, nw, grid, a, s);
         case EPI_RESID:
-            return a.W2 ? launch_stream_mt<EPI_RESID, true>(mt, ct, nw, grid, a, s)
-                        : launch_stream_mt<EPI_RESID>(mt, ct, nw, grid, a, s);
-        case EPI_SWIGLU: return launch_stream_mt<EPI_SWIGLU>(mt, ct, nw, grid, a, s);
-        case EPI_LMHEAD: return launch_stream_mt<EPI_LMHEAD>(mt, ct, nw, grid, a, s);
-        case EPI_SPLIT: return launch_stream_mt<EPI_SPLIT>(mt, ct, nw, grid, a, s);
+            return a.W2 ? launch_stream_ct<EPI_RESID, 1, true>(ct, nw, grid, a, s)
+                        : launch_stream_ct<EPI_RESID, 1, false>(ct, nw, grid, a, s);
+        case EPI_SWIGLU: return launch_stream_ct<EPI_SWIGLU, 1, false>(ct, nw, grid, a, s);
+        case EPI_LMHEAD: return launch_stream_ct<EPI_LMHEAD, 1, false>(ct, nw, grid, a, s);
+        case EPI_SPLIT: return launch_stream_ct<EPI_SPLIT, 1, false>(ct, nw, grid, a, s);
         default: return hipErrorInvalidValue;
     }
 }
 
 // =====================================================================================
-// Split-K GEMM (O and down projections with the residual epilogue, and the normed QKV and
-// gate/up projections; M <= 64).  Workgroup (column group cg,
+// Split-K GEMM (O and down projections with the residual epilogue, and the normed QKV
+// projection; up to 16 rows).  Workgroup (column group cg,
 // K slice ks) multiplies its slice of the operand against CT column tiles, so the
 // operand is read once per CT tiles and K slice instead of once per tile (the split
 // operand is twice as large as the weights it multiplies in these projections).  The
@@ -941,21 +678,17 @@ struct SkBatch {
 
 template <int MT, int CT, int NW, int EPI>
 __global__ void __launch_bounds__(NW * 64) gemm_splitk_kernel(GemmArgs a, float* part, unsigned* ctr, int ksplit) {
-    // Up to two row tiles: separate hi and lo accumulators and batches of several k-steps.  Four row
-    // tiles: one accumulator per output tile takes both operand halves and a batch is one k-step
-    // (the registers of 16 tiles' accumulators and of 12 operand quads per k-step).
-    constexpr bool MERGE = MT >= 4;
-    constexpr int U = MERGE ? 1 : Batch<MT, CT, true>::U;
+    constexpr int U = Batch<MT, CT, true>::U;
     typedef SkBatch<MT, CT, U> B;
     constexpr int NTL = MT * CT;   // output tiles of the workgroup; wavefront w finishes tiles w, w + NW, ...
-    constexpr bool NORMED = EPI == EPI_QKV || EPI == EPI_SWIGLU;
-    static_assert(EPI == EPI_RESID || NORMED, "residual, QKV or SwiGLU epilogue");
+    constexpr bool NORMED = EPI == EPI_QKV;
+    static_assert(EPI == EPI_RESID || NORMED, "residual or QKV epilogue");
     __shared__ f32x4_t red[NW][NTL][64];
     __shared__ float inv_s[16 * MT];
     __shared__ int last_s;
     // timeline class: a residual projection whose reduction is longer than its output is the down
     // projection, otherwise the O projection
-    const int TLC = EPI == EPI_QKV ? TL_QKV : (EPI == EPI_SWIGLU ? TL_GATE_UP : (a.K > a.n_tiles * 16 ? TL_DOWN : TL_O));
+    const int TLC = EPI == EPI_QKV ? TL_QKV : (a.K > a.n_tiles * 16 ? TL_DOWN : TL_O);
     (void)TLC;
     NLD_TS(TLC, 0);
 
@@ -998,17 +731,14 @@ __global__ void __launch_bounds__(NW * 64) gemm_splitk_kernel(GemmArgs a, float*
         ap[mt] = a.A + (size_t)mt * a.ksteps * 1024 + (size_t)lane * 8;
     }
 
-    f32x4_t acc[MT][CT], accl[MERGE ? 1 : MT][MERGE ? 1 : CT];
+    f32x4_t acc[MT][CT], accl[MT][CT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) acc[mt][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    if constexpr (!MERGE) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) accl[mt][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
+        for (int ct = 0; ct < CT; ++ct) {
+            acc[mt][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            accl[mt][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
 
     const uint4 zero4 = {0u, 0u, 0u, 0u};
     auto load = [&](int s, B& buf) __attribute__((always_inline)) {
@@ -1035,8 +765,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_splitk_kernel(GemmArgs a, float*
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) {
                     acc[mt][ct] = mfma_16x16x32(buf.x[u][mt], buf.w[u][ct], acc[mt][ct]);
-                    if constexpr (MERGE) acc[mt][ct] = mfma_16x16x32(buf.xl[u][mt], buf.w[u][ct], acc[mt][ct]);
-                    else accl[mt][ct] = mfma_16x16x32(buf.xl[u][mt], buf.w[u][ct], accl[mt][ct]);
+                    accl[mt][ct] = mfma_16x16x32(buf.xl[u][mt], buf.w[u][ct], accl[mt][ct]);
                 }
     };
 
@@ -1052,10 +781,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_splitk_kernel(GemmArgs a, float*
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            if constexpr (MERGE) red[wave][mt * CT + ct][lane] = acc[mt][ct];
-            else red[wave][mt * CT + ct][lane] = acc[mt][ct] + accl[mt][ct];
-        }
+        for (int ct = 0; ct < CT; ++ct) red[wave][mt * CT + ct][lane] = acc[mt][ct] + accl[mt][ct];
     __syncthreads();
     NLD_TS(TLC, 1);   // main loop done
 
@@ -1133,216 +859,423 @@ __global__ void __launch_bounds__(NW * 64) gemm_splitk_kernel(GemmArgs a, float*
             const int m = 16 * mt + 4 * g + i;
             if constexpr (EPI == EPI_RESID) {
                 epi_resid(a, v[q][i], m, t, lane, xres[i], gn);
-            } else if constexpr (EPI == EPI_QKV) {
+            } else {
                 const int mc = min(m, a.M - 1);
                 const int pos = committed_length(a.lengths, mc / a.k_blk, a.max_len, a.status) + mc % a.k_blk;
                 epi_qkv(a, v[q][i] * inv_s[m], m, t, lane, pos);
-            } else {
-                epi_swiglu(a, v[q][i] * inv_s[m], m, t, lane);
             }
         }
     }
 }
 
 bool gemm_splitk_supported(int epi, int M, int ct) {
-    return (epi == EPI_RESID || epi == EPI_QKV || epi == EPI_SWIGLU) && M >= 1 && M <= 64 && ct >= 2 && ct <= 4;
-}
-
-template <int EPI, int CT>
-static void launch_splitk_ct(dim3 grid, int mt, const GemmArgs& a, float* part, unsigned* ctr, int ksplit,
-                             hipStream_t s) {
-    if (mt == 4) launch(gemm_splitk_kernel<4, CT, 8, EPI>, grid, dim3(512), s, a, part, ctr, ksplit);
-    else if (mt == 2) launch(gemm_splitk_kernel<2, CT, 8, EPI>, grid, dim3(512), s, a, part, ctr, ksplit);
-    else launch(gemm_splitk_kernel<1, CT, 8, EPI>, grid, dim3(512), s, a, part, ctr, ksplit);
+    return (epi == EPI_RESID || epi == EPI_QKV) && M >= 1 && M <= 16 && ct >= 2 && ct <= 4;
 }
 
 template <int EPI>
-static void launch_splitk_epi(int ct, dim3 grid, int mt, const GemmArgs& a, float* part, unsigned* ctr, int ksplit,
-                              hipStream_t s) {
-    if (ct == 4) launch_splitk_ct<EPI, 4>(grid, mt, a, part, ctr, ksplit, s);
-    else if (ct == 3) launch_splitk_ct<EPI, 3>(grid, mt, a, part, ctr, ksplit, s);
-    else launch_splitk_ct<EPI, 2>(grid, mt, a, part, ctr, ksplit, s);
+static void launch_splitk_epi(int ct, dim3 grid, const GemmArgs& a, float* part, unsigned* ctr, int ksplit, hipStream_t s) {
+    if (ct == 4) launch(gemm_splitk_kernel<1, 4, 8, EPI>, grid, dim3(512), s, a, part, ctr, ksplit);
+    else if (ct == 3) launch(gemm_splitk_kernel<1, 3, 8, EPI>, grid, dim3(512), s, a, part, ctr, ksplit);
+    else launch(gemm_splitk_kernel<1, 2, 8, EPI>, grid, dim3(512), s, a, part, ctr, ksplit);
 }
 
 hipError_t launch_gemm_splitk(int epi, int ct, int ksplit, const GemmArgs& a, float* part, unsigned* ctr,
                               hipStream_t s) {
     if (!gemm_splitk_supported(epi, a.M, ct) || a.W2 || ksplit < 1 || ksplit > SPLITK_MAX) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((a.n_tiles + ct - 1) / ct), (unsigned)ksplit);
-    const int mt = a.M > 32 ? 4 : (a.M > 16 ? 2 : 1);
-    if (epi == EPI_RESID) launch_splitk_epi<EPI_RESID>(ct, grid, mt, a, part, ctr, ksplit, s);
-    else if (epi == EPI_QKV) launch_splitk_epi<EPI_QKV>(ct, grid, mt, a, part, ctr, ksplit, s);
-    else launch_splitk_epi<EPI_SWIGLU>(ct, grid, mt, a, part, ctr, ksplit, s);
+    if (epi == EPI_RESID) launch_splitk_epi<EPI_RESID>(ct, grid, a, part, ctr, ksplit, s);
+    else launch_splitk_epi<EPI_QKV>(ct, grid, a, part, ctr, ksplit, s);
     return hipGetLastError();
 }
 
 // =====================================================================================
-// Tiled GEMM for many rows (M > 64), where the projections approach the MFMA ridge: a
-// workgroup computes a 128-row x 128-column output tile over the whole reduction, so the
-// weights stream once per 128 rows and the operand once per 128 columns.  Per stage of
-// two k-steps the operand's eight row tiles (split: hi and lo) and the weights' eight
-// column tiles are copied into LDS, double buffered, with the next stage's global loads
-// in flight in registers while the current one is multiplied.  Wavefront w multiplies
-// row tiles 2(w/2), +1 against column tiles 4(w%2) .. +3 (8 MFMAs per operand half and
-// k-step).  Workgroups are ordered so that the row groups sharing a column group run
-// next to each other on one XCD (workgroup b runs on XCD b % 8) and find its weight
-// tiles in that XCD's L2.  Epilogues as in the other GEMMs.
+// Panel GEMM: every projection of a pass with more than 16 rows.  A workgroup of 8 wavefronts
+// computes 16*RT rows x 16*WC*CT columns over one K slice: WC wavefronts side by side, each with
+// CT column tiles against all RT row tiles, times WK = 8 / WC wavefront groups that take the
+// k-steps of a stage in turn and meet in LDS at the end.
+//
+// What bounds it and why this split.  A CU takes in about 25 GB/s of weights while all 256 stream
+// from HBM and about 95 GB/s from L2, and the two add up: the time is close to weights / 6.3 TB/s +
+// operand bytes per CU / 95 GB/s.  So the split operand (2 KiB per row tile and k-step, twice a
+// weight tile) goes through LDS once per workgroup and is shared by wavefronts that lie side by side
+// in columns; each weight block has one reader and goes straight to that wavefront's registers.  A
+// wavefront's RT x CT tile also sets the LDS rate: it reads 2 RT KiB per k-step for RT*CT pairs of
+// MFMAs, so CT = 3 at RT = 8 keeps the matrix cores ahead of LDS (8 x 2 just matches it).  Two
+// wavefronts per SIMD cover each other's barrier and LDS latency (four wavefronts of 8 x 6 tiles:
+// 176 us against 154 for gate/up at 512 rows).
+//
+// Stages are KB k-steps.  Stage s is multiplied from LDS slot s & 1 and weight registers s & 1;
+// a weight block's register is refilled with its stage s + 2 as soon as it has been multiplied, and
+// the operand of stage s + 1 (loaded two stages before) is stored to the other slot while stage s is
+// multiplied.  The weights are the MFMA's A operand, so a lane ends up with four neighbouring columns
+// of one row (lane 16g + r: row r, columns 4g .. 4g+3) and every epilogue stores 8 or 16 bytes.
+//
+// K slices (grid) meet like the split-K GEMM's: agent-scope partials, one counter per tile group,
+// the last arriver adds the slices in slice order and runs the epilogue.  K steps that do not fill a
+// stage, and the second source (LoRA), are multiplied after the loop, straight from global memory.
 // =====================================================================================
-namespace tile {
-constexpr int BR = 8;                        // row tiles per workgroup
-constexpr int BC = 8;                        // column tiles per workgroup
-constexpr int KS = 1;                        // k-steps per stage
-constexpr int A_CHUNKS = BR * KS * 2;        // 1 KiB operand blocks per stage (hi and lo)
-constexpr int W_CHUNKS = BC * KS;            // 1 KiB weight blocks per stage
-constexpr int CHUNKS = A_CHUNKS + W_CHUNKS;
-constexpr int NT = 512;
-constexpr int CPT = CHUNKS * 64 / NT;        // 16-byte pieces per thread per stage
-constexpr int PD = 4;                        // stages in flight in registers (even: LDS buffer = stage & 1)
-static_assert(PD % 2 == 0, "the LDS buffer of a stage is its parity");
-static_assert(A_CHUNKS * 64 % NT == 0 && CHUNKS * 64 % NT == 0, "pieces per thread must split by kind");
-}  // namespace tile
+// A thread's share of the sums of squares of a workgroup's ROWS rows: row threadIdx.x / TPR, partial sums
+// threadIdx.x % TPR, + TPR, ...  Requested before the main loop's first loads, added up after them, so that
+// the round trip hides behind theirs (row after row in front of the loop took 4 to 9 us per launch).
+template <int ROWS, int NT>
+struct RowSums {
+    static constexpr int TPR = NT / ROWS, U = 16;
+    float t[U];
+    __device__ __forceinline__ void load(const GemmArgs& a, int m0) {
+        const float* ps = a.part_ss + (size_t)(m0 + threadIdx.x / TPR) * a.n_ss;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int p = (int)threadIdx.x % TPR + u * TPR;
+            t[u] = p < a.n_ss ? ps[p] : 0.f;
+        }
+    }
+    // 1/rms per row into inv_s; rows past M get 0
+    __device__ __forceinline__ void finish(const GemmArgs& a, int m0, float* inv_s) {
+        const int row = threadIdx.x / TPR;
+        float s = 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += t[u];
+        const float* ps = a.part_ss + (size_t)(m0 + row) * a.n_ss;
+        for (int p = (int)threadIdx.x % TPR + U * TPR; p < a.n_ss; p += TPR) s += ps[p];
+#pragma unroll
+        for (int off = 1; off < TPR; off <<= 1) s += __shfl_xor(s, off);
+        if (threadIdx.x % TPR == 0) inv_s[row] = m0 + row < a.M ? 1.0f / sqrtf(s / (float)a.K + a.eps) : 0.f;
+    }
+};
 
-// K slices: with ksplit > 1, workgroup (x, y) multiplies the y-th of ksplit near-equal runs of
-// stages of its 128 x 128 tile and stores its accumulators to `part` with agent-scope stores; the
-// workgroup that completes the tile's counter adds the slices in slice order and runs the
-// epilogue, then resets the counter.
-template <int EPI>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
-gemm_tile_kernel(GemmArgs a, int R, int C, int ksplit, float* part, unsigned* ctr) {
-    using namespace tile;
+// ---- epilogues of four neighbouring columns n = 16t + 4g + i of row m (lane 16g + r: row r of the row tile)
+__device__ __forceinline__ void store_split4(uint16_t* p, size_t hi_index, const float* v, uint32_t plain) {
+    uint32_t h[2], l[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        h[q] = pack_bf16x2(v[2 * q], v[2 * q + 1]);
+        l[q] = plain ? 0u : pack_bf16x2(v[2 * q] - bf16_to_f32(h[q] & 0xFFFFu), v[2 * q + 1] - bf16_to_f32(h[q] >> 16));
+    }
+    *(uint2*)(p + hi_index) = uint2{h[0], h[1]};
+    *(uint2*)(p + hi_index + SPLIT_LO) = uint2{l[0], l[1]};
+}
+
+// One column tile of the QKV projection, decoded once for all its row tiles (t is uniform).
+struct QkvTile {
+    int kind, dim, head_q, row_q, kvh;   // kind 0 q, 1 k, 2 v; q: KV head and first block row of the head's rows
+    size_t dpart;                        // q: the head dimensions' share of q_index
+    __device__ __forceinline__ void decode(const GemmArgs& a, int t, int g) {
+        const int D = a.head_dim, tph = D / 16, hh = t / tph, u = t % tph, nq = a.n_q_heads, nkv = a.n_kv_heads;
+        kind = hh < nq ? 0 : (hh < nq + nkv ? 1 : 2);
+        dim = 8 * u + 4 * (g & 1) + (g < 2 ? 0 : D / 2);   // lanes g and g ^ 2 hold RoPE partners
+        const int G = nq / nkv;
+        head_q = hh / G;
+        row_q = (hh % G) * a.k_blk;
+        kvh = hh - nq - (kind == 2 ? nkv : 0);
+        dpart = (size_t)(dim >> 5) * 1024 + (((dim & 31) >> 3) << 7) + (dim & 7);
+    }
+};
+
+// Four columns of row m (sequence b, block row jb, absolute position pos); c0, c1: the (cos, sin) pairs of
+// their rotary frequencies.
+__device__ __forceinline__ void epi4_qkv(const GemmArgs& a, const QkvTile& tl, f32x4_t y, int m, int b, int jb, int pos,
+                                         int g, float4 c0, float4 c1) {
+    const int D = a.head_dim, nkv = a.n_kv_heads;
+    float out[4] = {y[0], y[1], y[2], y[3]};
+    if (tl.kind < 2) {
+        const float co[4] = {c0.x, c0.z, c1.x, c1.z}, si[4] = {c0.y, c0.w, c1.y, c1.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float partner = __shfl_xor(y[i], 32);
+            out[i] = g < 2 ? (y[i] * co[i] - partner * si[i]) : (y[i] * co[i] + partner * si[i]);
+        }
+    }
+    if (m >= a.M) return;
+    if (tl.kind == 0) {   // q_index(b * nkv + head_q, row_q + jb, dim, ...)
+        const int row = tl.row_q + jb;
+        const size_t at = (size_t)((b * nkv + tl.head_q) * a.q_row_tiles + (row >> 4)) * ((D >> 5) * 1024) + (row & 15) * 8;
+        store_split4(a.q_out, at + tl.dpart, out, a.plain & SITE_Q);
+        return;
+    }
+    const size_t unit = (size_t)b * nkv + tl.kvh;
+    const int dim = tl.dim;
+    const bool cache = a.write_cache && !(a.quad_k > 0 && jb >= a.quad_k);   // quadratic layout: chain rows only
+    if (cache && pos >= a.max_len) atomicOr(a.status, DEV_CAPACITY);
+    const bool wr = cache && pos < a.max_len;
+    uint32_t h[2], l[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        h[q] = pack_bf16x2(out[2 * q], out[2 * q + 1]);
+        l[q] = (a.plain & SITE_KV)
+                   ? 0u
+                   : pack_bf16x2(out[2 * q] - bf16_to_f32(h[q] & 0xFFFFu), out[2 * q + 1] - bf16_to_f32(h[q] >> 16));
+    }
+    if (tl.kind == 1) {
+        *(uint2*)(a.blk_k + (unit * 2 * 64 + jb) * D + dim) = uint2{h[0], h[1]};
+        *(uint2*)(a.blk_k + ((unit * 2 + 1) * 64 + jb) * D + dim) = uint2{l[0], l[1]};
+        if (wr) *(uint2*)(a.kc + (unit * a.max_len + pos) * D + dim) = uint2{h[0], h[1]};
+        return;
+    }
+    uint16_t* bv = a.blk_v + (unit * 2 * D + dim) * 64 + jb;   // values are stored transposed
+    uint16_t* cv = a.vc + ((unit * (a.max_len / 64) + pos / 64) * D + dim) * 64 + (pos & 63);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint16_t hb = (uint16_t)(h[i >> 1] >> (16 * (i & 1))), lb = (uint16_t)(l[i >> 1] >> (16 * (i & 1)));
+        bv[i * 64] = hb;
+        bv[(size_t)D * 64 + i * 64] = lb;
+        if (wr) cv[i * 64] = hb;
+    }
+}
+
+// y * sigmoid(y): exp2 of -y log2(e) with the product's rounding error carried to first order, and a
+// reciprocal, each within an ulp or two; the library's expf and division took a third of the epilogue's time.
+// exp(x) beyond +-104 is infinity or 0 in f32, so the clamp (which keeps infinities out of the error term)
+// changes no result.
+__device__ __forceinline__ float exp_f32(float x) {
+    const float xc = __builtin_amdgcn_fmed3f(x, -104.f, 104.f);
+    const float hi = 1.44269504f * xc, lo = fmaf(1.44269504f, xc, -hi) + 1.92596299e-8f * xc;
+    const float e = __builtin_amdgcn_exp2f(hi);
+    return fmaf(e, 0.69314718f * lo, e);
+}
+__device__ __forceinline__ float silu(float y) { return y * __builtin_amdgcn_rcpf(1.0f + exp_f32(-y)); }
+
+// rotation of the 16 lanes of a row by N (a register move, where a shuffle goes through LDS)
+template <int N>
+__device__ __forceinline__ uint32_t row_ror(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x120 | N, 0xF, 0xF, true);
+}
+template <int N>
+__device__ __forceinline__ float row_ror(float v) { return __uint_as_float(row_ror<N>(__float_as_uint(v))); }
+
+// Lanes g < 2 hold four gate columns, lanes g ^ 2 the matching up columns; each lane of a pair finishes two
+// of the four columns.
+__device__ __forceinline__ void epi4_swiglu(const GemmArgs& a, f32x4_t y, int m, int t, int g) {
+    const bool lowg = g < 2;
+    const float r0 = __shfl_xor(lowg ? y[2] : y[0], 32), r1 = __shfl_xor(lowg ? y[3] : y[1], 32);
+    const float a0 = silu(lowg ? y[0] : r0) * (lowg ? r0 : y[2]), a1 = silu(lowg ? y[1] : r1) * (lowg ? r1 : y[3]);
+    const int col = 8 * t + 4 * (g & 1) + (lowg ? 0 : 2);
+    if (m < a.M && col < a.ffn) {   // ffn is a multiple of 8: the tile's columns are in or out together
+        const uint32_t h = pack_bf16x2(a0, a1);
+        const uint32_t l = (a.plain & SITE_ACT) ? 0u : pack_bf16x2(a0 - bf16_to_f32(h & 0xFFFFu), a1 - bf16_to_f32(h >> 16));
+        uint16_t* p = a.act + split_index(m, col, (a.ffn + 31) / 32);
+        *(uint32_t*)p = h;
+        *(uint32_t*)(p + SPLIT_LO) = l;
+    }
+}
+
+// returns the sum of squares of the four new residual values
+__device__ __forceinline__ float epi4_resid(const GemmArgs& a, f32x4_t v, int m, int t, int g, float4 xr, uint2 gn) {
+    if (m >= a.M) return 0.f;
+    const int N = a.n_tiles * 16, n = t * 16 + 4 * g;
+    const float xn[4] = {xr.x + v[0], xr.y + v[1], xr.z + v[2], xr.w + v[3]};
+    *(float4*)(a.x + (size_t)m * N + n) = float4{xn[0], xn[1], xn[2], xn[3]};
+    const float xg[4] = {xn[0] * bf16_to_f32(gn.x & 0xFFFFu), xn[1] * bf16_to_f32(gn.x >> 16),
+                         xn[2] * bf16_to_f32(gn.y & 0xFFFFu), xn[3] * bf16_to_f32(gn.y >> 16)};
+    store_split4(a.xg_out, split_index(m, n, N / 32), xg, a.plain & (SITE_NORM | SITE_FINAL));
+    return (xn[0] * xn[0] + xn[1] * xn[1]) + (xn[2] * xn[2] + xn[3] * xn[3]);
+}
+
+// 16 bytes per lane at agent scope: what an agent-scope atomic store or load of 8 bytes compiles to (the
+// sc1 bit: through this XCD's L2, to and from where every XCD sees it), at twice the width.  `p` is the
+// lane's address; the buffer descriptor takes the first lane's as its base.
+constexpr int CPOL_AGENT = 16;   // sc1
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t agent_rsrc(const void* p, uint32_t* off) {
+    const uint64_t at = (uint64_t)p;
+    const uint64_t base = (uint64_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32)) << 32 |
+                          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+    *off = (uint32_t)(at - base);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7FFFFFFF, 0x00027000);
+}
+__device__ __forceinline__ void store_agent(f32x4_t* p, f32x4_t v) {
+    typedef uint32_t u32x4_b __attribute__((ext_vector_type(4)));
+    uint32_t off;
+    const __amdgpu_buffer_rsrc_t rs = agent_rsrc(p, &off);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_b, v), rs, off, 0, CPOL_AGENT);
+}
+__device__ __forceinline__ f32x4_t load_agent(const f32x4_t* p) {
+    uint32_t off;
+    const __amdgpu_buffer_rsrc_t rs = agent_rsrc(p, &off);
+    return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, CPOL_AGENT));
+}
+
+template <int RT, int WC, int CT, int KB, int EPI>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+gemm_panel_kernel(GemmArgs a, int R, int C, int ksplit, float* part, unsigned* ctr) {
+    constexpr int NW = 8, WK = NW / WC, KW = KB / WK, NT = NW * 64;
+    constexpr int BLOCKS = RT * KB * 2;       // 1 KiB operand blocks per stage
+    constexpr int APW = BLOCKS / NW;          // of them per wavefront
+    constexpr int NTL = RT * CT;              // output tiles per wavefront
     constexpr bool NORMED = EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LMHEAD;
-    __shared__ uint4 lds[2][CHUNKS * 64];
-    __shared__ float inv_s[BR * 16];
-    __shared__ int pos_s[BR * 16];
-    __shared__ unsigned long long key_s[BR * 16];
-    __shared__ float2 lse_s[BR * 16][BC];
+    static_assert(WC * WK == NW && KW * WK == KB && BLOCKS % NW == 0, "whole shares per wavefront");
+    constexpr int RED = WK > 1 ? NW * NTL : 0;   // 1 KiB blocks the k groups meet in
+    // Epilogue: a wavefront's tiles pass through LDS in PASSES runs of row tiles, so that the code of one row
+    // tile is a loop body.  Unrolled over the accumulators it ran once, straight from a cold instruction
+    // cache: 15-40 us per launch at 128 x 384.
+    constexpr int PASSES = NTL > 16 ? 4 : (NTL > 12 ? 2 : 1), RPP = RT / PASSES, STG = NW * RPP * CT;
+    constexpr int ROPE = EPI == EPI_QKV ? (RT * 16 * 33 + 63) / 64 : 0;   // the rows' RoPE pairs (epilogue)
+    constexpr int LDS0 = 2 * BLOCKS > RED ? 2 * BLOCKS : RED, LDS1 = STG + ROPE, LDSB = LDS0 > LDS1 ? LDS0 : LDS1;
+    __shared__ uint4 lds[LDSB * 64];
+    __shared__ float inv_s[RT * 16];
+    __shared__ int pos_s[RT * 16];
+    __shared__ int seq_s[RT * 16];   // sequence << 6 | block row (at most 64 of them)
+    __shared__ float ss_s[NW][RT * 16];
+    __shared__ unsigned long long key_s[NW][RT * 16];
+    __shared__ float2 lse_s[NW][RT * 16];
+    __shared__ int last_s;
+    constexpr int TLC = EPI == EPI_QKV ? TL_QKV : (EPI == EPI_SWIGLU ? TL_GATE_UP : (EPI == EPI_LMHEAD ? TL_LM : TL_DOWN));
+    (void)TLC;
+    NLD_TS(TLC, 0);
 
-    const int b = blockIdx.x, xcd = b & 7, gi = b >> 3;
-    const int rg = gi % R, c = (gi / R) * 8 + xcd;
-    if (c >= C) return;   // the whole workgroup leaves: the grid covers whole groups of 8 column groups
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
-    const int wr = wave >> 1, wc = wave & 1;
-    const int m0 = rg * BR * 16;
+    const int wc = wave % WC, wk = wave / WC;
+    // Workgroup b runs on XCD b % 8.  Logical id: row group fastest, then column group, then K slice,
+    // consecutive ids on one XCD, so that the row groups of a column group find its weights, and the
+    // column groups of a slice their operand, in that XCD's L2.
+    const int per = gridDim.x / 8;
+    const int id = (int)blockIdx.x < per * 8 ? (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+    const int rg = id % R, cg = (id / R) % C, ksl = id / (R * C);
+    const int m0 = rg * RT * 16;
 
-    if constexpr (EPI == EPI_LMHEAD) {
-        if (threadIdx.x < BR * 16) {
-            key_s[threadIdx.x] = 0ull;
-#pragma unroll
-            for (int j = 0; j < BC; ++j) lse_s[threadIdx.x][j] = float2{-INFINITY, 0.f};
-        }
-    }
-    if constexpr (NORMED) rms_scales(a, m0, BR * 16, inv_s);
-    if constexpr (EPI == EPI_QKV) {
-        if (threadIdx.x < BR * 16) {
-            const int m = min(m0 + (int)threadIdx.x, a.M - 1);
-            pos_s[threadIdx.x] = committed_length(a.lengths, m / a.k_blk, a.max_len, a.status) + m % a.k_blk;
-        }
-    }
+    RowSums<RT * 16, NT> sums;
+    if constexpr (NORMED) sums.load(a, m0);
+    // whole stages of full k-steps, cut into ksplit near-equal runs; the rest is the tail
+    const int full = a.K / 32;
+    const int nst_all = full / KB;
+    const int st0 = ksl * nst_all / ksplit, nst = (ksl + 1) * nst_all / ksplit - st0;
 
-    // Stage pieces: thread (wave, lane) copies piece q = 1 KiB block wave + 8q, 16 bytes at
-    // lane.  Blocks 0 .. A_CHUNKS-1 are operand blocks (row tile, k-step, half), the rest
-    // weight blocks (column tile, k-step).  The launcher guarantees whole stages (ksteps a
-    // multiple of KS, K a multiple of 32) and operand rows allocated up to a multiple of
-    // 128; column tiles past the end are read clamped and their outputs dropped.  So every
-    // load is unconditional and in bounds.
-    static_assert(A_CHUNKS % 8 == 0 && CHUNKS == 8 * CPT, "8 blocks per piece index");
-    // slice ksl: stages [ksl*n/ksplit, (ksl+1)*n/ksplit), at least one since ksplit <= n
-    const int ksl = blockIdx.y;
-    const int nst_all = a.ksteps / KS;
-    const int st0 = ksl * nst_all / ksplit;
-    const int nst = (ksl + 1) * nst_all / ksplit - st0;
-    const uint4* srcp[CPT];   // stage 0 address of each piece (the slice's first stage)
+    f32x4_t acc[RT][CT];
 #pragma unroll
-    for (int q = 0; q < CPT; ++q) {
-        const int chunk = wave + 8 * q;
-        if (q < A_CHUNKS / 8) {
-            const int rt = chunk / (KS * 2), ks = (chunk / 2) % KS, half = chunk & 1;
-            srcp[q] = (const uint4*)(a.A + ((size_t)((m0 / 16 + rt) * a.ksteps + ks) * 2 + half) * 512) + lane;
-        } else {
-            const int wck = chunk - A_CHUNKS, ct = wck / KS, ks = wck % KS;
-            srcp[q] = a.W + ((size_t)min(c * BC + ct, a.n_tiles - 1) * a.ksteps + ks) * 64 + lane;
-        }
-        srcp[q] += (size_t)st0 * KS * (q < A_CHUNKS / 8 ? 128 : 64);
-    }
-    // stage st: operand blocks advance by KS k-steps of 2 KiB, weight blocks by KS of 1 KiB
-    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-#define NLD_TILE_GLOAD(st, dst)                                                            \
-    _Pragma("unroll") for (int q = 0; q < CPT; ++q)                                         \
-        dst[q] = *(const u32x4_t*)(srcp[q] + (size_t)(st) * KS * (q < A_CHUNKS / 8 ? 128 : 64))
-#define NLD_TILE_LSTORE(v, buf) \
-    _Pragma("unroll") for (int q = 0; q < CPT; ++q) *(u32x4_t*)&lds[buf][threadIdx.x + q * NT] = v[q]
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    // one accumulator per output tile takes both operand halves (eight independent tiles keep
-    // the MFMA pipeline busy between the two dependent products)
-    f32x4_t acc[2][4];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    auto compute = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            uint4 ah[2], al[2], w[4];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int rt = 2 * wr + i;
-                ah[i] = lds[buf][((rt * KS + ks) * 2 + 0) * 64 + lane];
-                al[i] = lds[buf][((rt * KS + ks) * 2 + 1) * 64 + lane];
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) w[j] = lds[buf][(A_CHUNKS + (4 * wc + j) * KS + ks) * 64 + lane];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = mfma_16x16x32(ah[i], w[j], acc[i][j]);
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = mfma_16x16x32(al[i], w[j], acc[i][j]);
-        }
+    // LM head: rows 4g+i of column r instead, so that a logits store is 64 contiguous bytes per row
+    auto mm = [](uint4 w, uint4 x, f32x4_t c) __attribute__((always_inline)) {
+        return EPI == EPI_LMHEAD ? mfma_16x16x32(x, w, c) : mfma_16x16x32(w, x, c);
     };
 
-    // Stage s is multiplied from LDS buffer s & 1 while stages s+1 .. s+PD wait or are in flight in
-    // a ring of PD register slots: the slot of stage s is refilled with stage s+PD as soon as s is
-    // in LDS, so PD stages of loads cover the L2 / HBM latency.  The loop is unrolled by PD so
-    // that every slot index is a compile-time constant; loads past the last stage re-read it and
-    // are never stored.
-    u32x4_t rb[PD][CPT];
+    // this wavefront's operand blocks of a stage: blocks wave*APW .. +APW of [row tile][k-step][hi, lo]
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    const u32x4_t* ap[APW];
 #pragma unroll
-    for (int p = 0; p < PD; ++p) NLD_TILE_GLOAD(min(p, nst - 1), rb[p]);
-    NLD_TILE_LSTORE(rb[0], 0);
-    __syncthreads();
-    for (int st = 0; st < nst; st += PD) {
+    for (int q = 0; q < APW; ++q) {
+        const int ch = wave * APW + q, rt = ch / (KB * 2), in = ch % (KB * 2);
+        ap[q] = (const u32x4_t*)a.A + ((size_t)((m0 / 16 + rt) * a.ksteps + st0 * KB) * 2 + in) * 64;
+    }
+    const uint4* wp[CT];   // column tiles past the end are read clamped and their outputs dropped
 #pragma unroll
-        for (int u = 0; u < PD; ++u) {
-            const int cur = st + u;
-            if (cur >= nst) break;
-            NLD_TILE_GLOAD(min(cur + PD, nst - 1), rb[u]);
-            compute(u & 1);
-            if (cur + 1 < nst) { NLD_TILE_LSTORE(rb[(u + 1) % PD], (u + 1) & 1); }
-            __syncthreads();
+    for (int c = 0; c < CT; ++c) {
+        const int t = min((cg * WC + wc) * CT + c, a.n_tiles - 1);
+        wp[c] = a.W + ((size_t)t * a.ksteps + st0 * KB + wk * KW) * 64;
+    }
+
+    if (nst > 0) {
+        u32x4_t ar[2][APW];
+        uint4 wr[2][KW][CT];
+#define NLD_PANEL_LDA(st, set)                                                      \
+    {                                                                               \
+        const size_t so_ = (size_t)min((st), nst - 1) * KB * 128;                   \
+        _Pragma("unroll") for (int q = 0; q < APW; ++q) ar[set][q] = ap[q][so_ + lane]; \
+    }
+#define NLD_PANEL_LDW(st, set, kk)                                                  \
+    {                                                                               \
+        const size_t so_ = (size_t)(min((st), nst - 1) * KB + (kk)) * 64;           \
+        _Pragma("unroll") for (int c = 0; c < CT; ++c) wr[set][kk][c] = load_stream(wp[c] + so_ + lane); \
+    }
+#define NLD_PANEL_STA(set, slot)                                                    \
+    _Pragma("unroll") for (int q = 0; q < APW; ++q)                                 \
+        *(u32x4_t*)&lds[((slot) * BLOCKS + wave * APW + q) * 64 + lane] = ar[set][q];
+        NLD_PANEL_LDA(0, 0);
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int kk = 0; kk < KW; ++kk) NLD_PANEL_LDW(p, p, kk);
+        NLD_PANEL_LDA(1, 1);
+        if constexpr (NORMED) sums.finish(a, m0, inv_s);
+        NLD_PANEL_STA(0, 0);
+        NLD_PANEL_LDA(2, 0);
+        __syncthreads();
+        NLD_TS(TLC, 3);   // first stage in LDS
+        for (int st = 0; st < nst; st += 2) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (st + u >= nst) break;
+#pragma unroll
+                for (int kk = 0; kk < KW; ++kk) {
+#pragma unroll
+                    for (int i = 0; i < RT; ++i) {
+                        const int bi = (u * BLOCKS + (i * KB + wk * KW + kk) * 2) * 64 + lane;
+                        const uint4 ah = lds[bi], al = lds[bi + 64];
+#pragma unroll
+                        for (int c = 0; c < CT; ++c) acc[i][c] = mm(wr[u][kk][c], ah, acc[i][c]);
+#pragma unroll
+                        for (int c = 0; c < CT; ++c) acc[i][c] = mm(wr[u][kk][c], al, acc[i][c]);
+                    }
+                    NLD_PANEL_LDW(st + u + 2, u, kk);
+                    if (kk == 0) {
+                        NLD_PANEL_STA(u ^ 1, u ^ 1);
+                        NLD_PANEL_LDA(st + u + 3, u ^ 1);
+                    }
+                }
+                __syncthreads();
+            }
+        }
+#undef NLD_PANEL_LDA
+#undef NLD_PANEL_LDW
+#undef NLD_PANEL_STA
+    } else if constexpr (NORMED) {
+        sums.finish(a, m0, inv_s);
+    }
+
+    // the last slice also takes the k-steps that fill no stage (the last may be partial: columns past
+    // K meet zeroed operand lanes) and the second source's, the k groups by turns
+    if (ksl == ksplit - 1) {
+        const int s1 = nst_all * KB, n1 = a.ksteps - s1, n2 = a.W2 ? a.ksteps2 : 0;
+        for (int e = wk; e < n1 + n2; e += WK) {
+            const bool second = e >= n1;
+            const int s = second ? e - n1 : s1 + e, nk = second ? a.ksteps2 : a.ksteps;
+            const uint4* wb = second ? a.W2 : a.W;
+            const uint16_t* ab = second ? a.A2 : a.A;
+            const bool in = second || s * 32 + 8 * g < a.K;
+            uint4 w[CT];
+#pragma unroll
+            for (int c = 0; c < CT; ++c) w[c] = wb[((size_t)min((cg * WC + wc) * CT + c, a.n_tiles - 1) * nk + s) * 64 + lane];
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                const uint4* xp = (const uint4*)(ab + (size_t)((m0 / 16 + i) * nk + s) * 1024) + lane;
+                const uint4 ah = in ? xp[0] : uint4{0u, 0u, 0u, 0u}, al = in ? xp[64] : uint4{0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int c = 0; c < CT; ++c) acc[i][c] = mm(w[c], ah, acc[i][c]);
+#pragma unroll
+                for (int c = 0; c < CT; ++c) acc[i][c] = mm(w[c], al, acc[i][c]);
+            }
         }
     }
-#undef NLD_TILE_GLOAD
-#undef NLD_TILE_LSTORE
+    NLD_TS(TLC, 1);   // main loop done
+
+    // The k groups meet in LDS (fixed order); group wk keeps tiles wk, wk + WK, ... of its column wavefront.
+    if constexpr (WK > 1) {
+        f32x4_t* red = (f32x4_t*)lds;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NTL; ++q) red[(wave * NTL + q) * 64 + lane] = acc[q / CT][q % CT];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NTL; ++q) {
+            if (q % WK != wk) continue;
+            f32x4_t s = red[(wc * NTL + q) * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < WK; ++w) s += red[((w * WC + wc) * NTL + q) * 64 + lane];
+            acc[q / CT][q % CT] = s;
+        }
+    }
 
     if (ksplit > 1) {
-        // slice partials, 16 pairs of floats per thread, pair-major so that every store is one
-        // contiguous 512-byte run per wavefront
-        typedef unsigned long long u64;
-        __shared__ int last_s;
-        const int grp = c * R + rg;
-        u64* pp = (u64*)part + (size_t)(grp * ksplit + ksl) * 16 * NT + threadIdx.x;
+        // slice partials: one contiguous 1 KiB block per tile
+        const int grp = cg * R + rg;
+        auto at = [&](int sl) { return (f32x4_t*)part + ((size_t)(grp * ksplit + sl) * WC + wc) * NTL * 64 + lane; };
+        f32x4_t* pp = at(ksl);
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int q = (i * 4 + j) * 2;
-                __hip_atomic_store(pp + (size_t)q * NT, __builtin_bit_cast(u64, f32x2_t{acc[i][j][0], acc[i][j][1]}),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(pp + (size_t)(q + 1) * NT, __builtin_bit_cast(u64, f32x2_t{acc[i][j][2], acc[i][j][3]}),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+        for (int q = 0; q < NTL; ++q) {
+            if (WK > 1 && q % WK != wk) continue;
+            store_agent(pp + q * 64, acc[q / CT][q % CT]);
+        }
         // every lane's stores are acknowledged before the workgroup counts itself in
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         __builtin_amdgcn_s_waitcnt(0);
@@ -1353,114 +1286,302 @@ gemm_tile_kernel(GemmArgs a, int R, int C, int ksplit, float* part, unsigned* ct
         __syncthreads();
         if (!last_s) return;
         if (threadIdx.x == 0) __hip_atomic_exchange(ctr + grp, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        f32x4_t sum[2][4];
+        // fixed order over the slices, all of a slice's loads in flight at once (in two halves where the
+        // registers of a whole wavefront tile, its sums and its loads do not fit beside each other)
+        constexpr int CH = NTL > 16 ? NTL / 2 : NTL;
+        static_assert(NTL % CH == 0, "whole chunks");
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int q0 = 0; q0 < NTL; q0 += CH) {
+            f32x4_t sum[CH];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) sum[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        for (int sl = 0; sl < ksplit; ++sl) {   // fixed order over the slices
-            if (sl == ksl) {
+            for (int q = 0; q < CH; ++q) sum[q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int sl = 0; sl < ksplit; ++sl) {
+                if (sl == ksl) {
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) sum[i][j] += acc[i][j];
-                continue;
-            }
-            const u64* qq = (const u64*)part + (size_t)(grp * ksplit + sl) * 16 * NT + threadIdx.x;
-            f32x2_t v[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q)
-                v[q] = __builtin_bit_cast(f32x2_t, __hip_atomic_load(qq + (size_t)q * NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int q = (i * 4 + j) * 2;
-                    sum[i][j] += f32x4_t{v[q][0], v[q][1], v[q + 1][0], v[q + 1][1]};
+                    for (int q = 0; q < CH; ++q) sum[q] += acc[(q0 + q) / CT][(q0 + q) % CT];
+                    continue;
                 }
+                const f32x4_t* qq = at(sl) + q0 * 64;
+                f32x4_t v[CH];
+#pragma unroll
+                for (int q = 0; q < CH; ++q) {
+                    if (WK > 1 && (q0 + q) % WK != wk) continue;
+                    v[q] = load_agent(qq + q * 64);
+                }
+#pragma unroll
+                for (int q = 0; q < CH; ++q) {
+                    if (WK > 1 && (q0 + q) % WK != wk) continue;
+                    sum[q] += v[q];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < CH; ++q) acc[(q0 + q) / CT][(q0 + q) % CT] = sum[q];
         }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = sum[i][j];
     }
+    if constexpr (EPI == EPI_QKV) {
+        if (threadIdx.x < RT * 16) {
+            const int m = min(m0 + (int)threadIdx.x, a.M - 1), b = m / a.k_blk;
+            seq_s[threadIdx.x] = b << 6 | (m - b * a.k_blk);
+            pos_s[threadIdx.x] = committed_length(a.lengths, b, a.max_len, a.status) + m - b * a.k_blk;
+        }
+    }
+    if constexpr (NORMED) __syncthreads();   // inv_s, pos_s, seq_s
+    NLD_TS(TLC, 2);   // slices added
 
+    auto mine = [&](int i, int c) { return WK == 1 || (i * CT + c) % WK == wk; };
+    // f(i, tiles) for every row tile i, from the wavefront's own LDS
+    auto each_row_tile = [&](auto f) __attribute__((always_inline)) {
+        if constexpr (WK > 1) __syncthreads();   // every group has read the others' sums
+        f32x4_t* stg = (f32x4_t*)lds + wave * RPP * CT * 64 + lane;
+#pragma unroll 1
+        for (int ps = 0; ps < PASSES; ++ps) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+            for (int p2 = 0; p2 < PASSES; ++p2) {
+                if (ps != p2) continue;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const f32x4_t v = acc[i][j];
-            const int rt = 2 * wr + i, ct = 4 * wc + j;
-            const int t = c * BC + ct;
-            if (t >= a.n_tiles) continue;
+                for (int q = 0; q < RPP * CT; ++q) stg[q * 64] = acc[p2 * RPP + q / CT][q % CT];
+            }
+#pragma unroll 1
+            for (int i = 0; i < RPP; ++i) {
+                f32x4_t v[CT];
+#pragma unroll
+                for (int c = 0; c < CT; ++c) v[c] = stg[(i * CT + c) * 64];
+                f(ps * RPP + i, v);
+            }
+        }
+    };
+    if constexpr (EPI == EPI_LMHEAD) {
+        const int n0 = (cg * WC + wc) * CT * 16 + r;   // column of the lane in the wavefront's first tile
+        bool col[CT], cand[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            col[c] = n0 + 16 * c < a.vocab;
+            cand[c] = col[c] && n0 + 16 * c != a.exclude_id;
+        }
+        each_row_tile([&](int i, const f32x4_t (&v)[CT]) __attribute__((always_inline)) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int ml = rt * 16 + 4 * g + e;
-                const int m = m0 + ml;
-                if constexpr (EPI == EPI_RESID) {
-                    const int N = a.n_tiles * 16;
-                    const float xr = m < a.M ? a.x[(size_t)m * N + t * 16 + r] : 0.f;
-                    epi_resid(a, v[e], m, t, lane, xr, bf16_to_f32(a.gain_next[t * 16 + r]));
-                } else if constexpr (EPI == EPI_QKV) {
-                    epi_qkv(a, v[e] * inv_s[ml], m, t, lane, pos_s[ml]);
-                } else if constexpr (EPI == EPI_SWIGLU) {
-                    epi_swiglu(a, v[e] * inv_s[ml], m, t, lane);
-                } else {
-                    float2 tl;
-                    const unsigned long long key = epi_lmhead(a, v[e] * inv_s[ml], m, t, lane, &tl);
-                    if (r == 0) {
-                        atomicMax(&key_s[ml], key);
-                        if (a.part_lse) lse_s[ml][ct] = tl;   // each (row, column tile) is finished once
+                const int ml = 16 * i + 4 * g + e, m = m0 + ml;
+                const float inv = inv_s[ml];
+                float y[CT];
+#pragma unroll
+                for (int c = 0; c < CT; ++c) y[c] = v[c][e] * inv;
+                if (a.logits && m < a.M) {
+                    float* lp = a.logits + (size_t)m * a.vocab + n0;
+#pragma unroll
+                    for (int c = 0; c < CT; ++c)
+                        if (col[c] && mine(i, c)) lp[16 * c] = y[c];
+                }
+                if (a.ens_logits && m < a.M) {   // quadratic layout: verifier rows (chain row i, mask 1 of group i)
+                    const int b = m / a.k_blk, jb = m - b * a.k_blk, qk = a.quad_k;
+                    const int ci = jb < qk ? jb : ((jb - qk) % qk == 0 ? qk + (jb - qk) / qk : -1);
+                    float* ep = a.ens_logits + ((size_t)b * 2 * qk + ci) * a.vocab + n0;
+#pragma unroll
+                    for (int c = 0; c < CT; ++c)
+                        if (col[c] && ci >= 0 && mine(i, c)) ep[16 * c] = y[c];
+                }
+                // the order argmax_key gives (-0 as +0), as a signed number; then the lowest column of the largest
+                int32_t ord[CT], top = INT32_MIN;
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    const int32_t u = __float_as_int(y[c] + 0.0f);
+                    const bool take = cand[c] && mine(i, c);
+                    ord[c] = take ? (u ^ ((u >> 31) & 0x7FFFFFFF)) : INT32_MIN;
+                    top = max(top, ord[c]);
+                }
+                top = max(top, (int32_t)row_ror<8>((uint32_t)top));
+                top = max(top, (int32_t)row_ror<4>((uint32_t)top));
+                top = max(top, (int32_t)row_ror<2>((uint32_t)top));
+                top = max(top, (int32_t)row_ror<1>((uint32_t)top));
+                uint32_t first = 0xFFFFFFFFu;
+#pragma unroll
+                for (int c = CT - 1; c >= 0; --c) first = ord[c] == top ? (uint32_t)(n0 + 16 * c) : first;
+                first = min(first, row_ror<8>(first));
+                first = min(first, row_ror<4>(first));
+                first = min(first, row_ror<2>(first));
+                first = min(first, row_ror<1>(first));
+                if (a.part_lse) {
+                    float mx = -INFINITY;
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) mx = fmaxf(mx, ord[c] != INT32_MIN ? y[c] : -INFINITY);
+                    mx = fmaxf(mx, row_ror<8>(mx));
+                    mx = fmaxf(mx, row_ror<4>(mx));
+                    mx = fmaxf(mx, row_ror<2>(mx));
+                    mx = fmaxf(mx, row_ror<1>(mx));
+                    float sum = 0.f;
+#pragma unroll
+                    for (int c = 0; c < CT; ++c) sum += ord[c] != INT32_MIN ? exp_f32(y[c] - mx) : 0.f;
+                    sum += row_ror<8>(sum);
+                    sum += row_ror<4>(sum);
+                    sum += row_ror<2>(sum);
+                    sum += row_ror<1>(sum);
+                    if (r == 0) lse_s[wave][ml] = float2{mx, sum};
+                }
+                if (r == 0)   // no column of the row here: the empty key
+                    key_s[wave][ml] = top == INT32_MIN ? 0ull
+                                                       : ((unsigned long long)((uint32_t)top ^ 0x80000000u) << 32) |
+                                                             (unsigned long long)(0xFFFFFFFFu - first);
+            }
+        });
+        __syncthreads();
+        if (threadIdx.x < RT * 16) {
+            const int m = m0 + threadIdx.x;
+            if (m < a.M) {
+                unsigned long long best = 0ull;
+                float2 st = float2{-INFINITY, 0.f};
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    best = umax64(best, key_s[w][threadIdx.x]);
+                    if (a.part_lse) st = lse_merge(st, lse_s[w][threadIdx.x]);
+                }
+                a.part_keys[(size_t)m * a.n_parts + cg] = best;
+                if (a.part_lse) a.part_lse[(size_t)m * a.n_parts + cg] = st;
+            }
+        }
+    } else {
+        // Everything the epilogue reads is read before its first store: a wait for a load also waits for every
+        // store issued before it (about 1 us per tile when they alternate: 16-20 us at 128 x 384).  The
+        // residual goes to registers, the rows' RoPE pairs to LDS (rows 16 bytes apart in banks).
+        float4 xr[EPI == EPI_RESID ? CT : 1][EPI == EPI_RESID ? RT : 1];
+        constexpr int RS = 33;   // RoPE row stride in 16-byte pieces (head_dim <= 128)
+        if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int i = 0; i < RT; ++i) {
+                    if (WK > 1 && (i * CT + c) % WK != wk) continue;
+                    const int m = min(m0 + 16 * i + r, a.M - 1), t = min((cg * WC + wc) * CT + c, a.n_tiles - 1);
+                    xr[c][i] = *(const float4*)(a.x + (size_t)m * a.n_tiles * 16 + t * 16 + 4 * g);
+                }
+        }
+        float sq[RT];
+#pragma unroll
+        for (int i = 0; i < RT; ++i) sq[i] = 0.f;
+        const int t0 = (cg * WC + wc) * CT;
+        if constexpr (EPI == EPI_QKV) {
+            uint4* rope_s = lds + STG * 64;
+            const int pr = a.head_dim / 4, rot = a.head_dim / 16;   // 16-byte pieces per row; tiles per head
+            const uint4* src = (const uint4*)(a.rope + (size_t)m0 * (a.head_dim / 2));
+            __syncthreads();   // the stage buffers are free
+            for (int q = threadIdx.x; q < RT * 16 * pr; q += NT) rope_s[(q / pr) * RS + q % pr] = src[q];
+            __syncthreads();
+            QkvTile tl[CT];
+#pragma unroll
+            for (int c = 0; c < CT; ++c) tl[c].decode(a, t0 + c, g);
+            each_row_tile([&](int i, const f32x4_t (&v)[CT]) __attribute__((always_inline)) {
+                const int ml = 16 * i + r, seq = seq_s[ml], pos = pos_s[ml];
+                const float inv = inv_s[ml];
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    if (!mine(i, c) || t0 + c >= a.n_tiles) continue;
+                    const float4* cs = (const float4*)&rope_s[ml * RS + 4 * ((t0 + c) % rot) + 2 * (g & 1)];
+                    epi4_qkv(a, tl[c], v[c] * inv, m0 + ml, seq >> 6, seq & 63, pos, g, cs[0], cs[1]);
+                }
+            });
+        } else if constexpr (EPI == EPI_SWIGLU) {
+            each_row_tile([&](int i, const f32x4_t (&v)[CT]) __attribute__((always_inline)) {
+                const int ml = 16 * i + r;
+                const float inv = inv_s[ml];
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+                    if (mine(i, c) && t0 + c < a.n_tiles) epi4_swiglu(a, v[c] * inv, m0 + ml, t0 + c, g);
+            });
+        } else {
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                const int t = t0 + c;
+                uint2 gn = {0u, 0u};
+                if constexpr (EPI == EPI_RESID) gn = *(const uint2*)(a.gain_next + min(t, a.n_tiles - 1) * 16 + 4 * g);
+#pragma unroll
+                for (int i = 0; i < RT; ++i) {
+                    if (!mine(i, c) || t >= a.n_tiles) continue;
+                    const int m = m0 + 16 * i + r;
+                    const f32x4_t v = acc[i][c];
+                    if constexpr (EPI == EPI_RESID) sq[i] += epi4_resid(a, v, m, t, g, xr[c][i], gn);
+                    else if (m < a.M) {
+                        const float sv[4] = {a.out_scale * v[0], a.out_scale * v[1], a.out_scale * v[2], a.out_scale * v[3]};
+                        store_split4(a.xg_out, split_index(m, t * 16 + 4 * g, a.n_tiles / 2), sv, 0u);
                     }
                 }
             }
         }
-    if constexpr (EPI == EPI_LMHEAD) {
-        __syncthreads();
-        if (threadIdx.x < BR * 16) {
-            const int m = m0 + threadIdx.x;
-            if (m < a.M) {
-                a.part_keys[(size_t)m * a.n_parts + c] = key_s[threadIdx.x];
-                if (a.part_lse) {
-                    float2 st = float2{-INFINITY, 0.f};
 #pragma unroll
-                    for (int j = 0; j < BC; ++j) st = lse_merge(st, lse_s[threadIdx.x][j]);
-                    a.part_lse[(size_t)m * a.n_parts + c] = st;
-                }
+        for (int i = 0; i < RT; ++i) {
+            if constexpr (EPI == EPI_RESID) {
+                sq[i] += __shfl_xor(sq[i], 16);
+                sq[i] += __shfl_xor(sq[i], 32);
+                if (g == 0) ss_s[wave][16 * i + r] = sq[i];
+            }
+        }
+        if constexpr (EPI == EPI_RESID) {   // one sum of squares per row and column group
+            __syncthreads();
+            if (threadIdx.x < RT * 16 && m0 + (int)threadIdx.x < a.M) {
+                float s = 0.f;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) s += ss_s[w][threadIdx.x];
+                a.part_ss_out[(size_t)(m0 + threadIdx.x) * C + cg] = s;
             }
         }
     }
+#ifdef NLD_TIMELINE
+    __syncthreads();
+#endif
+    NLD_TS(TLC, 4);
 }
 
-int gemm_tile_parts(int n_tiles) { return (n_tiles + tile::BC - 1) / tile::BC; }
+// The workgroup shapes in use, by row tiles: {row tiles, wavefronts side by side, column tiles per
+// wavefront, k-steps per stage}.
+static constexpr PanelShape PANEL_SHAPES[] = {
+    {2, 8, 1, 2}, {2, 4, 1, 4}, {2, 4, 2, 4}, {2, 4, 3, 2}, {2, 2, 3, 4},
+    {4, 8, 1, 2}, {4, 4, 1, 4}, {4, 4, 2, 2}, {4, 4, 3, 2},
+    {8, 4, 1, 2}, {8, 8, 1, 2}, {8, 8, 2, 2}, {8, 8, 3, 2},
+};
+int gemm_panel_shapes() { return (int)(sizeof(PANEL_SHAPES) / sizeof(PANEL_SHAPES[0])); }
+PanelShape gemm_panel_shape(int i) { return PANEL_SHAPES[i]; }
 
-bool gemm_tile_supported(int M, int K, int ksteps) {
-    return M > 64 && K % 32 == 0 && ksteps % tile::KS == 0 && ksteps >= tile::KS;
-}
-
-int gemm_tile_row_pad() { return tile::BR * 16; }
-
-int gemm_tile_groups(int M, int n_tiles) { return ((M + tile::BR * 16 - 1) / (tile::BR * 16)) * gemm_tile_parts(n_tiles); }
-int gemm_tile_stages(int ksteps) { return ksteps / tile::KS; }
-size_t gemm_tile_part_floats_per_wg() { return (size_t)tile::NT * 32; }
-int gemm_tile_wgs_per_cu() { return 2; }
-
-hipError_t launch_gemm_tile(int epi, const GemmArgs& a, int ksplit, float* part, unsigned* ctr, hipStream_t s) {
-    if (!gemm_tile_supported(a.M, a.K, a.ksteps) || a.W2) return hipErrorInvalidValue;
-    // every slice gets at least one stage; the LM head's argmax partials are per column group
-    if (ksplit < 1 || ksplit > gemm_tile_stages(a.ksteps) || (ksplit > 1 && (!part || !ctr || epi == EPI_LMHEAD)))
-        return hipErrorInvalidValue;
-    const int R = (a.M + tile::BR * 16 - 1) / (tile::BR * 16);
-    const int C = gemm_tile_parts(a.n_tiles);
-    const dim3 grid((unsigned)(R * ((C + 7) / 8) * 8), (unsigned)ksplit), blk(tile::NT);
+template <int RT, int WC, int CT, int KB>
+static hipError_t launch_panel_epi(int epi, dim3 grid, int R, int C, const GemmArgs& a, int ksplit, float* part,
+                                   unsigned* ctr, hipStream_t s) {
+    const dim3 blk(512);
     switch (epi) {
-        case EPI_QKV: launch(gemm_tile_kernel<EPI_QKV>, grid, blk, s, a, R, C, ksplit, part, ctr); break;
-        case EPI_RESID: launch(gemm_tile_kernel<EPI_RESID>, grid, blk, s, a, R, C, ksplit, part, ctr); break;
-        case EPI_SWIGLU: launch(gemm_tile_kernel<EPI_SWIGLU>, grid, blk, s, a, R, C, ksplit, part, ctr); break;
-        case EPI_LMHEAD: launch(gemm_tile_kernel<EPI_LMHEAD>, grid, blk, s, a, R, C, ksplit, part, ctr); break;
+        case EPI_QKV: launch(gemm_panel_kernel<RT, WC, CT, KB, EPI_QKV>, grid, blk, s, a, R, C, ksplit, part, ctr); break;
+        case EPI_RESID: launch(gemm_panel_kernel<RT, WC, CT, KB, EPI_RESID>, grid, blk, s, a, R, C, ksplit, part, ctr); break;
+        case EPI_SWIGLU: launch(gemm_panel_kernel<RT, WC, CT, KB, EPI_SWIGLU>, grid, blk, s, a, R, C, ksplit, part, ctr); break;
+        case EPI_LMHEAD: launch(gemm_panel_kernel<RT, WC, CT, KB, EPI_LMHEAD>, grid, blk, s, a, R, C, ksplit, part, ctr); break;
+        case EPI_SPLIT:
+            if constexpr (WC == 4 && CT == 1) {   // gemm_panel_narrow
+                launch(gemm_panel_kernel<RT, WC, CT, KB, EPI_SPLIT>, grid, blk, s, a, R, C, ksplit, part, ctr);
+                break;
+            }
+            return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_gemm_panel(int epi, int shape, const GemmArgs& a, int ksplit, float* part, unsigned* ctr, hipStream_t s) {
+    if (shape < 0 || shape >= gemm_panel_shapes()) return hipErrorInvalidValue;
+    const PanelShape p = PANEL_SHAPES[shape];
+    // every slice gets at least one stage, slices need their partials and counters
+    if (ksplit < 1 || (ksplit > 1 && (ksplit > a.K / 32 / p.kb || !part || !ctr))) return hipErrorInvalidValue;
+    if (a.W2 && epi != EPI_RESID) return hipErrorInvalidValue;
+    const int R = (a.M + 16 * p.rt - 1) / (16 * p.rt), C = (a.n_tiles + p.wc * p.ct - 1) / (p.wc * p.ct);
+    const dim3 grid((unsigned)(R * C * ksplit));
+    switch (shape) {
+        case 0: return launch_panel_epi<2, 8, 1, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 1: return launch_panel_epi<2, 4, 1, 4>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 2: return launch_panel_epi<2, 4, 2, 4>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 3: return launch_panel_epi<2, 4, 3, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 4: return launch_panel_epi<2, 2, 3, 4>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 5: return launch_panel_epi<4, 8, 1, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 6: return launch_panel_epi<4, 4, 1, 4>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 7: return launch_panel_epi<4, 4, 2, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 8: return launch_panel_epi<4, 4, 3, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 9: return launch_panel_epi<8, 4, 1, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 10: return launch_panel_epi<8, 8, 1, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 11: return launch_panel_epi<8, 8, 2, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        default: return launch_panel_epi<8, 8, 3, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
+    }
 }
 
 // =====================================================================================
@@ -2005,6 +2126,7 @@ __global__ void __launch_bounds__(256) embed_kernel(EmbedArgs a) {
     const uint16_t* e = a.embed + (size_t)tok * a.hidden;
     const size_t row = (size_t)m * a.hidden;
     const int chunks = a.hidden / 16;
+    float row_ss = 0.f;
     for (int c = threadIdx.x; c < chunks; c += blockDim.x) {   // 16 columns per thread
         float ss = 0.f;
 #pragma unroll
@@ -2031,12 +2153,14 @@ __global__ void __launch_bounds__(256) embed_kernel(EmbedArgs a) {
             *(uint4*)(a.xg + xi) = hi;
             *(uint4*)(a.xg + xi + SPLIT_LO) = lo;
         }
-        a.part_ss[(size_t)m * chunks + c] = ss;
+        row_ss += ss;
     }
+    row_ss = wave_sum(row_ss);
+    if ((threadIdx.x & 63) == 0) a.part_ss[m * EMBED_SS + (threadIdx.x >> 6)] = row_ss;
 }
 
 hipError_t launch_embed(const EmbedArgs& a, hipStream_t s) {
-    launch(embed_kernel, dim3(a.M), dim3(256), s, a);
+    launch(embed_kernel, dim3(a.M), dim3(64 * EMBED_SS), s, a);
     return hipGetLastError();
 }
 

@@ -105,7 +105,7 @@ struct GemmArgs {
     // A operand: split bf16 activations in operand order (split_index with `ksteps`).
     // For the projections whose input is RMSNorm(x) (QKV, gate/up, LM head) A is
     // x * gain, written by the kernel that produced x, and part_ss holds that
-    // producer's sums of x^2 over 16-column chunks ([M][n_ss]); the consumer turns
+    // producer's sums of x^2 over its column chunks ([M][n_ss]); the consumer turns
     // them into 1/rms per row.
     const uint16_t* A;
     const float* part_ss;
@@ -117,7 +117,7 @@ struct GemmArgs {
     int n_tiles;
     int ksteps;          // ceil(K / 32)
     unsigned* tile_ctr;  // normed GEMM: dynamic tile counter (zeroed by the embedding kernel each pass)
-    // Second reduction source (streamed GEMM only, ksteps2 <= 2 * wavefronts): the sum
+    // Second reduction source (streamed GEMM, ksteps2 <= 2 * wavefronts, and panel GEMM): the sum
     // continues over ksteps2 more k-steps of W2 (packed, ksteps2 steps per tile) against A2
     // (split, ksteps2 steps per row tile).  The draft pass's O projection uses it for the
     // LoRA up-projection.
@@ -130,7 +130,7 @@ struct GemmArgs {
     float* x;
     uint16_t* xg_out;          // split x * gain_next, split_index with N/32 steps
     const uint16_t* gain_next;
-    float* part_ss_out;        // [M][N/16]
+    float* part_ss_out;        // [M][chunks]: 16-column chunks, or the panel GEMM's column groups
     // EPI_QKV
     uint16_t* q_out;     // split bf16 queries in the attention's operand order (q_index)
     int q_row_tiles;     // query-row tiles of 16 per (sequence, KV head)
@@ -198,6 +198,8 @@ struct AttnArgs {
                          // LDS, 2 both once the first is in LDS
 };
 
+constexpr int EMBED_SS = 4;   // sums of squares per row the embedding kernel writes (one per wavefront)
+
 struct EmbedArgs {
     const int32_t* tokens;  // source 0: [batch][k]
     const int32_t* anchor;  // sources 1, 2: [batch]
@@ -208,7 +210,7 @@ struct EmbedArgs {
     const uint16_t* gain;   // first layer's attention RMSNorm gain
     float* x;
     uint16_t* xg;           // split x * gain, split_index with hidden/32 steps
-    float* part_ss;         // [M][hidden/16]
+    float* part_ss;         // [M][EMBED_SS]
     uint32_t* status;
     unsigned* tile_ctr;     // [n_tile_ctr] dynamic tile counters of this pass's GEMMs, zeroed here
     int n_tile_ctr;
@@ -287,45 +289,30 @@ hipError_t launch_embed(const EmbedArgs& a, hipStream_t s);
 bool gemm_norm_supported(int ks);
 int gemm_norm_max_waves(int ks);
 hipError_t launch_gemm_norm(int epi, int ks, int waves, int grid, const GemmArgs& a, hipStream_t s);
-// Streamed GEMM: 16*mt rows x 16*ct columns per workgroup, nw wavefronts split K.
-// normed: the operand is an RMSNorm output (per-row scale from part_ss).
-// With a.W2 set (EPI_RESID only) the reduction continues over the second source.
-hipError_t launch_gemm_stream(int epi, int mt, int ct, int nw, int grid_x, int grid_y, const GemmArgs& a,
-                              hipStream_t s);
-// Normed multi-tile GEMM for 17..64 rows (EPI_QKV, EPI_SWIGLU, EPI_LMHEAD) with the K split
-// into slices of gemm_normk_kstep_span(M) k-steps (grid grid_x x slices); the slices meet in
-// `part` (n_tiles * slices * 256 * MT floats) through one counter per column tile in `tctr`
-// (zero before the launch and zero again after it).  LM head: n_parts = grid_x * slices.
-// Needs ceil(n_tiles / grid_x) <= gemm_normk_max_tiles().
-bool gemm_normk_supported(int epi, int M);
-int gemm_normk_kstep_span(int M);
-int gemm_normk_max_tiles();
-hipError_t launch_gemm_normk(int epi, int grid_x, const GemmArgs& a, float* part, unsigned* tctr, hipStream_t s);
-// Split-K GEMM (EPI_RESID, EPI_QKV or EPI_SWIGLU; M <= 64, no second source): ct column
-// tiles per workgroup (2..4), the reduction cut into ksplit slices (1..SPLITK_MAX) whose
-// partials meet in `part` (ceil(n_tiles/ct) * ksplit * 256*ct*MT floats, MT = 1, 2 or 4 row
-// tiles for M <= 16, 32, 64; unused with ksplit = 1); `ctr`
-// holds one counter per column group, zero before the launch and zero again after it.
-// The normed epilogues take the per-row RMSNorm scale from part_ss as the other GEMMs do.
+// Streamed GEMM (M <= 16): 16*ct columns per workgroup, nw wavefronts split K.  The normed epilogues form
+// the per-row scale from part_ss.  With a.W2 set (EPI_RESID only) the reduction continues over the second
+// source.
+hipError_t launch_gemm_stream(int epi, int ct, int nw, int grid_x, const GemmArgs& a, hipStream_t s);
+// Split-K GEMM (EPI_RESID or EPI_QKV; M <= 16, no second source): ct column tiles per workgroup (2..4), the
+// reduction cut into ksplit slices (1..SPLITK_MAX) whose partials meet in `part`
+// (ceil(n_tiles/ct) * ksplit * 256*ct floats; unused with ksplit = 1); `ctr` holds one counter per column
+// group, zero before the launch and zero again after it.
 constexpr int SPLITK_MAX = 8;
 bool gemm_splitk_supported(int epi, int M, int ct);
 hipError_t launch_gemm_splitk(int epi, int ct, int ksplit, const GemmArgs& a, float* part, unsigned* ctr,
                               hipStream_t s);
-// Tiled GEMM for M > 64 (no second source): 128 x 128 output tiles.  Needs K % 32 == 0, an
-// even k-step count and the A operand allocated for rows up to a multiple of
-// gemm_tile_row_pad().  gemm_tile_parts gives the number of column groups (the argmax
-// partials per row of the LM head).  ksplit > 1 (not for the LM head) cuts K into that many
-// slices of whole stages (at most gemm_tile_stages): `part` holds gemm_tile_part_floats_per_wg()
-// floats per (tile group, slice) and `ctr` one counter per tile group (gemm_tile_groups), zero
-// before the launch and zero again after it.
-bool gemm_tile_supported(int M, int K, int ksteps);
-int gemm_tile_row_pad();
-int gemm_tile_parts(int n_tiles);
-int gemm_tile_groups(int M, int n_tiles);
-int gemm_tile_stages(int ksteps);
-size_t gemm_tile_part_floats_per_wg();
-int gemm_tile_wgs_per_cu();   // workgroups of the tiled GEMM resident per CU
-hipError_t launch_gemm_tile(int epi, const GemmArgs& a, int ksplit, float* part, unsigned* ctr, hipStream_t s);
+// Panel GEMM (every projection of more than 16 rows): a workgroup takes 16*rt rows x 16*wc*ct columns and
+// one of ksplit K slices (each at least one stage of kb k-steps); the operand must be allocated for whole
+// row groups.  ksplit > 1: `part` holds 256*rt*wc*ct floats per (row group, column group, slice) and `ctr`
+// one counter per (row group, column group), zero before the launch and zero again after it.  The LM head
+// writes one argmax key per row and column group.
+struct PanelShape {
+    int rt, wc, ct, kb;
+};
+int gemm_panel_shapes();
+PanelShape gemm_panel_shape(int i);
+inline bool gemm_panel_narrow(PanelShape p) { return p.wc == 4 && p.ct == 1; }   // the shapes EPI_SPLIT has
+hipError_t launch_gemm_panel(int epi, int shape, const GemmArgs& a, int ksplit, float* part, unsigned* ctr, hipStream_t s);
 // kh: key halves per stage (2 when the unit has at most 4 row tiles, else 1); 8 wavefronts per workgroup.
 hipError_t launch_attention(int head_dim, int kh, int zslices, int units, const AttnArgs& a, hipStream_t s);
 hipError_t launch_attention_combine(int head_dim, int units, int rows, const AttnArgs& a, hipStream_t s);

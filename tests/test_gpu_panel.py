@@ -1,0 +1,78 @@
+"""The panel GEMM (every projection of more than 16 rows): each workgroup shape and K-slice count against
+the oracle, at the sizes where tiles, stages and slices do not divide.
+
+Tolerance.  Every product carries its activation as a bf16 value and its bf16 remainder, a relative error of
+at most 2^-17 per site, on f32 sums.  A pass of two layers has seven such sites per layer and the final norm:
+at most 15 * 2^-17 = 1.2e-4 where nothing amplifies them; the oracle's own f32 sums are below 1e-5.
+"""
+import numpy as np
+import pytest
+
+from gpu_common import log, rel_err
+from oracle import nld_oracle as O
+from synth.workloads import LazyWeights, ModelShape, SHAPE_TINY, tokens as synth_tokens
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+TOL = 1.2e-4
+
+# hidden 160: five k-steps (no whole number of stages); ffn 88: two k-steps and a partial one, 11 gate/up
+# tiles; vocab 333: a partial column tile; a LoRA rank of one k-step
+ODD = ModelShape(n_layers=2, hidden=160, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=88, vocab=333, lora_rank=32,
+                 lora_alpha=64.0)
+LONG = ModelShape(**{**SHAPE_TINY.__dict__, "hidden": 512, "ffn": 1072})   # enough stages for several slices
+SHAPES = {2: range(0, 5), 4: range(5, 9), 8: range(9, 13)}                # by row tiles
+NAMES = ("O", "DOWN", "QKV", "GU", "LM")
+
+
+@pytest.fixture(scope="module")
+def R():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2607_05722_amd import runtime
+    return runtime
+
+
+@pytest.fixture(scope="module", params=["odd", "long"])
+def model(R, request):
+    shape = ODD if request.param == "odd" else LONG
+    src = LazyWeights(shape, 11)
+    return {"shape": shape, "w": O.OracleWeights(shape, src, np.float32), "m": R.DeviceModel(shape, src)}
+
+
+def run(R, t, batch, k, mode):
+    shape = t["shape"]
+    tok = synth_tokens(shape, 11, "panel.%d.%d" % (batch, k), (batch, k))
+    okv = O.OracleKV(shape, batch, 128, np.float32)
+    ref, _, _ = O.block_forward(t["w"], okv, tok, mode)
+    cache, ws = R.DeviceCache(shape, batch, 128), R.Workspace(t["m"], batch, k, 128)
+    m = R.VERIFY if mode == O.VERIFY else R.DRAFT
+    got = [R.block_forward(t["m"], cache, ws, torch.from_numpy(tok).cuda(), m) for _ in range(2)]
+    assert R.read_device_status(ws) == 0
+    g = got[0][0].cpu().numpy()
+    assert torch.equal(got[0][0], got[1][0])   # slices add up in one order, whichever arrives last
+    assert np.array_equal(got[0][1].cpu().numpy(), np.argmax(g, axis=-1))
+    return rel_err(g, ref)
+
+
+@pytest.mark.parametrize("batch,k", [(1, 17), (1, 32), (3, 11), (1, 64), (5, 13), (2, 64), (3, 43)])
+@pytest.mark.parametrize("slices", [1, 3])
+def test_every_shape(R, model, monkeypatch, batch, k, slices):
+    """17..32, 33..64 and more than 64 rows (one and two row groups), every shape forced on every projection."""
+    rt = 2 if batch * k <= 32 else 4 if batch * k <= 64 else 8
+    for i in SHAPES[rt]:
+        for n in NAMES:
+            kb = {0: 2, 1: 4, 2: 4, 3: 2, 4: 4, 5: 2, 6: 4}.get(i, 2)
+            steps = (model["shape"].ffn if n == "DOWN" else model["shape"].hidden) // 32
+            monkeypatch.setenv("NLD_PANEL_" + n, "%d,%d" % (i, max(1, min(slices, steps // kb))))
+        for mode in (O.VERIFY, O.DRAFT):
+            e = run(R, model, batch, k, mode)
+            log("panel shape %d slices %d rows %d %s: rel err %.2e" % (i, slices, batch * k, mode, e))
+            assert e <= TOL
+
+
+@pytest.mark.parametrize("batch,k", [(1, 16), (1, 17), (2, 32), (2, 33), (9, 15)])
+def test_planned(R, model, batch, k):
+    """The plans the library picks, on both sides of each row-tile boundary."""
+    for mode in (O.VERIFY, O.DRAFT):
+        assert run(R, model, batch, k, mode) <= TOL
