@@ -115,7 +115,7 @@ namespace {
 
 // ---------------------------------------------------------------- workspace layout
 struct Layout {
-    int M, Mpad, units, n_splits, chunk, row_tiles, attn_kh, attn_z, n_parts, rows_pad, lm_tiles, lm_parts;
+    int M, Mpad, units, n_splits, chunk, row_tiles, attn_kh, attn_waves, attn_z, n_parts, rows_pad, lm_tiles, lm_parts;
     bool attn_items;         // length-aware attention work (batches)
     int n_tile_ctr;          // tile counters in all, zeroed by the embedding kernel at the start of a pass
     int n_ctr, ctr0;         // K slices: counters (one per group of tiles) from tile counter ctr0
@@ -135,31 +135,36 @@ Layout make_layout(const nld_config& c, int batch, int k, int max_len, int quad_
     const int G = c.n_q_heads / c.n_kv_heads;
     L.row_tiles = cdiv(G * k, 16);
     L.attn_kh = L.row_tiles <= 4 ? 2 : 1;          // wavefronts per row tile (each takes half of a stage's keys)
-    L.attn_z = cdiv(L.row_tiles, 8 / L.attn_kh);
-    L.rows_pad = L.attn_z * (8 / L.attn_kh) * 16;
     L.lm_tiles = cdiv(c.vocab, 16);
     L.lm_parts = L.lm_tiles;  // upper bound on argmax partials per row (one per LM-head workgroup)
-    // key splits: aim for about `target` workgroups, chunks a multiple of 64 keys.  One
-    // workgroup per CU while there are few (unit, row slice) pairs (batch 1: each workgroup
-    // is then a short latency chain); up to four per CU when there are many, so that long
-    // and ragged key ranges are cut finer than one per CU.
-    // With more than one sequence the workgroups take length-aware items (only splits holding
-    // committed keys get a workgroup), so the splits may be cut finer: with one row slice the plan
-    // aims at NLD_ATTN_ITEMS_FINER (default 2) times as many workgroups as it would at max_len.
-    // (Measured: 8B batch 32, ragged prefixes, one slice: 198 us against 214 us at 1x and 254 us
-    // without items; 14B batch 8, equal prefixes, two slices: 2x 366 us against 341 us at 1x.)
+    // Attention.  Partials: room for `room` rows per unit, from a first cut of max_len into key splits that
+    // aims for about `target` workgroups of 8 wavefronts.
     L.attn_items = batch > 1 && !env_int("NLD_ATTN_NO_ITEMS", 0);
-    const int pairs = L.units * L.attn_z;
-    const int finer = L.attn_items ? env_int("NLD_ATTN_ITEMS_FINER", L.attn_z == 1 ? 2 : 1) : 1;
+    const int z8 = cdiv(L.row_tiles, 8 / L.attn_kh), pairs = L.units * z8, max_splits = cdiv(max_len, 64);
+    auto cut = [&](int ns) { L.chunk = cdiv(cdiv(max_len, std::max(1, std::min(std::min(ns, max_splits), 255))), 64) * 64; };
+    const int finer = L.attn_items ? env_int("NLD_ATTN_ITEMS_FINER", z8 == 1 ? 2 : 1) : 1;
     const int target = env_int("NLD_ATTN_TARGET_WG", finer * device_cus() * std::min(4, std::max(1, pairs / 16)));
-    int ns = target / (L.units * L.attn_z) - 1;    // one workgroup per (unit, row slice) is the block part
-    const int max_splits = cdiv(max_len, 64);
-    if (ns > max_splits) ns = max_splits;
-    if (ns > 255) ns = 255;   // the merge handles up to 256 partials per row
-    if (ns < 1) ns = 1;
-    L.chunk = cdiv(cdiv(max_len, ns), 64) * 64;
+    cut(target / pairs - 1);
+    const size_t room = (size_t)(cdiv(max_len, L.chunk) + 1) * z8 * (8 / L.attn_kh) * 16;
+    // One sequence: that cut, a workgroup of 8 wavefronts (kh 2) or one per row tile; the merge handles up to
+    // 256 partials per row.  A batch: workgroups as wide as the rows need, and items of about 1024 keys where
+    // the capacity has at least four of those per CU, else of 384, so that the CUs share few sequences evenly
+    // (an item's own start, its place in the list, queries and first stage, is about 6 us, or five stages);
+    // never more than fit the room at 16 rows per row tile.  Attention and merge at 1024 / 384 keys: batch 32
+    // at 8064 keys, k = 1 200 / 214 us; batch 5 at 3000 keys, k = 24 45 / 28 us; batch 2 at 4000 keys, k = 16
+    // 31 / 20 us.  NLD_ATTN_ITEM_KEYS overrides.
+    const int zmax = L.attn_kh == 2 ? 4 : 12;
+    L.attn_z = cdiv(L.row_tiles, zmax);
+    const int rz = cdiv(L.row_tiles, L.attn_z);
+    L.attn_waves = L.attn_kh == 2 ? (L.attn_items ? 2 * rz : 8) : rz;
+    L.rows_pad = L.row_tiles * 16;
+    if (L.attn_items) {
+        const int parts = (int)std::min<size_t>(room / L.rows_pad, 255);
+        const bool many = (size_t)L.units * L.attn_z * cdiv(max_len, 1024) >= (size_t)4 * device_cus();
+        cut(std::min(parts, cdiv(max_len, std::max(1, env_int("NLD_ATTN_ITEM_KEYS", many ? 1024 : 384)))));
+    }
     L.n_splits = cdiv(max_len, L.chunk);
-    L.n_parts = L.n_splits + 1;   // prefix splits + the block part (key halves merge inside the workgroup)
+    L.n_parts = L.n_splits + (L.attn_items ? 0 : 1);
 
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -199,8 +204,8 @@ Layout make_layout(const nld_config& c, int batch, int k, int max_len, int quad_
     L.n_tile_ctr = L.ctr0 + L.n_ctr;
     L.tile_ctr = take(4 * (size_t)L.n_tile_ctr);
     L.part = take(4 * L.part_floats);
-    L.po = take(4 * (size_t)L.units * L.n_parts * L.rows_pad * c.head_dim);
-    L.pml = take(4 * 2 * (size_t)L.units * L.n_parts * L.rows_pad);
+    L.po = take(4 * (size_t)L.units * room * c.head_dim);
+    L.pml = take(4 * 2 * (size_t)L.units * room);
     L.blk_k = take(2 * (size_t)L.units * 2 * 64 * c.head_dim);   // block K/V, split: [unit][hi, lo][64][D]
     L.blk_v = take(2 * (size_t)L.units * 2 * 64 * c.head_dim);
     L.lora_t = take(4 * (size_t)L.Mpad * c.lora_rank);   // split lora_scale * (A o), draft passes only
@@ -594,14 +599,9 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
         at_.n_seq = batch;
         at_.scale_log2 = (float)(1.4426950408889634 / sqrt((double)D));
         at_.plain = plain & (SITE_P | SITE_O);
-        // Prefix stages 1 and 2 are requested once stage 0 is in LDS: requested with it, the three
-        // stages of every workgroup arrive interleaved and stage 0 comes late (8B shapes, k = 16:
-        // 16.55 against 17.43 us per attention and merge).  NLD_ATTN_LATE = 0 / 1: all at once /
-        // stage 2 only.
-        at_.late = env_int("NLD_ATTN_LATE", 2);
         {
             TraceScope ts(NLD_TRACE_ATTENTION, s);
-            HIP_TRY(launch_attention(D, L.attn_kh, L.attn_z, L.units, at_, s));
+            HIP_TRY(launch_attention(D, L.attn_kh, L.attn_waves, L.attn_z, L.units, at_, s));
             HIP_TRY(launch_attention_combine(D, L.units, (nq / nkv) * k, at_, s));
         }
 

@@ -1585,20 +1585,25 @@ hipError_t launch_gemm_panel(int epi, int shape, const GemmArgs& a, int ksplit, 
 }
 
 // =====================================================================================
-// Block-masked GQA attention.  Workgroup = (key split, sequence x KV head, row slice);
-// one compute wavefront per 16 query rows of the GQA group (rows = heads of the
-// group x block rows).  The committed prefix [0, P) is cut into key splits that
-// read the bf16 cache; one more workgroup per (unit, row slice), the block part,
-// covers the block's own k keys (causal or bidirectional per the mode) from the
-// split K/V the QKV epilogue left in the workspace, so this pass sees its own keys
-// and values at about 16 significant bits while the cache keeps bf16.  Keys stream
-// through LDS in stages of 64 (K rows and the transposed V tile, XOR-swizzled for
-// conflict-free operand reads), double buffered: the next stage's global loads are
-// in flight while the current one is multiplied.  S^T = K Q^T on MFMA puts one
-// query row per lane column, so a row's softmax statistics live in lanes r, r+16,
-// r+32, r+48 and P^T is already the B operand of O^T = V^T P^T.  Queries and P are
-// split operands.  Online softmax in base 2, fp32; every workgroup writes one
-// partial (max, sum, unnormalised output) per row for the merge.
+// Block-masked GQA attention.  Workgroup = (key split, sequence x KV head, row slice); rows = heads of
+// the GQA group x block rows, in tiles of 16.  The committed prefix [0, P) is cut into key splits that
+// read the bf16 cache; the block part covers the block's own k keys (causal or bidirectional per the
+// mode) from the split K/V the QKV epilogue left in the workspace, so this pass sees its own keys and
+// values at about 16 significant bits while the cache keeps bf16.  With one sequence the block part is a
+// workgroup of its own; in a batch the last split of a unit takes it along.
+//
+// Keys stream through LDS in stages of 64 (K rows and the transposed V tile, XOR-swizzled for
+// conflict-free operand reads).  The stages go from global memory straight to LDS (global_load_lds, the
+// swizzle on the global side), so no register holds keys on their way: with NS = 2 slots the kernel fits
+// 128 registers and two workgroups share a CU, one loading while the other computes; a batch has work for
+// both.  One sequence has at most one workgroup per CU and takes NS = 4, three stages ahead.  (Staged through
+// registers the kernel took 224 registers, one workgroup per CU: ten round trips of latency in a row.)
+//
+// KH = 2 (up to four row tiles): two wavefronts per row tile, each with half of a stage's keys; KH = 1: one.
+// S^T = K Q^T on MFMA puts one query row per lane column, so a row's softmax statistics live in lanes r, r+16,
+// r+32, r+48 and P^T is already the B operand of O^T = V^T P^T.  Queries and P are split operands.  Online
+// softmax in base 2, fp32; every workgroup writes one partial (max, sum, unnormalised output) per row for the
+// merge.
 // =====================================================================================
 template <int D>
 struct AttnCfg {
@@ -1606,6 +1611,7 @@ struct AttnCfg {
     static constexpr int KCHUNKS = 64 * KCH;             // K tile chunks per stage
     static constexpr int VCHUNKS = D * 8;                // V tile chunks per stage (D rows x 64 keys)
     static constexpr int CHUNKS = KCHUNKS + VCHUNKS;
+    static constexpr int BLOCKS = CHUNKS / 64;           // 1 KiB blocks per stage
 };
 
 // XOR swizzles (chunk index within a row): make the 16 rows read by one MFMA
@@ -1623,15 +1629,37 @@ __device__ __forceinline__ int stage_key(int tau, int rho) {
     return 32 * (tau >> 1) + 8 * (rho >> 2) + 4 * (tau & 1) + (rho & 3);
 }
 
+// 16 bytes per lane from global memory to LDS at byte `dst` + 16 * lane (dst uniform).  Inline assembly: the
+// compiler waits for every such load before any later LDS read, which would take the stages one by one.
+// It has no register result; stage_wait() and a barrier stand between it and the reads.
+__device__ __forceinline__ void load_to_lds(const void* src, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory", "m0");
+}
+// at most N vector memory operations of this wavefront still under way
+template <int N>
+__device__ __forceinline__ void stage_wait() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// max (or sum) over the lanes r, r+16, r+32, r+48, in every lane
+__device__ __forceinline__ float rows_max(float v) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 // committed length of sequence b as the attention reads it: clamped to [0, max_len]
 __device__ __forceinline__ int attn_length(const AttnArgs& a, int b) {
     const int p = a.lengths[b];
     return p < 0 ? 0 : (p > a.max_len ? a.max_len : p);
 }
+// work items of one KV head of a sequence with committed length P (batches): its prefix splits, the last of
+// which takes the block part along
+__device__ __forceinline__ int attn_items(const AttnArgs& a, int P) { return max(1, (P + a.chunk - 1) / a.chunk); }
 
-// Length-aware work item `item` -> (unit, split), split == n_splits for the block part; false past
-// the last item.  Wavefront 0 scans the sequences' item counts (nkv * (ceil(P_b / chunk) + 1)) 64
-// at a time; the result goes to every thread through LDS.
+// Length-aware work item `item` -> (unit, split); false past the last item.  Wavefront 0 scans the
+// sequences' item counts 64 at a time; the result goes to every thread through LDS.
 __device__ bool attn_item(const AttnArgs& a, int item, int* unit, int* split) {
     __shared__ int su_s, ss_s;
     if (threadIdx.x < 64) {
@@ -1639,8 +1667,8 @@ __device__ bool attn_item(const AttnArgs& a, int item, int* unit, int* split) {
         int base = 0, su = -1, ss = 0;
         for (int b0 = 0; b0 < a.n_seq && su < 0; b0 += 64) {
             const int b = b0 + lane;
-            const int nc = b < a.n_seq ? (attn_length(a, b) + a.chunk - 1) / a.chunk : 0;
-            const int cnt = b < a.n_seq ? (nc + 1) * a.n_kv_heads : 0;
+            const int ni = b < a.n_seq ? attn_items(a, attn_length(a, b)) : 0;
+            const int cnt = ni * a.n_kv_heads;
             int incl = cnt;
 #pragma unroll
             for (int off = 1; off < 64; off <<= 1) {
@@ -1652,9 +1680,9 @@ __device__ bool attn_item(const AttnArgs& a, int item, int* unit, int* split) {
             const unsigned long long who = __ballot(mine);
             if (who) {
                 const int src = __ffsll((long long)who) - 1;
-                const int r = __shfl(item - base - excl, src), ncs = __shfl(nc, src);
-                su = (b0 + src) * a.n_kv_heads + r / (ncs + 1);
-                ss = r % (ncs + 1) == ncs ? a.n_splits : r % (ncs + 1);
+                const int r = __shfl(item - base - excl, src), nis = __shfl(ni, src);
+                su = (b0 + src) * a.n_kv_heads + r / nis;
+                ss = r % nis;
             }
             base += __shfl(incl, 63);
         }
@@ -1669,101 +1697,91 @@ __device__ bool attn_item(const AttnArgs& a, int item, int* unit, int* split) {
     return su_s >= 0;
 }
 
-template <int D, int KH>
-__global__ void __launch_bounds__(512) attention_kernel(AttnArgs a) {
+template <int D, int KH, int NS>
+__global__ void __launch_bounds__(KH == 2 ? 512 : 768) __attribute__((amdgpu_waves_per_eu(KH == 2 && NS == 2 ? 4 : 1)))
+attention_kernel(AttnArgs a) {
     typedef AttnCfg<D> C;
     constexpr int DC = D / 32;
     constexpr int DT = D / 16;
-    constexpr int NT = 512;                    // threads per workgroup
-    constexpr int CPT = C::CHUNKS / NT;        // stage chunks per thread
-    constexpr int RZ = 8 / KH;                 // row tiles per workgroup
     constexpr int TPW = 4 / KH;                // S tiles (16 keys) per wavefront per stage
     constexpr float RESCALE_SLACK = 8.0f;      // log2 headroom before the reference max moves
-    // two stage slots, each K tile (KCHUNKS) followed by the V tile (VCHUNKS)
-    __shared__ uint4 lds[2 * C::CHUNKS];
+    // stage slots, each K tile (KCHUNKS) followed by the V tile (VCHUNKS)
+    __shared__ uint4 lds[NS * C::CHUNKS];
 
     NLD_TS(TL_ATTENTION, 0);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
     const int r = lane & 15, g = lane >> 4;
+    const int RZ = nw / KH;                    // row tiles per workgroup
     int split = blockIdx.x, unit = blockIdx.y;
-    if (a.items && !attn_item(a, blockIdx.x, &unit, &split)) return;   // the whole workgroup leaves
-    const bool blockpart = split == a.n_splits;   // the block's own keys, read in split form
+    if (a.items) {
+        if (!attn_item(a, blockIdx.x, &unit, &split)) return;   // the whole workgroup leaves
+        unit = __builtin_amdgcn_readfirstlane(unit);
+        split = __builtin_amdgcn_readfirstlane(split);
+    }
     const int nkv = a.n_kv_heads, G = a.n_q_heads / nkv;
-    const int b = unit / nkv, kvh = unit % nkv;
+    const int b = unit / nkv;
     const int k = a.k_blk, R = G * k;
-    const int kh = wave / RZ;                  // which half of each stage's keys (KH == 2)
-    const int rt = blockIdx.z * RZ + (wave % RZ);
+    const int kh = KH == 2 ? wave / RZ : 0;    // which half of each stage's keys
+    const int rt = blockIdx.z * RZ + wave % RZ;
     const bool computes = rt < a.row_tiles;
     const int row = rt * 16 + r;
     const bool row_ok = computes && row < R;
     const int j = row_ok ? row % k : 0;
 
     const int P_raw = a.lengths[b];   // requested first; the loads below do not depend on it
-    // Block columns this row sees.  Verify: c <= j.  Draft: every column from row bidir_from on.
-    // Quadratic layout (mode 2, chain length qk): chain row j sees chain columns c <= j; a mask of
-    // group grp sees chain columns c <= grp and the columns [lo_c, hi_c) of its own group.
+    // Block columns this row sees: c <= lim and, in the quadratic layout, [lo_c, lo_c + n_c).  Verify: c <= j.
+    // Draft: every column from row bidir_from on.  Quadratic layout (mode 2, chain length qk): chain row j sees
+    // chain columns c <= j; a mask of group grp sees chain columns c <= grp and the columns of its own group.
     const int qk = a.quad_k;
-    const bool quad = a.mode == 2;
-    const bool bidir_row = (a.mode == 1) && (j >= a.bidir_from);
-    const int grp = (quad && j >= qk) ? (j - qk) / qk : j;
-    const int lo_c = (quad && j >= qk) ? qk + grp * qk : k, hi_c = (quad && j >= qk) ? lo_c + qk : k;
-    int split_beg = split * a.chunk;   // prefix splits: first key of the split (< max_len)
+    const bool qmask = a.mode == 2 && j >= qk;
+    const int grp = qmask ? (j - qk) / qk : 0;
+    const int lim = qmask ? grp : (a.mode == 1 && j >= a.bidir_from ? k : j);
+    const int lo_c = qmask ? qk + grp * qk : 0, n_c = qmask ? qk : 0;
 
-    const size_t head_off = (size_t)(b * nkv + kvh) * a.max_len * D;
-    const uint16_t* kbase = a.kc + head_off;   // where gload reads stages from
+    const size_t head_off = (size_t)unit * a.max_len * D;
+    const uint16_t* kbase = a.kc + head_off;
     const uint16_t* vbase = a.vc + head_off;
+    const uint16_t* bkbase = a.blk_k + (size_t)unit * 2 * 64 * D;   // the block's keys and values: hi, then lo
+    const uint16_t* bvbase = a.blk_v + (size_t)unit * 2 * 64 * D;
 
-    // per-thread stage chunks: global offsets within a stage and LDS slots (swizzled)
-    int goff[CPT], loff[CPT];
-#pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-        const int q = threadIdx.x + i * NT;
-        if (q < C::KCHUNKS) {
-            const int kr = q / C::KCH, c = q % C::KCH;
-            goff[i] = q * 8;                                   // relative to kbase + kb * D
-            loff[i] = kr * C::KCH + (c ^ kswz<D>(kr));
-        } else {
-            const int qv = q - C::KCHUNKS, d = qv >> 3, c = qv & 7;
-            goff[i] = qv * 8;                                  // relative to the V tile
-            loff[i] = C::KCHUNKS + d * 8 + (c ^ vswz(d));      // V slots follow the K slots
+    // 64 keys from kp and vp into a slot: wavefront w takes 1 KiB blocks w, w + nw, ...  LDS position p of a
+    // row holds chunk p ^ swizzle(row).
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+    auto dma = [&](const uint16_t* kp, const uint16_t* vp, int slot) __attribute__((always_inline)) {
+        const uint32_t dst = lds0 + (uint32_t)slot * C::CHUNKS * 16;
+#pragma unroll 1
+        for (int i = wave; i < C::KCHUNKS / 64; i += nw) {
+            const int q = i * 64 + lane, kr = q / C::KCH, c = (q % C::KCH) ^ kswz<D>(kr);
+            load_to_lds(kp + (kr * C::KCH + c) * 8, __builtin_amdgcn_readfirstlane(dst + i * 1024));
         }
-    }
-    struct Stage {
-        uint4 v[CPT];
-    };
-    auto gload = [&](int kb) __attribute__((always_inline)) {
-        Stage st;
-        const uint16_t* kp = kbase + (size_t)kb * D;
-        const uint16_t* vp = vbase + (size_t)(kb >> 6) * D * 64;
-#pragma unroll
-        for (int i = 0; i < CPT; ++i) {
-            const bool is_k = threadIdx.x + i * NT < C::KCHUNKS;   // resolved at compile time for most i
-            st.v[i] = *(const uint4*)((is_k ? kp : vp) + goff[i]);
+#pragma unroll 1
+        for (int i = wave; i < C::VCHUNKS / 64; i += nw) {
+            const int q = i * 64 + lane, d = q >> 3, c = (q & 7) ^ vswz(d);
+            load_to_lds(vp + (d * 8 + c) * 8, __builtin_amdgcn_readfirstlane(dst + C::KCHUNKS * 16 + i * 1024));
         }
-        return st;
     };
-    auto lstore = [&](const Stage& st, int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < CPT; ++i) lds[buf * C::CHUNKS + loff[i]] = st.v[i];
+    auto dma_keys = [&](int kb, int slot) __attribute__((always_inline)) {
+        dma(kbase + (size_t)kb * D, vbase + (size_t)kb * D, slot);   // kb is a multiple of 64: a V tile's start
     };
+    constexpr int PB = C::BLOCKS / 8;   // a wavefront's loads per stage (NS > 2 runs with 8 wavefronts)
 
-    // operand offsets in LDS (per lane, fixed for every stage)
-    int koff[TPW][DC], voff[TPW / 2][DT];
+    // Operand positions in LDS: K chunk c of S tile tau at kidx[c] + tau's rows, V rows of 16 dims apart.
+    // (The swizzles only see row bits that tau and the dim tile leave alone.)
+    int kidx[DC], vidx[TPW / 2];
+    {
+        const int kr = stage_key(TPW * kh, r);
 #pragma unroll
-    for (int tt = 0; tt < TPW; ++tt) {
-        const int kr = stage_key(TPW * kh + tt, r);
+        for (int c = 0; c < DC; ++c) kidx[c] = kr * C::KCH + ((4 * c + g) ^ kswz<D>(kr));
 #pragma unroll
-        for (int c = 0; c < DC; ++c) koff[tt][c] = kr * C::KCH + ((4 * c + g) ^ kswz<D>(kr));
+        for (int kk = 0; kk < TPW / 2; ++kk) vidx[kk] = C::KCHUNKS + r * 8 + ((4 * ((TPW / 2) * kh + kk) + g) ^ vswz(r));
     }
-#pragma unroll
-    for (int kk = 0; kk < TPW / 2; ++kk) {
-        const int ks = (TPW / 2) * kh + kk;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-            const int d = 16 * dt + r;
-            voff[kk][dt] = d * 8 + ((4 * ks + g) ^ vswz(d));
-        }
-    }
+
+    // The first stage is requested before the committed length is known: a prefix split's first 64 keys
+    // (always inside the cache; masked below if they are not committed), or the block part's hi halves.
+    const bool blockonly = !a.items && split == a.n_splits;
+    int split_beg = split * a.chunk;   // prefix splits: first key of the split (< max_len)
+    if (blockonly) dma(bkbase, bvbase, 0);
+    else dma_keys(split_beg, 0);
 
     const uint4 zero4 = {0u, 0u, 0u, 0u};
     uint4 qb[DC], ql[DC];   // split queries: hi and lo operands
@@ -1775,46 +1793,30 @@ __global__ void __launch_bounds__(512) attention_kernel(AttnArgs a) {
             ql[c] = row_ok ? *(const uint4*)(qp + (size_t)c * 1024 + SPLIT_LO) : zero4;
         }
     }
-    // The first stage is requested before the committed length is known: a prefix split's
-    // first 64 keys (always inside the cache; masked below if they are not committed), or
-    // the block part's hi and lo halves.
-    Stage s0{}, s1{}, s2{};
-    if (blockpart) {
-        const size_t kv_unit = (size_t)unit * 2 * 64 * D;
-        kbase = a.blk_k + kv_unit;
-        vbase = a.blk_v + kv_unit;
-        s0 = gload(0);
-        kbase += 64 * D;
-        vbase += 64 * D;
-        s1 = gload(0);
-    } else {
-        s0 = gload(split_beg);
-    }
 
-    int P = P_raw < 0 ? 0 : (P_raw > a.max_len ? a.max_len : P_raw);
-    // One sequence: the n_splits prefix splits are cut from the committed length, chunk =
-    // ceil(P / n_splits) rounded up to whole stages (at most the plan's chunk, which was cut from
-    // max_len), so that a cache much longer than its prefix still spreads the prefix over every
-    // split.  The first stage went out at the plan's split start; it is requested again where
-    // the two differ.
+    const int P = P_raw < 0 ? 0 : (P_raw > a.max_len ? a.max_len : P_raw);
+    // One sequence: the n_splits prefix splits are cut from the committed length, chunk = ceil(P / n_splits)
+    // rounded up to whole stages (at most the plan's chunk, which was cut from max_len), so that a cache much
+    // longer than its prefix still spreads the prefix over every split.  The first stage went out at the
+    // plan's split start; it is requested again where the two differ.
     int chunk = a.chunk;
-    if (!a.items && !blockpart) {
+    if (!a.items && !blockonly) {
         chunk = max(64, ((P + a.n_splits - 1) / a.n_splits + 63) / 64 * 64);
         const int beg = split * chunk;
         if (beg != split_beg) {
             split_beg = beg;
-            if (beg < P) s0 = gload(beg);   // beg < P <= max_len, a multiple of 64: inside the cache
+            if (beg < P) {   // beg < P <= max_len, a multiple of 64: inside the cache
+                stage_wait<0>();   // the two requests write the same slot
+                dma_keys(beg, 0);
+            }
         }
     }
-    // prefix splits cover committed keys [kbeg, kend) of [0, P); the block part covers [P, P + k)
-    const int kbeg = blockpart ? P : split_beg;
-    const int kend = blockpart ? P + k : min(kbeg + chunk, P);
-    const int nst = blockpart ? 1 : (kend > kbeg ? (kend - kbeg + 63) / 64 : 0);
+    // committed keys [split_beg, kend) of [0, P), then (the unit's last item, or the block's own workgroup)
+    // the block's keys [P, P + k)
+    const int kend = min(split_beg + chunk, P);
+    const int nst = blockonly ? 0 : (kend > split_beg ? (kend - split_beg + 63) / 64 : 0);
+    const bool blockpart = blockonly || (a.items && split == attn_items(a, P) - 1);
     NLD_TS(TL_ATTENTION, 1);   // committed length known
-    if (!blockpart) {
-        if (nst > 1 && a.late < 2) s1 = gload(kbeg + 64);
-        if (nst > 2 && a.late < 1) s2 = gload(kbeg + 128);
-    }
 
     f32x4_t acc[DT];
 #pragma unroll
@@ -1823,44 +1825,46 @@ __global__ void __launch_bounds__(512) attention_kernel(AttnArgs a) {
     // so the accumulators are rescaled rarely (any reference gives the same ratio).
     float m_ref = -INFINITY, l_part = 0.f;
 
-    // kb: first key of the stage.  lo_slot: the block part keeps the lo halves of
-    // the block's keys and values in the second stage slot.
-    auto compute = [&](int kb, int buf, bool lo_slot) __attribute__((always_inline)) {
-        if (!computes) return;
-        f32x4_t s[TPW], sl[TPW];
+    // One stage of keys kb .. kb+63 from slot hi; own: the block part, its keys' and values' lo halves in slot
+    // lo; edge: the stage holds keys at or past `end` (or the block's), which are masked.
+    auto stage = [&](int kb, int end, int hi, int lo, auto own, auto edge) __attribute__((always_inline)) {
+        const uint4* kv = lds + hi * C::CHUNKS;
+        const uint4* kvl = lds + lo * C::CHUNKS;
+        f32x4_t s[TPW];
 #pragma unroll
-        for (int tt = 0; tt < TPW; ++tt) {
-            s[tt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            sl[tt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int tt = 0; tt < TPW; ++tt) s[tt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        // The scheduling barriers keep the compiler from reading a whole stage's operands ahead, which takes
+        // more registers than a wavefront has here.
 #pragma unroll
-            for (int c = 0; c < DC; ++c) {
-                const uint4 kop = lds[buf * C::CHUNKS + koff[tt][c]];
+        for (int c = 0; c < DC; ++c) {
+#pragma unroll
+            for (int tt = 0; tt < TPW; ++tt) {
+                const int at = kidx[c] + (32 * (tt >> 1) + 4 * (tt & 1)) * C::KCH;
+                const uint4 kop = kv[at];
                 s[tt] = mfma_16x16x32(kop, qb[c], s[tt]);
-                sl[tt] = mfma_16x16x32(kop, ql[c], sl[tt]);
-                if (lo_slot) sl[tt] = mfma_16x16x32(lds[C::CHUNKS + koff[tt][c]], qb[c], sl[tt]);
+                s[tt] = mfma_16x16x32(kop, ql[c], s[tt]);
+                if constexpr (own) s[tt] = mfma_16x16x32(kvl[at], qb[c], s[tt]);
             }
-            s[tt] += sl[tt];
+            if ((c & 1) || own) __builtin_amdgcn_sched_barrier(0);
         }
-        const bool edge = (kb + 64 > P) || (kb + 64 > kend);   // stage touches the block or the split end
-        float sv[4 * TPW];
-        float mloc = -INFINITY;
+        if constexpr (edge) {
+#pragma unroll
+            for (int tt = 0; tt < TPW; ++tt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int key = kb + stage_key(TPW * kh + tt, 4 * g + i);
+                    const int c = key - P;   // block column (negative: the prefix)
+                    const bool vis = (key < end) & ((c <= lim) | ((unsigned)(c - lo_c) < (unsigned)n_c));
+                    s[tt][i] = vis ? s[tt][i] : -INFINITY;
+                }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        float mloc = s[0][0];
 #pragma unroll
         for (int tt = 0; tt < TPW; ++tt)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float x = s[tt][i] * a.scale_log2;
-                if (edge) {
-                    const int key = kb + stage_key(TPW * kh + tt, 4 * g + i);
-                    const int c = key - P;   // block column (keys < P are the prefix)
-                    const bool vis = key < kend && (key < P || (quad ? ((c < qk && c <= grp) || (c >= lo_c && c < hi_c))
-                                                                     : (c <= j || bidir_row)));
-                    x = vis ? x : -INFINITY;
-                }
-                sv[tt * 4 + i] = x;
-                mloc = fmaxf(mloc, x);
-            }
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+            for (int i = 0; i < 4; ++i) mloc = fmaxf(mloc, s[tt][i]);
+        mloc = rows_max(mloc) * a.scale_log2;      // scale_log2 > 0
         if (mloc > m_ref + RESCALE_SLACK) {        // new reference: rescale what has accumulated
             const float alpha = __builtin_amdgcn_exp2f(m_ref - mloc);   // 0 when m_ref = -inf
             l_part *= alpha;
@@ -1868,69 +1872,102 @@ __global__ void __launch_bounds__(512) attention_kernel(AttnArgs a) {
             for (int dt = 0; dt < DT; ++dt) acc[dt] *= alpha;
             m_ref = mloc;
         }
+        const float m_use = m_ref == -INFINITY ? 0.f : m_ref;   // no key visible yet: every p is exp2(-inf) = 0
         float p[4 * TPW];
         float psum = 0.f;
 #pragma unroll
         for (int e = 0; e < 4 * TPW; ++e) {
-            p[e] = __builtin_amdgcn_exp2f(sv[e] - m_ref);   // -inf - finite -> 0; m_ref finite once any key is visible
+            p[e] = __builtin_amdgcn_exp2f(fmaf(s[e >> 2][e & 3], a.scale_log2, -m_use));
             psum += p[e];
         }
-        if (m_ref == -INFINITY) psum = 0.f;
         l_part += psum;
 #pragma unroll
         for (int kk = 0; kk < TPW / 2; ++kk) {
-            const int ks = (TPW / 2) * kh + kk;          // 32-key PV step within the stage
             // slot jj of lane group g <-> key kb + 32ks + 8g + jj
             uint4 pop, pol;                               // P^T as split operands
             split8(p + 8 * kk, pop, pol, a.plain & SITE_P);
-            if (m_ref == -INFINITY) pop = pol = zero4;
-            const int key0 = kb + 32 * ks + 8 * g;
-            const bool vmask = edge && (key0 + 8 > kend);  // V rows past the valid keys may hold anything
-            auto masked = [&](uint4 vop) __attribute__((always_inline)) {
-                if (!vmask) return vop;
-                uint32_t w[4] = {vop.x, vop.y, vop.z, vop.w};
+            const int key0 = kb + 32 * ((TPW / 2) * kh + kk) + 8 * g;
+            uint32_t vm[4];                               // V rows past the valid keys may hold anything
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    w[e] = (key0 + 2 * e < kend ? (w[e] & 0xFFFFu) : 0u) | (key0 + 2 * e + 1 < kend ? (w[e] & 0xFFFF0000u) : 0u);
-                return uint4{w[0], w[1], w[2], w[3]};
+            for (int e = 0; e < 4; ++e)
+                vm[e] = (key0 + 2 * e < end ? 0xFFFFu : 0u) | (key0 + 2 * e + 1 < end ? 0xFFFF0000u : 0u);
+            auto masked = [&](uint4 v) __attribute__((always_inline)) {
+                return edge ? uint4{v.x & vm[0], v.y & vm[1], v.z & vm[2], v.w & vm[3]} : v;
             };
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
-                const uint4 vop = masked(lds[buf * C::CHUNKS + C::KCHUNKS + voff[kk][dt]]);
+                const int at = vidx[kk] + dt * 128;
+                const uint4 vop = masked(kv[at]);
                 acc[dt] = mfma_16x16x32(vop, pop, acc[dt]);
                 acc[dt] = mfma_16x16x32(vop, pol, acc[dt]);
-                if (lo_slot) acc[dt] = mfma_16x16x32(masked(lds[C::CHUNKS + C::KCHUNKS + voff[kk][dt]]), pop, acc[dt]);
+                if constexpr (own) acc[dt] = mfma_16x16x32(masked(kvl[at]), pop, acc[dt]);
+                if ((dt & 3) == 3 || own) __builtin_amdgcn_sched_barrier(0);
             }
         }
     };
+    struct Yes { constexpr operator bool() const { return true; } };
+    struct No { constexpr operator bool() const { return false; } };
+    const int nfull = kend > split_beg ? (kend - split_beg) / 64 : 0;   // whole stages; the rest masks keys
 
-    if (blockpart) {
-        // one stage (k <= 64): hi halves in slot 0, lo halves in slot 1
-        lstore(s0, 0);
-        lstore(s1, 1);
-        __syncthreads();
-        compute(kbeg, 0, true);
-        __syncthreads();
-    } else {
-        // Stages of 64 keys.  Stage st is multiplied from LDS slot st & 1 while stages st+1
-        // and st+2 are in flight in registers (s1 and s2 by turns; the loop is unrolled by
-        // two so that no register copy waits on a load still in flight).
-        if (nst > 0) lstore(s0, 0);
-        if (nst > 1 && a.late >= 2) s1 = gload(kbeg + 64);
-        if (nst > 2 && a.late >= 1) s2 = gload(kbeg + 128);
-        __syncthreads();
-        NLD_TS(TL_ATTENTION, 2);   // first stage in LDS
-        for (int st = 0; st < nst; st += 2) {
-            compute(kbeg + 64 * st, 0, false);
-            if (st + 1 < nst) lstore(s1, 1);
-            if (st + 3 < nst) s1 = gload(kbeg + 64 * (st + 3));
+    // Stage st is multiplied from slot st % NS.  NS = 2: the next one (then the block's hi halves) is under way
+    // meanwhile.  NS = 4 (one sequence): stages 1 .. 3 are requested once the first is in LDS, since
+    // requested with it they arrive interleaved and the first comes late, and three stay under way.
+    // The queries are named here so that the compiler's own wait for their loads stands here too: it does not
+    // know of the wait before, and in the loop that wait would also be one for every stage under way.
+    stage_wait<0>();
+#pragma unroll
+    for (int c = 0; c < DC; ++c) {
+        asm volatile("" : "+v"(qb[c].x), "+v"(qb[c].y), "+v"(qb[c].z), "+v"(qb[c].w));
+        asm volatile("" : "+v"(ql[c].x), "+v"(ql[c].y), "+v"(ql[c].z), "+v"(ql[c].w));
+    }
+    __syncthreads();
+    NLD_TS(TL_ATTENTION, 2);   // first stage in LDS
+    if constexpr (NS == 4) {
+#pragma unroll
+        for (int i = 1; i < 4; ++i)
+            if (i < nst) dma_keys(split_beg + 64 * i, i);
+        auto next = [&](int st) __attribute__((always_inline)) {   // stage st done: st + 1 has to be in LDS
+            const int ahead = min(nst - 1 - st, 3) - 1;   // stages under way after it
+            if (ahead >= 2) stage_wait<2 * PB>();
+            else if (ahead == 1) stage_wait<PB>();
+            else stage_wait<0>();
             __syncthreads();
-            if (st + 1 >= nst) break;
-            compute(kbeg + 64 * (st + 1), 1, false);
-            if (st + 2 < nst) lstore(s2, 0);
-            if (st + 4 < nst) s2 = gload(kbeg + 64 * (st + 4));
+            if (st + 4 < nst) dma_keys(split_beg + 64 * (st + 4), st % 4);
+        };
+        for (int st = 0; st < nfull; ++st) {
+            if (computes) stage(split_beg + 64 * st, kend, st % 4, 0, No{}, No{});
+            next(st);
+        }
+        if (nst > nfull) {
+            if (computes) stage(split_beg + 64 * nfull, kend, nfull % 4, 0, No{}, Yes{});
+            next(nfull);
+        }
+    } else {
+        auto ahead = [&](int st) __attribute__((always_inline)) {   // what follows stage st, into the other slot
+            if (st + 1 < nst) dma_keys(split_beg + 64 * (st + 1), (st + 1) & 1);
+            else if (blockpart) dma(bkbase, bvbase, (st + 1) & 1);
+        };
+        for (int st = 0; st < nfull; ++st) {
+            ahead(st);
+            if (computes) stage(split_beg + 64 * st, kend, st & 1, 0, No{}, No{});
+            stage_wait<0>();
             __syncthreads();
         }
+        if (nst > nfull) {
+            ahead(nfull);
+            if (computes) stage(split_beg + 64 * nfull, kend, nfull & 1, 0, No{}, Yes{});
+            stage_wait<0>();
+            __syncthreads();
+        }
+    }
+    if (blockpart) {
+        const int hi = nst % NS;   // NS = 4: the block's own workgroup, nst = 0
+        if (!blockonly && nst == 0) dma(bkbase, bvbase, hi);   // no prefix: slot 0 holds uncommitted keys
+        dma(bkbase + 64 * D, bvbase + 64 * D, hi ^ 1);
+        stage_wait<0>();
+        __syncthreads();
+        if (computes) stage(P, P + k, hi, hi ^ 1, Yes{}, Yes{});
+        __syncthreads();
     }
 
     NLD_TS(TL_ATTENTION, 3);   // stages done
@@ -1938,7 +1975,7 @@ __global__ void __launch_bounds__(512) attention_kernel(AttnArgs a) {
     l_tot += __shfl_xor(l_tot, 32);
     if constexpr (KH == 2) {
         // merge the two key halves of each row tile through LDS (the stage buffers are free now)
-        float* mrg = (float*)lds;                    // [RZ][16 rows][D + 2] floats, within the 2 stage slots
+        float* mrg = (float*)lds;                    // [RZ][16 rows][D + 2] floats, within the stage slots
         float* slot = mrg + ((size_t)(wave % RZ) * 16 + r) * (D + 2);
         if (kh == 1 && computes) {
 #pragma unroll
@@ -1985,10 +2022,9 @@ __global__ void __launch_bounds__(D) attention_combine_kernel(AttnArgs a) {
     const int unit = blockIdx.x, rw = blockIdx.y, d = threadIdx.x;
     const int nkv = a.n_kv_heads, G = a.n_q_heads / nkv;
     const int b = unit / nkv, kvh = unit % nkv, k = a.k_blk;
-    // parts: prefix splits 0 .. nvalid-1 (the ones holding committed keys), then the block part
-    const int nvalid = a.items ? (attn_length(a, b) + a.chunk - 1) / a.chunk : a.n_splits;
-    const int ns = nvalid + 1;
-    auto pidx = [&](int j) { return j < nvalid ? j : a.n_splits; };
+    // parts: a batch's work items, or one sequence's prefix splits and the block part
+    const int ns = a.items ? attn_items(a, attn_length(a, b)) : a.n_splits + 1;
+    auto pidx = [](int j) { return j; };
     const size_t ubase = (size_t)unit * a.n_parts * a.rows_pad + rw;
     // With at most FAST parts every load of the workgroup is issued at once: thread d's part
     // statistics and its column of every part's output.  More parts take the looped path.
@@ -2073,15 +2109,21 @@ __global__ void __launch_bounds__(D) attention_combine_kernel(AttnArgs a) {
     NLD_TS(TL_COMBINE, 1);
 }
 
-hipError_t launch_attention(int head_dim, int kh, int zslices, int units, const AttnArgs& a, hipStream_t s) {
-    // prefix splits + the block part per unit; length-aware items: all of them on x
-    const dim3 grid = a.items ? dim3((a.n_splits + 1) * units, 1, zslices) : dim3(a.n_splits + 1, units, zslices);
-    if (head_dim == 128 && kh == 2) launch(attention_kernel<128, 2>, dim3(grid), dim3(512), s, a);
-    else if (head_dim == 128 && kh == 1) launch(attention_kernel<128, 1>, dim3(grid), dim3(512), s, a);
-    else if (head_dim == 64 && kh == 2) launch(attention_kernel<64, 2>, dim3(grid), dim3(512), s, a);
-    else if (head_dim == 64 && kh == 1) launch(attention_kernel<64, 1>, dim3(grid), dim3(512), s, a);
-    else return hipErrorInvalidValue;
+template <int D>
+static hipError_t launch_attention_d(int kh, int waves, dim3 grid, const AttnArgs& a, hipStream_t s) {
+    const dim3 blk(64 * waves);
+    if (kh == 2 && !a.items) launch(attention_kernel<D, 2, 4>, grid, blk, s, a);
+    else if (kh == 2) launch(attention_kernel<D, 2, 2>, grid, blk, s, a);
+    else launch(attention_kernel<D, 1, 2>, grid, blk, s, a);
     return hipGetLastError();
+}
+
+hipError_t launch_attention(int head_dim, int kh, int waves, int zslices, int units, const AttnArgs& a, hipStream_t s) {
+    // four stage slots count on 8 wavefronts' loads
+    if (waves < kh || waves % kh || waves > (kh == 2 ? 8 : 12) || (kh == 2 && !a.items && waves != 8)) return hipErrorInvalidValue;
+    // prefix splits + the block part per unit; length-aware items: all of them on x
+    const dim3 grid = a.items ? dim3(a.n_splits * units, 1, zslices) : dim3(a.n_splits + 1, units, zslices);
+    return head_dim == 128 ? launch_attention_d<128>(kh, waves, grid, a, s) : launch_attention_d<64>(kh, waves, grid, a, s);
 }
 
 hipError_t launch_attention_combine(int head_dim, int units, int rows, const AttnArgs& a, hipStream_t s) {

@@ -186,16 +186,15 @@ struct AttnArgs {
     int k_blk, n_q_heads, n_kv_heads, max_len, n_splits, chunk, mode, bidir_from, rows_pad;
     int row_tiles;       // query-row tiles of 16 per unit (GQA group size x k / 16, rounded up)
     int quad_k;          // mode 2 (quadratic self-speculation): chain length of the block's layout
-    int n_parts;         // partial results per (unit, row): n_splits prefix splits + the block part
+    int n_parts;         // partial results per (unit, row)
     float scale_log2;    // log2(e) / sqrt(D)
     // Length-aware work (batches): grid.x counts (unit, split) items numbered unit by unit from the
-    // committed lengths, unit u of sequence b taking ceil(P_b / chunk) prefix splits and the block
-    // part; items past the total leave at once, and the merge reads only the valid parts.
+    // committed lengths, unit u of sequence b taking ceil(P_b / chunk) prefix splits (at least one), the
+    // last of which takes the block part along; items past the total leave at once, and the merge reads
+    // only the valid parts.
     int items;
     int n_seq;           // sequences (units / n_kv_heads)
     uint32_t plain;      // PlainSite bits: SITE_P (probabilities), SITE_O (the merged output)
-    int late;            // prefix stages 1, 2 requested: 0 with the first, 1 stage 2 once the first is in
-                         // LDS, 2 both once the first is in LDS
 };
 
 constexpr int EMBED_SS = 4;   // sums of squares per row the embedding kernel writes (one per wavefront)
@@ -313,8 +312,9 @@ int gemm_panel_shapes();
 PanelShape gemm_panel_shape(int i);
 inline bool gemm_panel_narrow(PanelShape p) { return p.wc == 4 && p.ct == 1; }   // the shapes EPI_SPLIT has
 hipError_t launch_gemm_panel(int epi, int shape, const GemmArgs& a, int ksplit, float* part, unsigned* ctr, hipStream_t s);
-// kh: key halves per stage (2 when the unit has at most 4 row tiles, else 1); 8 wavefronts per workgroup.
-hipError_t launch_attention(int head_dim, int kh, int zslices, int units, const AttnArgs& a, hipStream_t s);
+// kh: wavefronts per row tile (2 when the unit has at most 4 row tiles, else 1); waves / kh row tiles per
+// workgroup (at most 8 wavefronts with kh = 2, exactly 8 for one sequence; at most 12 with kh = 1).
+hipError_t launch_attention(int head_dim, int kh, int waves, int zslices, int units, const AttnArgs& a, hipStream_t s);
 hipError_t launch_attention_combine(int head_dim, int units, int rows, const AttnArgs& a, hipStream_t s);
 hipError_t launch_finish(const FinishArgs& a, hipStream_t s);
 // Quadratic self-speculation: the ensemble verifier's per-chunk keys (0 < lambda < 1; grid
