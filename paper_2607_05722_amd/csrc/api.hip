@@ -240,13 +240,10 @@ nld_status check_config(const nld_config* c) {
 }
 
 // ---------------------------------------------------------------- GEMM launch plans
-// Normed multi-tile GEMM: k-steps per wavefront and wavefront count with ks * waves == ksteps.
-bool plan_norm(int epi, int M, int ksteps, int* ks, int* waves) {
+// Normed multi-tile GEMM (the LM head): k-steps per wavefront and wavefront count with ks * waves == ksteps.
+bool plan_norm(int M, int ksteps, int* ks, int* waves) {
     if (M > 16 || env_int("NLD_NO_NORM_GEMM", 0)) return false;
-    // k-steps per wavefront: 16 (8 wavefronts) where the epilogue needs registers, 8 (16 wavefronts) for SwiGLU
-    const int pref = env_int(epi == EPI_QKV ? "NLD_NORM_KS_QKV" : epi == EPI_SWIGLU ? "NLD_NORM_KS_GU" : "NLD_NORM_KS_LM",
-                             epi == EPI_SWIGLU ? 8 : 16);
-    const int cand[] = {pref, 8, 16, 20, 4};
+    const int cand[] = {env_int("NLD_NORM_KS_LM", 16), 8, 16, 20, 4};   // 16: 8 wavefronts, the epilogue needs registers
     for (int c : cand) {
         if (gemm_norm_supported(c) && ksteps % c == 0 && ksteps / c >= 1 && ksteps / c <= gemm_norm_max_waves(c)) {
             *ks = c;
@@ -270,40 +267,6 @@ int device_cus() {
                           ? n : 256;
     }
     return cached[dev];
-}
-
-// Workgroups of the normed GEMM: one per CU, but at least two tiles per workgroup on
-// average (each workgroup loads the whole operand once); tiles beyond the first one per
-// workgroup are handed out dynamically.
-// NLD_NORM_TPW_QKV / _GU / _LM: tiles per workgroup to aim for instead of 2.
-int norm_grid(int epi, int n_tiles) {
-    const int cus = device_cus();
-    const int tpw = std::max(1, env_int(epi == EPI_QKV ? "NLD_NORM_TPW_QKV" : epi == EPI_SWIGLU ? "NLD_NORM_TPW_GU"
-                                                                                                : "NLD_NORM_TPW_LM", 2));
-    const int want = (n_tiles + tpw - 1) / tpw;
-    return want < cus ? want : cus;
-}
-
-struct StreamPlan {
-    int ct, nw, gx;
-};
-
-StreamPlan plan_stream(int epi, int n_tiles) {
-    StreamPlan p;
-    if (epi == EPI_LMHEAD) {
-        p.ct = 4;
-        p.nw = 4;
-    } else if (epi == EPI_SWIGLU) {
-        p.ct = 2;
-        p.nw = 8;
-    } else {
-        // O and down on this kernel: 16 wavefronts with every load of their 8 k-steps in flight (O at the 8B
-        // shapes: 10.8-11.0 against 11.2 us with 8 wavefronts)
-        p.ct = 1;
-        p.nw = epi == EPI_RESID ? env_int("NLD_STREAM_NW_RESID", 16) : 8;
-    }
-    p.gx = cdiv(n_tiles, p.ct);
-    return p;
 }
 
 enum Source { SRC_TOKENS = 0, SRC_DRAFT = 1, SRC_VERIFY = 2, SRC_QUAD = 3 };
@@ -357,19 +320,15 @@ nld_status validate_call(const nld_model* m, const nld_kv_cache* kv, int batch, 
 
 enum ProjKind { PROJ_O = 0, PROJ_DOWN = 1, PROJ_QKV = 2, PROJ_GU = 3, PROJ_LM = 4, PROJ_LORA = 5, N_PROJ = 6 };
 
-// Split-K plan of a projection with at most 16 rows: ct column tiles per workgroup and
-// ksplit K slices, so that column groups x slices is at most one workgroup per CU, with
-// every wavefront (8 per workgroup) getting at least two k-steps.  Defaults per
-// projection (measured on MI355X at the 8B shapes): down 2 tiles, O off (the streamed GEMM,
-// 11.3 against 12.9 us), QKV off (the normed multi-tile kernel is faster).  Environment overrides:
-// NLD_SPLITK_<O|DOWN|QKV> = "ct,ksplit" ("ct,0": ksplit from the rule; "0": off),
-// NLD_SPLITK / NLD_SPLITK_CT for every projection at once, NLD_NO_SPLITK = 1: off.
-bool plan_splitk(int kind, int epi, const GemmArgs& g, const Layout& L, int* ct, int* ksplit) {
+// Split-K plan of a residual projection with at most 16 rows: ct column tiles per workgroup and ksplit K
+// slices, so that column groups x slices is at most one workgroup per CU, with every wavefront (8 per
+// workgroup) getting at least two k-steps.  Default: the down projection of up to 8 rows, 2 tiles (O runs
+// streamed, 11.3 against 12.9 us).  Environment overrides: NLD_SPLITK_<O|DOWN> = "ct,ksplit" ("ct,0": ksplit
+// from the rule; "0": off), NLD_SPLITK / NLD_SPLITK_CT for both at once, NLD_NO_SPLITK = 1: off.
+bool plan_splitk(int kind, const GemmArgs& g, const Layout& L, int* ct, int* ksplit) {
     if (g.W2 || env_int("NLD_NO_SPLITK", 0)) return false;
-    static const char* names[] = {"NLD_SPLITK_O", "NLD_SPLITK_DOWN", "NLD_SPLITK_QKV"};
-    static const int dflt_ct[] = {0, 2, 0};
-    int c = dflt_ct[kind], ks = 0;
-    const char* v = getenv(names[kind]);
+    int c = kind == PROJ_DOWN && g.M <= 8 ? 2 : 0, ks = 0;
+    const char* v = getenv(kind == PROJ_O ? "NLD_SPLITK_O" : "NLD_SPLITK_DOWN");
     if (v && *v) {
         c = atoi(v);
         const char* comma = strchr(v, ',');
@@ -377,7 +336,7 @@ bool plan_splitk(int kind, int epi, const GemmArgs& g, const Layout& L, int* ct,
     }
     c = env_int("NLD_SPLITK_CT", c);
     ks = env_int("NLD_SPLITK", ks);
-    if (c <= 0 || !gemm_splitk_supported(epi, g.M, c)) return false;
+    if (c < 2 || c > 4) return false;
     const int groups = cdiv(g.n_tiles, c);
     if (ks <= 0) ks = std::min(std::max(1, device_cus() / groups), std::max(1, g.ksteps / 16));
     if (groups > L.n_ctr) ks = 1;   // no counters (and no partials) for that many groups
@@ -386,12 +345,12 @@ bool plan_splitk(int kind, int epi, const GemmArgs& g, const Layout& L, int* ct,
     return true;
 }
 
-// Panel GEMM (M > 16): workgroup shape and K slices of one projection, the cheapest by an estimate in
+// Panel GEMM: workgroup shape and K slices of one projection, the cheapest by an estimate in
 // microseconds from rates measured on this part: weights 6.3 TB/s from HBM with every CU reading (32 GB/s
 // into one CU), operand and re-read weights 80 GB/s per CU from L2, which add up; MFMA at 80% of 1024 flops
-// per cycle and SIMD, LDS 128 bytes per cycle; slices 1.5 us to meet and 0.6 us each, their partials written at
-// 5 TB/s in all and read back by one CU at 60 GB/s.  Against a sweep of every shape and slice count at the 8B shapes (32,
-// 64, 100, 512 rows) and the 14B ones (256) the picked plan is within 4% of the fastest one, for the LM
+// per cycle and SIMD, LDS 128 bytes per cycle; slices 1.5 us to meet and 0.6 us each, their partials written
+// at 5 TB/s in all and read back by one CU at 60 GB/s.  Against a sweep of every shape and slice count at the
+// 8B shapes (8, 16, 32, 64, 100, 512 rows) and the 14B ones (256) the picked plan is within 4% of the fastest one, for the LM
 // head of a short vocabulary within 10%.
 // NLD_PANEL_<O|DOWN|QKV|GU|LM|LORA> = "shape,slices" overrides a plan; NLD_TILE_KSPLIT_<O|DOWN|QKV|GU> (more
 // than 64 rows) and NLD_SPLITK (17..64) the slices alone.
@@ -403,7 +362,7 @@ PanelPlan plan_panel(int kind, int M, int n_tiles, int K, const Layout& L) {
     static const char* names[] = {"NLD_PANEL_O", "NLD_PANEL_DOWN", "NLD_PANEL_QKV", "NLD_PANEL_GU", "NLD_PANEL_LM", "NLD_PANEL_LORA"};
     static const char* slices[] = {"NLD_TILE_KSPLIT_O", "NLD_TILE_KSPLIT_DOWN", "NLD_TILE_KSPLIT_QKV", "NLD_TILE_KSPLIT_GU", "", ""};
     const double cus = device_cus(), cyc = 2.2e3;   // cycles per microsecond
-    const int rt = M <= 32 ? 2 : (M <= 64 ? 4 : 8), full = K / 32, R = cdiv(M, 16 * rt);
+    const int rt = M <= 16 ? 1 : (M <= 32 ? 2 : (M <= 64 ? 4 : 8)), full = K / 32, R = cdiv(M, 16 * rt);
     int want = kind < PROJ_LM ? env_int(M > 64 ? slices[kind] : "NLD_SPLITK", 0) : 0, only = -1;
     if (const char* force = getenv(names[kind])) {
         only = atoi(force);
@@ -448,40 +407,31 @@ hipError_t panel_gemm(int epi, const PanelPlan& p, GemmArgs& g, void* ws, const 
     return launch_gemm_panel(epi, p.shape, g, p.ksplit, at<float>(ws, L.part), at<unsigned>(ws, L.tile_ctr) + L.ctr0, s);
 }
 
-// Residual projections (O, down): the panel GEMM above 16 rows, else the split-K GEMM (down) or the streamed
-// one.  n_ss: sums of squares per row the projection writes for the next RMSNorm.
+// Residual projections (O, down).  Up to 16 rows O runs streamed and, up to 8, down on the split-K kernel (at
+// those kernels: both sides measured); the rest on the panel GEMM.  n_ss: sums of squares per row the
+// projection writes for the next RMSNorm.
 hipError_t resid_gemm(int kind, const PanelPlan* plans, GemmArgs& g, void* ws, const Layout& L, hipStream_t s, int* n_ss) {
-    if (g.M > 16) return panel_gemm(EPI_RESID, plans[kind], g, ws, L, s, n_ss);
     *n_ss = g.n_tiles;
     int ct = 0, ksplit = 0;
-    if (plan_splitk(kind, EPI_RESID, g, L, &ct, &ksplit))
-        return launch_gemm_splitk(EPI_RESID, ct, ksplit, g, at<float>(ws, L.part), at<unsigned>(ws, L.tile_ctr) + L.ctr0, s);
-    StreamPlan p = plan_stream(EPI_RESID, g.n_tiles);
-    if (g.W2) p.nw = 8;   // the second source's k-steps need the 8-wavefront kernel's registers
-    return launch_gemm_stream(EPI_RESID, p.ct, p.nw, p.gx, g, s);
+    if (g.M <= 16 && plan_splitk(kind, g, L, &ct, &ksplit))
+        return launch_gemm_splitk(ct, ksplit, g, at<float>(ws, L.part), at<unsigned>(ws, L.tile_ctr) + L.ctr0, s);
+    if (g.M <= 16 && kind == PROJ_O) return launch_gemm_stream(env_int("NLD_STREAM_NW_RESID", 16), g, s);
+    return panel_gemm(EPI_RESID, plans[kind], g, ws, L, s, n_ss);
 }
 
-// One projection whose operand is RMSNorm(x) (QKV, gate/up, LM head): the panel GEMM above 16 rows, else the
-// normed multi-tile kernel where it divides the reduction, else the streamed kernel (all read the split
-// operand and the row statistics the producer of x wrote).
+// One projection whose operand is RMSNorm(x) (QKV, gate/up, LM head): the panel GEMM, or, for the LM head of
+// up to 16 rows with at least four column tiles per CU (both sides measured at that kernel; 64 tiles: 13.1
+// against 5.7 us), the normed multi-tile kernel where it divides the reduction.  Both read the split operand and the row statistics the producer of x wrote.
 hipError_t normed_gemm(int kind, int epi, const PanelPlan* plans, GemmArgs g, void* ws, const Layout& L, hipStream_t s,
                        int* parts_out) {
     g.A = at<uint16_t>(ws, L.xg);
     g.part_ss = at<float>(ws, L.part_ss);
-    if (g.M > 16) return panel_gemm(epi, plans[kind], g, ws, L, s, parts_out);
-    int ks = 0, waves = 0, ct = 0, ksplit = 0;
-    if (epi == EPI_QKV && plan_splitk(PROJ_QKV, epi, g, L, &ct, &ksplit))
-        return launch_gemm_splitk(epi, ct, ksplit, g, at<float>(ws, L.part), at<unsigned>(ws, L.tile_ctr) + L.ctr0, s);
-    if (plan_norm(epi, g.M, g.ksteps, &ks, &waves)) {
-        const int grid = norm_grid(epi, g.n_tiles);
-        if (parts_out) *parts_out = grid;
-        g.n_parts = grid;
-        return launch_gemm_norm(epi, ks, waves, grid, g, s);
+    int ks = 0, waves = 0;
+    if (kind == PROJ_LM && g.n_tiles >= 4 * device_cus() && plan_norm(g.M, g.ksteps, &ks, &waves)) {
+        g.n_parts = *parts_out = device_cus();   // tiles beyond the first one per workgroup are handed out dynamically
+        return launch_gemm_norm(ks, waves, g.n_parts, g, s);
     }
-    const StreamPlan p = plan_stream(epi, g.n_tiles);
-    if (parts_out) *parts_out = p.gx;
-    g.n_parts = p.gx;
-    return launch_gemm_stream(epi, p.ct, p.nw, p.gx, g, s);
+    return panel_gemm(epi, plans[kind], g, ws, L, s, parts_out);
 }
 
 nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int k, const PassIO& io, void* ws,
@@ -528,14 +478,12 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
     const int ks_h = cdiv(c.hidden, 32), ks_q = cdiv(nq * D, 32), ks_f = cdiv(c.ffn, 32);
     const bool lora = io.mode == NLD_MODE_DRAFT && c.lora_rank > 0;
     PanelPlan plans[N_PROJ];   // the same for every layer
-    if (M > 16) {
-        plans[PROJ_O] = plan_panel(PROJ_O, M, c.hidden / 16, nq * D, L);
-        plans[PROJ_DOWN] = plan_panel(PROJ_DOWN, M, c.hidden / 16, c.ffn, L);
-        plans[PROJ_QKV] = plan_panel(PROJ_QKV, M, (nq + 2 * nkv) * D / 16, c.hidden, L);
-        plans[PROJ_GU] = plan_panel(PROJ_GU, M, cdiv(c.ffn, 8), c.hidden, L);
-        plans[PROJ_LM] = plan_panel(PROJ_LM, M, L.lm_tiles, c.hidden, L);
-        if (lora) plans[PROJ_LORA] = plan_panel(PROJ_LORA, M, c.lora_rank / 16, nq * D, L);
-    }
+    plans[PROJ_O] = plan_panel(PROJ_O, M, c.hidden / 16, nq * D, L);
+    plans[PROJ_DOWN] = plan_panel(PROJ_DOWN, M, c.hidden / 16, c.ffn, L);
+    plans[PROJ_QKV] = plan_panel(PROJ_QKV, M, (nq + 2 * nkv) * D / 16, c.hidden, L);
+    plans[PROJ_GU] = plan_panel(PROJ_GU, M, cdiv(c.ffn, 8), c.hidden, L);
+    plans[PROJ_LM] = plan_panel(PROJ_LM, M, L.lm_tiles, c.hidden, L);
+    if (lora) plans[PROJ_LORA] = plan_panel(PROJ_LORA, M, c.lora_rank / 16, nq * D, L);
     for (int l = 0; l < c.n_layers; ++l) {
         const nld_layer_weights& W = mdl->layers[l];
         uint16_t* kc = (uint16_t*)kv->k + (size_t)l * kv_layer;
@@ -626,12 +574,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
             gt.out_scale = c.lora_scale;
             {
                 TraceScope ts(NLD_TRACE_O_PROJ, s);
-                if (M > 16) {
-                    HIP_TRY(panel_gemm(EPI_SPLIT, plans[PROJ_LORA], gt, ws, L, s, nullptr));
-                } else {
-                    const StreamPlan p = plan_stream(EPI_SPLIT, gt.n_tiles);
-                    HIP_TRY(launch_gemm_stream(EPI_SPLIT, p.ct, p.nw, p.gx, gt, s));
-                }
+                HIP_TRY(panel_gemm(EPI_SPLIT, plans[PROJ_LORA], gt, ws, L, s, nullptr));
             }
             go.W2 = (const uint4*)W.lora_b;
             go.A2 = at<uint16_t>(ws, L.lora_t);

@@ -102,62 +102,6 @@ __device__ __forceinline__ unsigned long long umax64(unsigned long long a, unsig
 // handles rows 4g + i of the tile (g = lane / 16) and lane 16g + r holds column r.
 // y is the finished (RMSNorm-scaled) value of row m, column r.
 // =====================================================================================
-// pos: absolute position of row m (block row j at P_b + j).  RoPE uses the per-row
-// (cos, sin) table built by the embedding kernel.
-__device__ __forceinline__ void epi_qkv(const GemmArgs& a, float y, int m, int t, int lane, int pos) {
-    const int r = lane & 15;
-    const int D = a.head_dim;
-    const int tiles_per_head = D / 16;
-    const int hh = t / tiles_per_head, u = t % tiles_per_head;
-    const int fi = 8 * u + (r & 7);             // rotary frequency index, < D/2
-    const int dim = (r < 8) ? fi : D / 2 + fi;  // lanes r and r^8 hold the pair (fi, fi + D/2)
-    const int nq = a.n_q_heads, nkv = a.n_kv_heads;
-    const int kind = hh < nq ? 0 : (hh < nq + nkv ? 1 : 2);
-    const bool ok = m < a.M;
-    const float partner = __shfl_xor(y, 8);
-    float out = y;
-    if (kind < 2) {
-        const float2 cs = a.rope[(size_t)(ok ? m : 0) * (D / 2) + fi];
-        out = (r < 8) ? (y * cs.x - partner * cs.y) : (y * cs.x + partner * cs.y);
-    }
-    if (!ok) return;
-    const int b = m / a.k_blk, jb = m - b * a.k_blk;
-    if (kind == 0) {
-        const int G = nq / nkv;
-        const int row = (hh % G) * a.k_blk + jb;
-        store_split(a.q_out, q_index(b * nkv + hh / G, row, dim, a.q_row_tiles, D), out, a.plain & SITE_Q);
-        return;
-    }
-    // K/V: split into the block buffer (what this pass's attention over the block's
-    // own keys reads) and, in a verify pass, bf16 into the cache (what a commit keeps)
-    const int kvh = hh - nq - (kind == 2 ? nkv : 0);
-    const size_t unit = (size_t)b * nkv + kvh;
-    const uint16_t ob = (uint16_t)f32_to_bf16(out);
-    const uint16_t lo = (a.plain & SITE_KV) ? (uint16_t)0 : (uint16_t)f32_to_bf16(out - bf16_to_f32(ob));
-    if (kind == 1) {
-        a.blk_k[(unit * 2 * 64 + jb) * D + dim] = ob;
-        a.blk_k[((unit * 2 + 1) * 64 + jb) * D + dim] = lo;
-    } else {
-        a.blk_v[(unit * 2 * D + dim) * 64 + jb] = ob;
-        a.blk_v[((unit * 2 + 1) * D + dim) * 64 + jb] = lo;
-    }
-    if (!a.write_cache) return;
-    if (a.quad_k > 0 && jb >= a.quad_k) return;   // quadratic layout: only the chain rows are AR rows
-    if (pos >= a.max_len) atomicOr(a.status, DEV_CAPACITY);
-    else if (kind == 1) a.kc[(unit * a.max_len + pos) * D + dim] = ob;
-    else a.vc[((unit * (a.max_len / 64) + pos / 64) * D + dim) * 64 + (pos & 63)] = ob;
-}
-
-__device__ __forceinline__ void epi_swiglu(const GemmArgs& a, float y, int m, int t, int lane) {
-    const int r = lane & 15;
-    const int col = 8 * t + (r & 7);
-    const float partner = __shfl_xor(y, 8);   // lanes r < 8 hold gate columns, r^8 the matching up columns
-    if (m < a.M && r < 8 && col < a.ffn) {
-        const float act = y / (1.0f + expf(-y)) * partner;
-        store_split(a.act, split_index(m, col, (a.ffn + 31) / 32), act, a.plain & SITE_ACT);
-    }
-}
-
 // Softmax statistics as (max, sum of exp(z - max)); (-inf, 0) is the empty set.
 __device__ __forceinline__ float2 lse_merge(float2 a, float2 b) {
     if (b.x == -INFINITY) return a;
@@ -234,35 +178,29 @@ __device__ __forceinline__ void rms_scales(const GemmArgs& a, int m0, int rows, 
 }
 
 // =====================================================================================
-// Normed multi-tile GEMM (M <= 16 rows).  A workgroup of NW wavefronts owns a
-// contiguous range of output tiles; wavefront w owns the reduction slice
-// [32*KS*w, 32*KS*(w+1)).  At the start each wavefront loads its slice of the
-// split operand bf16(x * gain) (hi and lo) and keeps it in registers for all
-// tiles; the per-row RMSNorm scale comes from the producer's partial sums of
-// squares.  Weights stream through one register buffer: the load of the next
-// tile's step s is issued as soon as step s of the current tile has been
-// multiplied, so one tile's worth of loads is in flight throughout.  Per tile
-// the NW partial products meet in LDS and one wavefront (rotating) runs the
-// epilogue.
+// Normed multi-tile GEMM: the LM head of up to 16 rows.  A workgroup of NW wavefronts takes output tiles
+// from a counter; wavefront w owns the reduction slice [32*KS*w, 32*KS*(w+1)).  At the start each wavefront
+// loads its slice of the split operand bf16(x * gain) (hi and lo) and keeps it in registers for all tiles;
+// the per-row RMSNorm scale comes from the producer's partial sums of squares.  Weights stream through one
+// register buffer: the load of the next tile's step s is issued as soon as step s of the current tile has
+// been multiplied, so one tile's worth of loads is in flight throughout.  Per tile the NW partial products
+// meet in LDS and one group of wavefronts (rotating) runs the epilogue.  Against the panel GEMM it has no
+// prologue per tile and no uneven last round: 198 against 203 us for 9496 tiles (vocab 151936, hidden 4096),
+// 27.5 against 28.6 us for 1055; for a projection with few tiles per CU the panel GEMM is faster.
 // =====================================================================================
-template <int KS, int EPI>
+template <int KS>
 __global__ void __launch_bounds__(KS >= 16 ? 512 : 1024) gemm_norm_kernel(GemmArgs a) {
     __shared__ f32x4_t red[2][16][64];
     __shared__ float inv_s[16];
     __shared__ unsigned long long key_s[16][16];
     __shared__ float2 lse_s[16][16];
-    __shared__ int pos_s[16];
-
     __shared__ int next_s[2];
 
-    constexpr int TLC = EPI == EPI_QKV ? TL_QKV : (EPI == EPI_SWIGLU ? TL_GATE_UP : TL_LM);
-    NLD_TS(TLC, 0);
+    NLD_TS(TL_LM, 0);
     const int NW = blockDim.x >> 6;
-    if constexpr (EPI == EPI_LMHEAD) {
-        if (threadIdx.x < 256) {
-            key_s[threadIdx.x >> 4][threadIdx.x & 15] = 0ull;
-            lse_s[threadIdx.x >> 4][threadIdx.x & 15] = float2{-INFINITY, 0.f};
-        }
+    if (threadIdx.x < 256) {
+        key_s[threadIdx.x >> 4][threadIdx.x & 15] = 0ull;
+        lse_s[threadIdx.x >> 4][threadIdx.x & 15] = float2{-INFINITY, 0.f};
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, g = lane >> 4;
@@ -279,8 +217,7 @@ __global__ void __launch_bounds__(KS >= 16 ? 512 : 1024) gemm_norm_kernel(GemmAr
 
     // operand slice: row r, columns 32*(s0+s) + 8g .. +8, hi and lo.  Requested before the first
     // weight tile: loads complete in issue order, and the operand (L2 hits after the first workgroups)
-    // then no longer waits behind the tile's HBM reads (8B shapes, k = 16: QKV 16.7 against 17.5 us,
-    // gate/up 37.8 against 39.4 us, LM head 198.5 against 200.5 us).
+    // then no longer waits behind the tile's HBM reads (8B shapes, k = 16: 198.5 against 200.5 us).
     uint4 ah[KS], al[KS];
     const bool row_ok = r < a.M;
     const uint16_t* ar = a.A + (size_t)s0 * 1024 + (size_t)lane * 8;
@@ -296,18 +233,12 @@ __global__ void __launch_bounds__(KS >= 16 ? 512 : 1024) gemm_norm_kernel(GemmAr
         for (int s = 0; s < KS; ++s) wb[s] = load_stream(p + (size_t)s * 64);
     }
     rms_scales(a, 0, 16, inv_s);
-    if constexpr (EPI == EPI_QKV) {
-        if (threadIdx.x < 16) {   // absolute position of block row m: P_b + j
-            const int m = min((int)threadIdx.x, a.M - 1);
-            pos_s[threadIdx.x] = committed_length(a.lengths, m / a.k_blk, a.max_len, a.status) + m % a.k_blk;
-        }
-    }
     if (threadIdx.x == 0) next_s[0] = G < T ? min(G + (int)grab, T) : T;
     __syncthreads();
 
     // A tile is finished by FIN wavefronts (wavefront i of the group takes rows 4g + i,
     // 4g + i + FIN, ...); the groups take the tiles in turn.
-    NLD_TS(TLC, 1);   // operand, first tile and row statistics in
+    NLD_TS(TL_LM, 1);   // operand, first tile and row statistics in
     const int FIN = NW < 4 ? NW : 4, groups = NW / FIN;
     for (int it = 0; cur < T; ++it) {
         const int t = cur;
@@ -333,208 +264,125 @@ __global__ void __launch_bounds__(KS >= 16 ? 512 : 1024) gemm_norm_kernel(GemmAr
                 float v = rp[i];
                 for (int w = 1; w < NW; ++w) v += rp[w * 256 + i];   // fixed order over the K-slices
                 const int m = 4 * g + i;
-                const float y = v * inv_s[m];
-                if constexpr (EPI == EPI_QKV) epi_qkv(a, y, m, t, lane, pos_s[m]);
-                else if constexpr (EPI == EPI_SWIGLU) epi_swiglu(a, y, m, t, lane);
-                else {
-                    float2 tl;
-                    const unsigned long long key = epi_lmhead(a, y, m, t, lane, &tl);
-                    if (r == 0) {
-                        key_s[wave][m] = umax64(key_s[wave][m], key);
-                        if (a.part_lse) lse_s[wave][m] = lse_merge(lse_s[wave][m], tl);
-                    }
+                float2 tl;
+                const unsigned long long key = epi_lmhead(a, v * inv_s[m], m, t, lane, &tl);
+                if (r == 0) {
+                    key_s[wave][m] = umax64(key_s[wave][m], key);
+                    if (a.part_lse) lse_s[wave][m] = lse_merge(lse_s[wave][m], tl);
                 }
             }
         }
     }
 
-    NLD_TS(TLC, 2);
-    if constexpr (EPI == EPI_LMHEAD) {
-        // one argmax key per row for this workgroup
-        __syncthreads();
-        if ((int)threadIdx.x < a.M && threadIdx.x < 16) {
-            unsigned long long best = 0ull;
-            for (int w = 0; w < NW; ++w) best = umax64(best, key_s[w][threadIdx.x]);
-            a.part_keys[(size_t)threadIdx.x * a.n_parts + blockIdx.x] = best;
-            if (a.part_lse) {
-                float2 st = float2{-INFINITY, 0.f};
-                for (int w = 0; w < NW; ++w) st = lse_merge(st, lse_s[w][threadIdx.x]);
-                a.part_lse[(size_t)threadIdx.x * a.n_parts + blockIdx.x] = st;
-            }
+    NLD_TS(TL_LM, 2);
+    // one argmax key per row for this workgroup
+    __syncthreads();
+    if ((int)threadIdx.x < a.M && threadIdx.x < 16) {
+        unsigned long long best = 0ull;
+        for (int w = 0; w < NW; ++w) best = umax64(best, key_s[w][threadIdx.x]);
+        a.part_keys[(size_t)threadIdx.x * a.n_parts + blockIdx.x] = best;
+        if (a.part_lse) {
+            float2 st = float2{-INFINITY, 0.f};
+            for (int w = 0; w < NW; ++w) st = lse_merge(st, lse_s[w][threadIdx.x]);
+            a.part_lse[(size_t)threadIdx.x * a.n_parts + blockIdx.x] = st;
         }
     }
 }
 
 bool gemm_norm_supported(int ks) { return ks == 4 || ks == 8 || ks == 16 || ks == 20; }
 
-template <int KS>
-static hipError_t launch_norm_ks(int epi, int waves, int grid, const GemmArgs& a, hipStream_t s) {
-    const dim3 blk(waves * 64);
-    switch (epi) {
-        case EPI_QKV: launch(gemm_norm_kernel<KS, EPI_QKV>, dim3(grid), dim3(blk), s, a); break;
-        case EPI_SWIGLU: launch(gemm_norm_kernel<KS, EPI_SWIGLU>, dim3(grid), dim3(blk), s, a); break;
-        case EPI_LMHEAD: launch(gemm_norm_kernel<KS, EPI_LMHEAD>, dim3(grid), dim3(blk), s, a); break;
+int gemm_norm_max_waves(int ks) { return ks >= 16 ? 8 : 16; }
+
+hipError_t launch_gemm_norm(int ks, int waves, int grid, const GemmArgs& a, hipStream_t s) {
+    if (waves < 1 || waves > gemm_norm_max_waves(ks)) return hipErrorInvalidValue;
+    switch (ks) {
+        case 4: launch(gemm_norm_kernel<4>, dim3(grid), dim3(waves * 64), s, a); break;
+        case 8: launch(gemm_norm_kernel<8>, dim3(grid), dim3(waves * 64), s, a); break;
+        case 16: launch(gemm_norm_kernel<16>, dim3(grid), dim3(waves * 64), s, a); break;
+        case 20: launch(gemm_norm_kernel<20>, dim3(grid), dim3(waves * 64), s, a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-int gemm_norm_max_waves(int ks) { return ks >= 16 ? 8 : 16; }
-
-hipError_t launch_gemm_norm(int epi, int ks, int waves, int grid, const GemmArgs& a, hipStream_t s) {
-    if (waves < 1 || waves > gemm_norm_max_waves(ks)) return hipErrorInvalidValue;
-    switch (ks) {
-        case 4: return launch_norm_ks<4>(epi, waves, grid, a, s);
-        case 8: return launch_norm_ks<8>(epi, waves, grid, a, s);
-        case 16: return launch_norm_ks<16>(epi, waves, grid, a, s);
-        case 20: return launch_norm_ks<20>(epi, waves, grid, a, s);
-        default: return hipErrorInvalidValue;
-    }
-}
-
 // =====================================================================================
-// Streamed GEMM (up to 16 rows): out[m][n] = sum_k A[m][k] W[n][k] for 16*CT columns per
-// workgroup; the NW wavefronts split the reduction, each streaming its slice of the
-// weights and of the bf16 activations with one batch in flight ahead of the MFMAs.
-// Every operand is split (two MFMAs per weight operand).  Used for the O projection
-// (residual epilogue, with the LoRA adapter as a second source) and for the normed
-// projections whose reduction the normed GEMM does not divide (the per-row RMSNorm scale
-// is then formed in the prologue).
+// Streamed GEMM: the O projection of up to 16 rows.  A workgroup takes one column tile; its NW wavefronts
+// split the reduction, each streaming its slice of the weights and of the split activations with one batch
+// in flight ahead of the MFMAs (two per weight operand).  No slices meet and rows past M are not read: 8.2 us
+// at 8 rows of the 8B shapes against 10.6 us for the panel GEMM, 8.0 against 11.0 at 16.  XK: the reduction
+// continues over a second source (the LoRA up-projection).
 // =====================================================================================
-template <int MT, int CT, bool SPLIT, int NW = 8>
+// Operand and weight registers of one batch: U k-steps of CT column tiles.
+template <int CT, int U>
 struct Batch {
-    static constexpr int OPS = CT + MT * (SPLIT ? 2 : 1);   // operand quads per k-step
-    // 16 wavefronts (1024 threads, at most 128 registers each): half the batch
-    static constexpr int U = ((OPS <= 3) ? 8 : ((OPS <= 5) ? 4 : 2)) / (NW > 8 ? 2 : 1);
     uint4 w[U][CT];
-    uint4 x[U][MT];
-    uint4 xl[SPLIT ? U : 1][SPLIT ? MT : 1];
+    uint4 x[U];
+    uint4 xl[U];
 };
 
-template <int MT, int CT, int NW, int EPI, bool XK>
+template <int NW, bool XK>
 __global__ void __launch_bounds__(NW * 64) gemm_stream_kernel(GemmArgs a) {
-    constexpr bool SPLIT = true;
-    constexpr bool NORMED = EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_LMHEAD;
-    typedef Batch<MT, CT, SPLIT, NW> B;
-    constexpr int U = B::U;
-    constexpr int BSTRIDE = SPLIT ? 1024 : 512;   // elements per (row tile, k-step) block
-    __shared__ f32x4_t red[NW][MT * CT][64];
-    __shared__ unsigned long long key_s[16 * MT];
-    __shared__ float2 lse_s[16 * MT][CT];
-    __shared__ float inv_s[16 * MT];
+    constexpr int U = NW > 8 ? 4 : 8;   // 16 wavefronts (at most 128 registers each): half the batch
+    typedef Batch<1, U> B;
+    __shared__ f32x4_t red[NW][64];
     NLD_TS(TL_O, 0);
 
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, g = lane >> 4;
-    const int t0 = blockIdx.x * CT;
-    const int m0 = blockIdx.y * 16 * MT;
-
+    const int t = blockIdx.x;
     const int per = (a.ksteps + NW - 1) / NW;
-    const int s_begin = min(a.ksteps, wave * per);
-    const int s_end = min(a.ksteps, s_begin + per);
+    const int s_begin = min(a.ksteps, wave * per), s_end = min(a.ksteps, s_begin + per);
+    const uint4* wp = a.W + (size_t)t * a.ksteps * 64 + lane;
+    const uint16_t* ap = a.A + (size_t)lane * 8;
+    const bool aok = r < a.M;
+    const uint4 zero4 = {0u, 0u, 0u, 0u};
 
-    const uint4* wp[CT];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-        const int t = min(t0 + ct, a.n_tiles - 1);
-        wp[ct] = a.W + (size_t)t * a.ksteps * 64 + lane;
-    }
-    const uint16_t* ap[MT];
-    bool aok[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        aok[mt] = m0 + mt * 16 + r < a.M;
-        ap[mt] = a.A + (size_t)(blockIdx.y * MT + mt) * a.ksteps * BSTRIDE + (size_t)lane * 8;
-    }
     // XK: the second source's k-steps (W2 against A2) go one to a wavefront (wavefront w takes step
-    // w, then w + NW, ...).  They are loaded before the main stream and multiplied after it, so the
+    // w, then w + NW).  They are loaded before the main stream and multiplied after it, so the
     // main loop is the same as without them.
     constexpr int XS = XK ? 2 : 1;   // second-source k-steps held per wavefront (at most 2 * NW in all)
-    uint4 xw[XS][CT], xa[XS][MT], xal[XS][MT];
+    uint4 xw[XS], xa[XS], xal[XS];
     if constexpr (XK) {
 #pragma unroll
         for (int i = 0; i < XS; ++i) {
             const int s2 = wave + i * NW;
             const bool in = s2 < a.ksteps2;
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-                const int t = min(t0 + ct, a.n_tiles - 1);
-                xw[i][ct] = in ? a.W2[((size_t)t * a.ksteps2 + s2) * 64 + lane] : uint4{0u, 0u, 0u, 0u};
-            }
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const uint16_t* ap2 = a.A2 + ((size_t)(blockIdx.y * MT + mt) * a.ksteps2 + s2) * BSTRIDE + (size_t)lane * 8;
-                const bool ok = in && aok[mt];
-                xa[i][mt] = ok ? *(const uint4*)ap2 : uint4{0u, 0u, 0u, 0u};
-                xal[i][mt] = ok ? *(const uint4*)(ap2 + SPLIT_LO) : uint4{0u, 0u, 0u, 0u};
-            }
+            const uint16_t* ap2 = a.A2 + (size_t)s2 * 1024 + (size_t)lane * 8;
+            xw[i] = in ? a.W2[((size_t)t * a.ksteps2 + s2) * 64 + lane] : zero4;
+            xa[i] = in && aok ? *(const uint4*)ap2 : zero4;
+            xal[i] = in && aok ? *(const uint4*)(ap2 + SPLIT_LO) : zero4;
         }
     }
 
-    f32x4_t acc[MT][CT], accl[SPLIT ? MT : 1][SPLIT ? CT : 1];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) acc[mt][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    if constexpr (SPLIT) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) accl[mt][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // Epilogue: wavefront i < 4 takes rows 4g + i; its residual value and next gain are fetched up front so
+    // that the epilogue waits on no load.
+    const int m = 4 * g + wave;
+    float xres = 0.f, gn = 0.f;
+    if (wave < 4) {
+        gn = bf16_to_f32(a.gain_next[t * 16 + r]);
+        if (m < a.M) xres = a.x[(size_t)m * a.n_tiles * 16 + t * 16 + r];
     }
 
-    // Epilogue assignment: a tile is finished by FIN = 4 wavefronts, wavefront i of the
-    // group taking rows 4g + i; the NW / 4 groups take the MT x CT tiles in turn.
-    constexpr int FIN = 4, GROUPS = NW / FIN;
-    static_assert(NW % FIN == 0, "wavefront count must be a multiple of 4");
-    const int fi_row = wave % FIN, ti0 = wave / FIN;
-    // residual value and next gain for this wavefront's first epilogue row, fetched up
-    // front so that the epilogue waits on no load
-    float xres0 = 0.f, gn0 = 0.f;
-    if constexpr (EPI == EPI_RESID) {
-        if (ti0 < MT * CT) {
-            const int mt = ti0 / CT, ct = ti0 % CT;
-            const int m = m0 + 16 * mt + 4 * g + fi_row;
-            if (t0 + ct < a.n_tiles) {
-                gn0 = bf16_to_f32(a.gain_next[(t0 + ct) * 16 + r]);
-                if (m < a.M) xres0 = a.x[(size_t)m * a.n_tiles * 16 + (t0 + ct) * 16 + r];
-            }
-        }
-    }
-
-    const uint4 zero4 = {0u, 0u, 0u, 0u};
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f}, accl = {0.f, 0.f, 0.f, 0.f};
     auto load = [&](int s, B& buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int ss = s + u;
-            const bool in = ss < s_end;
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) buf.w[u][ct] = in ? wp[ct][(size_t)ss * 64] : zero4;
-            const int kcol = ss * 32 + 8 * g;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const bool ok = in && aok[mt] && kcol < a.K;
-                buf.x[u][mt] = ok ? *(const uint4*)(ap[mt] + (size_t)ss * BSTRIDE) : zero4;
-                if constexpr (SPLIT) buf.xl[u][mt] = ok ? *(const uint4*)(ap[mt] + (size_t)ss * BSTRIDE + SPLIT_LO) : zero4;
-            }
+            const bool in = ss < s_end, ok = in && aok && ss * 32 + 8 * g < a.K;
+            buf.w[u][0] = in ? wp[(size_t)ss * 64] : zero4;
+            buf.x[u] = ok ? *(const uint4*)(ap + (size_t)ss * 1024) : zero4;
+            buf.xl[u] = ok ? *(const uint4*)(ap + (size_t)ss * 1024 + SPLIT_LO) : zero4;
         }
     };
     auto compute = [&](const B& buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int ct = 0; ct < CT; ++ct) {
-                    acc[mt][ct] = mfma_16x16x32(buf.x[u][mt], buf.w[u][ct], acc[mt][ct]);
-                    if constexpr (SPLIT) accl[mt][ct] = mfma_16x16x32(buf.xl[u][mt], buf.w[u][ct], accl[mt][ct]);
-                }
+        for (int u = 0; u < U; ++u) {
+            acc = mfma_16x16x32(buf.x[u], buf.w[u][0], acc);
+            accl = mfma_16x16x32(buf.xl[u], buf.w[u][0], accl);
+        }
     };
-
     B b0, b1;
     load(s_begin, b0);
-    if constexpr (NORMED) rms_scales(a, m0, 16 * MT, inv_s);   // visible after the barrier below
     for (int s = s_begin; s < s_end; s += 2 * U) {
         load(s + U, b1);
         compute(b0);
@@ -545,78 +393,19 @@ __global__ void __launch_bounds__(NW * 64) gemm_stream_kernel(GemmArgs a) {
     NLD_TS(TL_O, 1);   // main loop done
     if constexpr (XK) {
 #pragma unroll
-        for (int i = 0; i < XS; ++i)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int ct = 0; ct < CT; ++ct) {
-                    acc[mt][ct] = mfma_16x16x32(xa[i][mt], xw[i][ct], acc[mt][ct]);
-                    accl[mt][ct] = mfma_16x16x32(xal[i][mt], xw[i][ct], accl[mt][ct]);
-                }
+        for (int i = 0; i < XS; ++i) {
+            acc = mfma_16x16x32(xa[i], xw[i], acc);
+            accl = mfma_16x16x32(xal[i], xw[i], accl);
+        }
     }
-    if constexpr (SPLIT) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) acc[mt][ct] += accl[mt][ct];
-    }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) red[wave][mt * CT + ct][lane] = acc[mt][ct];
-    if constexpr (EPI == EPI_LMHEAD) {
-        if (threadIdx.x < 16 * MT) key_s[threadIdx.x] = 0ull;
-        if (threadIdx.x < 16 * MT * CT) lse_s[threadIdx.x / CT][threadIdx.x % CT] = float2{-INFINITY, 0.f};
-    }
+    red[wave][lane] = acc + accl;
     __syncthreads();
-    for (int ti = ti0; ti < MT * CT; ti += GROUPS) {
-        const float* rp = (const float*)&red[0][ti][lane];
-        float v = rp[fi_row];
+    if (wave < 4) {
+        const float* rp = (const float*)&red[0][lane];
+        float v = rp[wave];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) v += rp[w * MT * CT * 256 + fi_row];   // fixed order over the K-slices
-        const int mt = ti / CT, ct = ti % CT;
-        const int t = t0 + ct;
-        if (t >= a.n_tiles) continue;
-        const int ml = 16 * mt + 4 * g + fi_row;   // row within the workgroup's rows
-        const int m = m0 + ml;
-        if constexpr (EPI == EPI_RESID) {
-            float xr = xres0, gn = gn0;
-            if (ti != ti0) {
-                xr = m < a.M ? a.x[(size_t)m * a.n_tiles * 16 + t * 16 + r] : 0.f;
-                gn = bf16_to_f32(a.gain_next[t * 16 + r]);
-            }
-            epi_resid(a, v, m, t, lane, xr, gn);
-        } else if constexpr (EPI == EPI_QKV) {
-            const int mc = min(m, a.M - 1);
-            const int pos = committed_length(a.lengths, mc / a.k_blk, a.max_len, a.status) + mc % a.k_blk;
-            epi_qkv(a, v * inv_s[ml], m, t, lane, pos);
-        } else if constexpr (EPI == EPI_SWIGLU) {
-            epi_swiglu(a, v * inv_s[ml], m, t, lane);
-        } else if constexpr (EPI == EPI_SPLIT) {
-            if (m < a.M) store_split(a.xg_out, split_index(m, t * 16 + r, a.n_tiles / 2), a.out_scale * v);
-        } else {
-            float2 tl;
-            const unsigned long long key = epi_lmhead(a, v * inv_s[ml], m, t, lane, &tl);
-            if (r == 0) {
-                atomicMax(&key_s[ml], key);
-                if (a.part_lse) lse_s[ml][ct] = tl;   // each (row, column tile) is finished once
-            }
-        }
-    }
-    if constexpr (EPI == EPI_LMHEAD) {
-        __syncthreads();
-        if (threadIdx.x < 16 * MT) {
-            const int m = m0 + threadIdx.x;
-            if (m < a.M) {
-                a.part_keys[(size_t)m * a.n_parts + blockIdx.x] = key_s[threadIdx.x];
-                if (a.part_lse) {
-                    float2 st = float2{-INFINITY, 0.f};
-#pragma unroll
-                    for (int c = 0; c < CT; ++c) st = lse_merge(st, lse_s[threadIdx.x][c]);
-                    a.part_lse[(size_t)m * a.n_parts + blockIdx.x] = st;
-                }
-            }
-        }
+        for (int w = 1; w < NW; ++w) v += rp[w * 256 + wave];   // fixed order over the K-slices
+        epi_resid(a, v, m, t, lane, xres, gn);
     }
 #ifdef NLD_TIMELINE
     __syncthreads();
@@ -624,37 +413,20 @@ __global__ void __launch_bounds__(NW * 64) gemm_stream_kernel(GemmArgs a) {
     NLD_TS(TL_O, 2);
 }
 
-template <int EPI, int MT, bool XK>
-static hipError_t launch_stream_ct(int ct, int nw, dim3 grid, const GemmArgs& a, hipStream_t s) {
-    if (ct == 1 && nw == 8) launch(gemm_stream_kernel<MT, 1, 8, EPI, XK>, dim3(grid), dim3(512), s, a);
-    else if (ct == 1 && nw == 16 && !XK) {
-        if constexpr (!XK) launch(gemm_stream_kernel<MT, 1, 16, EPI, false>, dim3(grid), dim3(1024), s, a);
-    }
-    else if (ct == 2 && nw == 8) launch(gemm_stream_kernel<MT, 2, 8, EPI, XK>, dim3(grid), dim3(512), s, a);
-    else if (ct == 4 && nw == 4) launch(gemm_stream_kernel<MT, 4, 4, EPI, XK>, dim3(grid), dim3(256), s, a);
-    else if (ct == 1 && nw == 4) launch(gemm_stream_kernel<MT, 1, 4, EPI, XK>, dim3(grid), dim3(256), s, a);
+hipError_t launch_gemm_stream(int nw, const GemmArgs& a, hipStream_t s) {
+    if (a.M > 16 || (a.W2 && a.ksteps2 > 16)) return hipErrorInvalidValue;
+    const dim3 grid(a.n_tiles);
+    if (a.W2) launch(gemm_stream_kernel<8, true>, grid, dim3(512), s, a);   // its k-steps need these registers
+    else if (nw == 16) launch(gemm_stream_kernel<16, false>, grid, dim3(1024), s, a);
+    else if (nw == 8) launch(gemm_stream_kernel<8, false>, grid, dim3(512), s, a);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_stream(int epi, int ct, int nw, int grid_x, const GemmArgs& a, hipStream_t s) {
-    const dim3 grid(grid_x);
-    if (a.M > 16 || (a.W2 && epi != EPI_RESID)) return hipErrorInvalidValue;
-    switch (epi) {
-        case EPI_QKV: return launch_stream_ct<EPI_QKV, 1, false>(ct, nw, grid, a, s);
-        case EPI_RESID:
-            return a.W2 ? launch_stream_ct<EPI_RESID, 1, true>(ct, nw, grid, a, s)
-                        : launch_stream_ct<EPI_RESID, 1, false>(ct, nw, grid, a, s);
-        case EPI_SWIGLU: return launch_stream_ct<EPI_SWIGLU, 1, false>(ct, nw, grid, a, s);
-        case EPI_LMHEAD: return launch_stream_ct<EPI_LMHEAD, 1, false>(ct, nw, grid, a, s);
-        case EPI_SPLIT: return launch_stream_ct<EPI_SPLIT, 1, false>(ct, nw, grid, a, s);
-        default: return hipErrorInvalidValue;
-    }
-}
-
 // =====================================================================================
-// Split-K GEMM (O and down projections with the residual epilogue, and the normed QKV
-// projection; up to 16 rows).  Workgroup (column group cg,
+// Split-K GEMM: the down projection of up to 8 rows.  (Rows past M are not read: 19.5 us at 1 row of the
+// 8B shapes against 20.9 us for the panel GEMM, 20.9 against 21.1 at 8 rows, 24.7 against 21.3 at 16.)
+// Workgroup (column group cg,
 // K slice ks) multiplies its slice of the operand against CT column tiles, so the
 // operand is read once per CT tiles and K slice instead of once per tile (the split
 // operand is twice as large as the weights it multiplies in these projections).  The
@@ -668,27 +440,15 @@ hipError_t launch_gemm_stream(int epi, int ct, int nw, int grid_x, const GemmArg
 // the next launch and runs the residual epilogue.  No workgroup ever waits for
 // another: there is no spin and no cache-wide fence.
 // =====================================================================================
-// Operand and weight registers of one batch of the split-K GEMM: U k-steps.
-template <int MT, int CT, int U>
-struct SkBatch {
-    uint4 w[U][CT];
-    uint4 x[U][MT];
-    uint4 xl[U][MT];
-};
-
-template <int MT, int CT, int NW, int EPI>
+template <int CT, int NW>
 __global__ void __launch_bounds__(NW * 64) gemm_splitk_kernel(GemmArgs a, float* part, unsigned* ctr, int ksplit) {
-    constexpr int U = Batch<MT, CT, true>::U;
-    typedef SkBatch<MT, CT, U> B;
-    constexpr int NTL = MT * CT;   // output tiles of the workgroup; wavefront w finishes tiles w, w + NW, ...
-    constexpr bool NORMED = EPI == EPI_QKV;
-    static_assert(EPI == EPI_RESID || NORMED, "residual or QKV epilogue");
-    __shared__ f32x4_t red[NW][NTL][64];
-    __shared__ float inv_s[16 * MT];
+    constexpr int U = CT <= 3 ? 4 : 2;   // k-steps per batch (the registers of 2 + CT operand quads each)
+    typedef Batch<CT, U> B;
+    static_assert(CT <= NW, "a wavefront finishes at most one tile");
+    __shared__ f32x4_t red[NW][CT][64];
     __shared__ int last_s;
-    // timeline class: a residual projection whose reduction is longer than its output is the down
-    // projection, otherwise the O projection
-    const int TLC = EPI == EPI_QKV ? TL_QKV : (a.K > a.n_tiles * 16 ? TL_DOWN : TL_O);
+    // timeline class: a reduction longer than the output is the down projection's
+    const int TLC = a.K > a.n_tiles * 16 ? TL_DOWN : TL_O;
     (void)TLC;
     NLD_TS(TLC, 0);
 
@@ -705,73 +465,55 @@ __global__ void __launch_bounds__(NW * 64) gemm_splitk_kernel(GemmArgs a, float*
     const int s_begin = min(ke, kb + wave * per);
     const int s_end = min(ke, s_begin + per);
 
-    // epilogue inputs of this wavefront's first tile, fetched up front: residual rows 4g + i
-    // of the tile and the next RMSNorm gain of column r
+    // epilogue inputs of this wavefront's tile (wavefronts past CT have none), fetched up front: residual rows
+    // 4g + i of the tile and the next RMSNorm gain of column r
+    const int t = t0 + wave;
+    const bool mine = wave < CT && t < a.n_tiles;
     float xres[4] = {0.f, 0.f, 0.f, 0.f}, gn = 0.f;
-    if (EPI == EPI_RESID && wave < NTL) {
-        const int mt = wave / CT, t = t0 + wave % CT;
-        if (t < a.n_tiles) {
-            gn = bf16_to_f32(a.gain_next[t * 16 + r]);
+    if (mine) {
+        gn = bf16_to_f32(a.gain_next[t * 16 + r]);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int m = 16 * mt + 4 * g + i;
-                if (m < a.M) xres[i] = a.x[(size_t)m * N + t * 16 + r];
-            }
-        }
+        for (int i = 0; i < 4; ++i)
+            if (4 * g + i < a.M) xres[i] = a.x[(size_t)(4 * g + i) * N + t * 16 + r];
     }
 
     const uint4* wp[CT];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) wp[ct] = a.W + (size_t)min(t0 + ct, a.n_tiles - 1) * a.ksteps * 64 + lane;
-    const uint16_t* ap[MT];
-    bool aok[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        aok[mt] = mt * 16 + r < a.M;
-        ap[mt] = a.A + (size_t)mt * a.ksteps * 1024 + (size_t)lane * 8;
-    }
+    const bool aok = r < a.M;
+    const uint16_t* ap = a.A + (size_t)lane * 8;
 
-    f32x4_t acc[MT][CT], accl[MT][CT];
+    f32x4_t acc[CT], accl[CT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            acc[mt][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            accl[mt][ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        }
+    for (int ct = 0; ct < CT; ++ct) {
+        acc[ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        accl[ct] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
 
     const uint4 zero4 = {0u, 0u, 0u, 0u};
     auto load = [&](int s, B& buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int ss = s + u;
-            const bool in = ss < s_end;
+            const bool in = ss < s_end, ok = in && aok && ss * 32 + 8 * g < a.K;
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) buf.w[u][ct] = in ? wp[ct][(size_t)ss * 64] : zero4;
-            const int kcol = ss * 32 + 8 * g;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const bool ok = in && aok[mt] && kcol < a.K;
-                buf.x[u][mt] = ok ? *(const uint4*)(ap[mt] + (size_t)ss * 1024) : zero4;
-                buf.xl[u][mt] = ok ? *(const uint4*)(ap[mt] + (size_t)ss * 1024 + SPLIT_LO) : zero4;
-            }
+            buf.x[u] = ok ? *(const uint4*)(ap + (size_t)ss * 1024) : zero4;
+            buf.xl[u] = ok ? *(const uint4*)(ap + (size_t)ss * 1024 + SPLIT_LO) : zero4;
         }
     };
     auto compute = [&](const B& buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int ct = 0; ct < CT; ++ct) {
-                    acc[mt][ct] = mfma_16x16x32(buf.x[u][mt], buf.w[u][ct], acc[mt][ct]);
-                    accl[mt][ct] = mfma_16x16x32(buf.xl[u][mt], buf.w[u][ct], accl[mt][ct]);
-                }
+            for (int ct = 0; ct < CT; ++ct) {
+                acc[ct] = mfma_16x16x32(buf.x[u], buf.w[u][ct], acc[ct]);
+                accl[ct] = mfma_16x16x32(buf.xl[u], buf.w[u][ct], accl[ct]);
+            }
     };
 
     B b0, b1;
     load(s_begin, b0);
-    if constexpr (NORMED) rms_scales(a, 0, 16 * MT, inv_s);   // visible after the barrier below
     for (int s = s_begin; s < s_end; s += 2 * U) {
         load(s + U, b1);
         compute(b0);
@@ -779,37 +521,24 @@ __global__ void __launch_bounds__(NW * 64) gemm_splitk_kernel(GemmArgs a, float*
         compute(b1);
     }
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) red[wave][mt * CT + ct][lane] = acc[mt][ct] + accl[mt][ct];
+    for (int ct = 0; ct < CT; ++ct) red[wave][ct][lane] = acc[ct] + accl[ct];
     __syncthreads();
     NLD_TS(TLC, 1);   // main loop done
 
+    // the workgroup's partial of the wavefront's tile (fixed order over the wavefronts), kept in registers and,
+    // with ksplit > 1, stored for the last workgroup
     typedef unsigned long long u64;
-    // the workgroup's partials of the wavefront's tiles ti = wave, wave + NW, ... (fixed order over
-    // the wavefronts), kept in registers and, with ksplit > 1, stored for the last workgroup
-    constexpr int TPW = (NTL + NW - 1) / NW;
-    f32x4_t v[TPW];
+    f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+    if (wave < CT) {
 #pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-        const int ti = wave + q * NW;
-        v[q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        if (ti < NTL) {
-#pragma unroll
-            for (int w = 0; w < NW; ++w) v[q] += red[w][ti][lane];
-        }
+        for (int w = 0; w < NW; ++w) v += red[w][wave][lane];
     }
     if (ksplit > 1) {
-#pragma unroll
-        for (int q = 0; q < TPW; ++q) {
-            const int ti = wave + q * NW;
-            if (ti < NTL) {
-                u64* pp = (u64*)(part + ((((size_t)cg * ksplit + ks) * NTL + ti) * 64 + lane) * 4);
-                __hip_atomic_store(pp, __builtin_bit_cast(u64, f32x2_t{v[q][0], v[q][1]}), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(pp + 1, __builtin_bit_cast(u64, f32x2_t{v[q][2], v[q][3]}), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            }
+        auto at = [&](int sl) { return (u64*)(part + ((((size_t)cg * ksplit + sl) * CT + wave) * 64 + lane) * 4); };
+        if (wave < CT) {
+            u64* pp = at(ks);
+            __hip_atomic_store(pp, __builtin_bit_cast(u64, f32x2_t{v[0], v[1]}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(pp + 1, __builtin_bit_cast(u64, f32x2_t{v[2], v[3]}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         // every lane's stores are acknowledged before the workgroup counts itself in
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -822,74 +551,38 @@ __global__ void __launch_bounds__(NW * 64) gemm_splitk_kernel(GemmArgs a, float*
         NLD_TS(TLC, 2);   // partial counted in
         if (!last_s) return;
         if (threadIdx.x == 0) __hip_atomic_exchange(ctr + cg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int q = 0; q < TPW; ++q) {
-            const int ti = wave + q * NW;
-            if (ti >= NTL) continue;
+        if (wave < CT) {
             f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
             for (int sl = 0; sl < ksplit; ++sl) {
                 if (sl == ks) {
-                    sum += v[q];
+                    sum += v;
                     continue;
                 }
-                const u64* qq = (const u64*)(part + ((((size_t)cg * ksplit + sl) * NTL + ti) * 64 + lane) * 4);
+                const u64* qq = at(sl);
                 const f32x2_t lo = __builtin_bit_cast(f32x2_t, __hip_atomic_load(qq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
                 const f32x2_t hi = __builtin_bit_cast(f32x2_t, __hip_atomic_load(qq + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
                 sum += f32x4_t{lo[0], lo[1], hi[0], hi[1]};
             }
-            v[q] = sum;
+            v = sum;
         }
     }
+    if (!mine) return;
 #pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-        const int ti = wave + q * NW;
-        if (ti >= NTL) continue;
-        const int mt = ti / CT, t = t0 + ti % CT;
-        if (t >= a.n_tiles) continue;
-        if (EPI == EPI_RESID && q > 0) {
-            gn = bf16_to_f32(a.gain_next[t * 16 + r]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int m = 16 * mt + 4 * g + i;
-                xres[i] = m < a.M ? a.x[(size_t)m * N + t * 16 + r] : 0.f;
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int m = 16 * mt + 4 * g + i;
-            if constexpr (EPI == EPI_RESID) {
-                epi_resid(a, v[q][i], m, t, lane, xres[i], gn);
-            } else {
-                const int mc = min(m, a.M - 1);
-                const int pos = committed_length(a.lengths, mc / a.k_blk, a.max_len, a.status) + mc % a.k_blk;
-                epi_qkv(a, v[q][i] * inv_s[m], m, t, lane, pos);
-            }
-        }
-    }
+    for (int i = 0; i < 4; ++i) epi_resid(a, v[i], 4 * g + i, t, lane, xres[i], gn);
 }
 
-bool gemm_splitk_supported(int epi, int M, int ct) {
-    return (epi == EPI_RESID || epi == EPI_QKV) && M >= 1 && M <= 16 && ct >= 2 && ct <= 4;
-}
-
-template <int EPI>
-static void launch_splitk_epi(int ct, dim3 grid, const GemmArgs& a, float* part, unsigned* ctr, int ksplit, hipStream_t s) {
-    if (ct == 4) launch(gemm_splitk_kernel<1, 4, 8, EPI>, grid, dim3(512), s, a, part, ctr, ksplit);
-    else if (ct == 3) launch(gemm_splitk_kernel<1, 3, 8, EPI>, grid, dim3(512), s, a, part, ctr, ksplit);
-    else launch(gemm_splitk_kernel<1, 2, 8, EPI>, grid, dim3(512), s, a, part, ctr, ksplit);
-}
-
-hipError_t launch_gemm_splitk(int epi, int ct, int ksplit, const GemmArgs& a, float* part, unsigned* ctr,
-                              hipStream_t s) {
-    if (!gemm_splitk_supported(epi, a.M, ct) || a.W2 || ksplit < 1 || ksplit > SPLITK_MAX) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((a.n_tiles + ct - 1) / ct), (unsigned)ksplit);
-    if (epi == EPI_RESID) launch_splitk_epi<EPI_RESID>(ct, grid, a, part, ctr, ksplit, s);
-    else launch_splitk_epi<EPI_QKV>(ct, grid, a, part, ctr, ksplit, s);
+hipError_t launch_gemm_splitk(int ct, int ksplit, const GemmArgs& a, float* part, unsigned* ctr, hipStream_t s) {
+    if (a.M > 16 || a.W2 || ct < 2 || ct > 4 || ksplit < 1 || ksplit > SPLITK_MAX) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((a.n_tiles + ct - 1) / ct), (unsigned)ksplit), blk(512);
+    if (ct == 4) launch(gemm_splitk_kernel<4, 8>, grid, blk, s, a, part, ctr, ksplit);
+    else if (ct == 3) launch(gemm_splitk_kernel<3, 8>, grid, blk, s, a, part, ctr, ksplit);
+    else launch(gemm_splitk_kernel<2, 8>, grid, blk, s, a, part, ctr, ksplit);
     return hipGetLastError();
 }
 
 // =====================================================================================
-// Panel GEMM: every projection of a pass with more than 16 rows.  A workgroup of 8 wavefronts
+// Panel GEMM: every projection, except where the three kernels above are faster at up to 16 rows (the LM
+// head of a long vocabulary, O, and down up to 8 rows).  A workgroup of 8 wavefronts
 // computes 16*RT rows x 16*WC*CT columns over one K slice: WC wavefronts side by side, each with
 // CT column tiles against all RT row tiles, times WK = 8 / WC wavefront groups that take the
 // k-steps of a stage in turn and meet in LDS at the end.
@@ -1535,6 +1228,7 @@ static constexpr PanelShape PANEL_SHAPES[] = {
     {2, 8, 1, 2}, {2, 4, 1, 4}, {2, 4, 2, 4}, {2, 4, 3, 2}, {2, 2, 3, 4},
     {4, 8, 1, 2}, {4, 4, 1, 4}, {4, 4, 2, 2}, {4, 4, 3, 2},
     {8, 4, 1, 2}, {8, 8, 1, 2}, {8, 8, 2, 2}, {8, 8, 3, 2},
+    {1, 2, 3, 4}, {1, 4, 1, 4}, {1, 8, 1, 4}, {1, 1, 3, 8},
 };
 int gemm_panel_shapes() { return (int)(sizeof(PANEL_SHAPES) / sizeof(PANEL_SHAPES[0])); }
 PanelShape gemm_panel_shape(int i) { return PANEL_SHAPES[i]; }
@@ -1580,7 +1274,11 @@ hipError_t launch_gemm_panel(int epi, int shape, const GemmArgs& a, int ksplit, 
         case 9: return launch_panel_epi<8, 4, 1, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
         case 10: return launch_panel_epi<8, 8, 1, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
         case 11: return launch_panel_epi<8, 8, 2, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
-        default: return launch_panel_epi<8, 8, 3, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 12: return launch_panel_epi<8, 8, 3, 2>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 13: return launch_panel_epi<1, 2, 3, 4>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 14: return launch_panel_epi<1, 4, 1, 4>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        case 15: return launch_panel_epi<1, 8, 1, 4>(epi, grid, R, C, a, ksplit, part, ctr, s);
+        default: return launch_panel_epi<1, 1, 3, 8>(epi, grid, R, C, a, ksplit, part, ctr, s);
     }
 }
 

@@ -284,23 +284,20 @@ hipError_t launch_pack(const PackArgs& a, hipStream_t s);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_copy_u32(const uint32_t* src, uint32_t* dst, hipStream_t s);   // *dst = *src (one word)
 hipError_t launch_embed(const EmbedArgs& a, hipStream_t s);
-// Normed multi-tile GEMM (M <= 16).  ks = k-steps per wavefront (ksteps = ks * waves); grid = workgroups.
+// Normed multi-tile GEMM (LM head, M <= 16).  ks = k-steps per wavefront (ksteps = ks * waves); grid = workgroups.
 bool gemm_norm_supported(int ks);
 int gemm_norm_max_waves(int ks);
-hipError_t launch_gemm_norm(int epi, int ks, int waves, int grid, const GemmArgs& a, hipStream_t s);
-// Streamed GEMM (M <= 16): 16*ct columns per workgroup, nw wavefronts split K.  The normed epilogues form
-// the per-row scale from part_ss.  With a.W2 set (EPI_RESID only) the reduction continues over the second
-// source.
-hipError_t launch_gemm_stream(int epi, int ct, int nw, int grid_x, const GemmArgs& a, hipStream_t s);
-// Split-K GEMM (EPI_RESID or EPI_QKV; M <= 16, no second source): ct column tiles per workgroup (2..4), the
-// reduction cut into ksplit slices (1..SPLITK_MAX) whose partials meet in `part`
-// (ceil(n_tiles/ct) * ksplit * 256*ct floats; unused with ksplit = 1); `ctr` holds one counter per column
-// group, zero before the launch and zero again after it.
+hipError_t launch_gemm_norm(int ks, int waves, int grid, const GemmArgs& a, hipStream_t s);
+// Streamed GEMM (EPI_RESID, M <= 16): one column tile per workgroup, nw (8 or 16) wavefronts split K.  With
+// a.W2 set the reduction continues over the second source.
+hipError_t launch_gemm_stream(int nw, const GemmArgs& a, hipStream_t s);
+// Split-K GEMM (EPI_RESID, M <= 16, no second source): ct column tiles per workgroup (2..4), the reduction cut
+// into ksplit slices (1..SPLITK_MAX) whose partials meet in `part` (ceil(n_tiles/ct) * ksplit * 256*ct floats;
+// unused with ksplit = 1); `ctr` holds one counter per column group, zero before the launch and zero again
+// after it.
 constexpr int SPLITK_MAX = 8;
-bool gemm_splitk_supported(int epi, int M, int ct);
-hipError_t launch_gemm_splitk(int epi, int ct, int ksplit, const GemmArgs& a, float* part, unsigned* ctr,
-                              hipStream_t s);
-// Panel GEMM (every projection of more than 16 rows): a workgroup takes 16*rt rows x 16*wc*ct columns and
+hipError_t launch_gemm_splitk(int ct, int ksplit, const GemmArgs& a, float* part, unsigned* ctr, hipStream_t s);
+// Panel GEMM (any projection): a workgroup takes 16*rt rows x 16*wc*ct columns and
 // one of ksplit K slices (each at least one stage of kb k-steps); the operand must be allocated for whole
 // row groups.  ksplit > 1: `part` holds 256*rt*wc*ct floats per (row group, column group, slice) and `ctr`
 // one counter per (row group, column group), zero before the launch and zero again after it.  The LM head

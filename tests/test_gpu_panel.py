@@ -1,4 +1,4 @@
-"""The panel GEMM (every projection of more than 16 rows): each workgroup shape and K-slice count against
+"""The panel GEMM: each workgroup shape and K-slice count against
 the oracle, at the sizes where tiles, stages and slices do not divide.
 
 Tolerance.  Every product carries its activation as a bf16 value and its bf16 remainder, a relative error of
@@ -21,7 +21,8 @@ TOL = 1.2e-4
 ODD = ModelShape(n_layers=2, hidden=160, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=88, vocab=333, lora_rank=32,
                  lora_alpha=64.0)
 LONG = ModelShape(**{**SHAPE_TINY.__dict__, "hidden": 512, "ffn": 1072})   # enough stages for several slices
-SHAPES = {2: range(0, 5), 4: range(5, 9), 8: range(9, 13)}                # by row tiles
+SHAPES = {2: range(0, 5), 4: range(5, 9), 8: range(9, 13), 1: range(13, 17)}   # by row tiles
+STAGE = {1: 4, 2: 4, 4: 4, 6: 4, 13: 4, 14: 4, 15: 4, 16: 8}                   # k-steps per stage (2 else)
 NAMES = ("O", "DOWN", "QKV", "GU", "LM")
 
 
@@ -55,23 +56,23 @@ def run(R, t, batch, k, mode):
     return rel_err(g, ref)
 
 
-@pytest.mark.parametrize("batch,k", [(1, 17), (1, 32), (3, 11), (1, 64), (5, 13), (2, 64), (3, 43)])
+@pytest.mark.parametrize("batch,k", [(1, 1), (3, 3), (1, 16), (1, 17), (1, 32), (3, 11), (1, 64), (5, 13), (2, 64), (3, 43)])
 @pytest.mark.parametrize("slices", [1, 3])
 def test_every_shape(R, model, monkeypatch, batch, k, slices):
-    """17..32, 33..64 and more than 64 rows (one and two row groups), every shape forced on every projection."""
-    rt = 2 if batch * k <= 32 else 4 if batch * k <= 64 else 8
+    """Up to 16, 32, 64 and more than 64 rows (one and two row groups), every shape forced on every projection
+    that takes it (up to 16 rows O has a kernel of its own, and down up to 8)."""
+    rt = 1 if batch * k <= 16 else 2 if batch * k <= 32 else 4 if batch * k <= 64 else 8
     for i in SHAPES[rt]:
         for n in NAMES:
-            kb = {0: 2, 1: 4, 2: 4, 3: 2, 4: 4, 5: 2, 6: 4}.get(i, 2)
             steps = (model["shape"].ffn if n == "DOWN" else model["shape"].hidden) // 32
-            monkeypatch.setenv("NLD_PANEL_" + n, "%d,%d" % (i, max(1, min(slices, steps // kb))))
+            monkeypatch.setenv("NLD_PANEL_" + n, "%d,%d" % (i, max(1, min(slices, steps // STAGE.get(i, 2)))))
         for mode in (O.VERIFY, O.DRAFT):
             e = run(R, model, batch, k, mode)
             log("panel shape %d slices %d rows %d %s: rel err %.2e" % (i, slices, batch * k, mode, e))
             assert e <= TOL
 
 
-@pytest.mark.parametrize("batch,k", [(1, 16), (1, 17), (2, 32), (2, 33), (9, 15)])
+@pytest.mark.parametrize("batch,k", [(1, 8), (1, 9), (1, 16), (1, 17), (2, 32), (2, 33), (9, 15)])
 def test_planned(R, model, batch, k):
     """The plans the library picks, on both sides of each row-tile boundary."""
     for mode in (O.VERIFY, O.DRAFT):
