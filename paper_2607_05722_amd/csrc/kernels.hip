@@ -1330,8 +1330,13 @@ __device__ __forceinline__ int stage_key(int tau, int rho) {
 // 16 bytes per lane from global memory to LDS at byte `dst` + 16 * lane (dst uniform).  Inline assembly: the
 // compiler waits for every such load before any later LDS read, which would take the stages one by one.
 // It has no register result; stage_wait() and a barrier stand between it and the reads.
+// ONCE: nobody reads the bytes again before they leave the caches, which the load passes by.
+template <bool ONCE>
 __device__ __forceinline__ void load_to_lds(const void* src, uint32_t dst) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory", "m0");
+    if constexpr (ONCE)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(dst), "v"(src) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(dst), "v"(src) : "memory", "m0");
 }
 // at most N vector memory operations of this wavefront still under way
 template <int N>
@@ -1445,17 +1450,24 @@ attention_kernel(AttnArgs a) {
     // 64 keys from kp and vp into a slot: wavefront w takes 1 KiB blocks w, w + nw, ...  LDS position p of a
     // row holds chunk p ^ swizzle(row).
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+    // A batch's cache is read once per pass where one workgroup takes all rows (KH 2, NS 2: the batches' kernel
+    // for up to 64 rows).  Non-temporal loads there: attention and merge 197 -> 183 us at batch 100, k = 1 (840 MB of
+    // keys and values), 178 -> 160 us at batch 32, k = 16 (580 MB), 112 -> 104 us at batch 8 of 16000 keys.  With
+    // five and more row tiles (KH 1) the matrix units are the bound, and one sequence's cache fits the caches:
+    // neither gains.  (K and V rows requested half a stage apart, so that a stage and a half is always under
+    // way: no gain over this, 241 instead of 210 us at KH 1.)
+    constexpr bool ONCE = KH == 2 && NS == 2;
     auto dma = [&](const uint16_t* kp, const uint16_t* vp, int slot) __attribute__((always_inline)) {
         const uint32_t dst = lds0 + (uint32_t)slot * C::CHUNKS * 16;
 #pragma unroll 1
         for (int i = wave; i < C::KCHUNKS / 64; i += nw) {
             const int q = i * 64 + lane, kr = q / C::KCH, c = (q % C::KCH) ^ kswz<D>(kr);
-            load_to_lds(kp + (kr * C::KCH + c) * 8, __builtin_amdgcn_readfirstlane(dst + i * 1024));
+            load_to_lds<ONCE>(kp + (kr * C::KCH + c) * 8, __builtin_amdgcn_readfirstlane(dst + i * 1024));
         }
 #pragma unroll 1
         for (int i = wave; i < C::VCHUNKS / 64; i += nw) {
             const int q = i * 64 + lane, d = q >> 3, c = (q & 7) ^ vswz(d);
-            load_to_lds(vp + (d * 8 + c) * 8, __builtin_amdgcn_readfirstlane(dst + C::KCHUNKS * 16 + i * 1024));
+            load_to_lds<ONCE>(vp + (d * 8 + c) * 8, __builtin_amdgcn_readfirstlane(dst + C::KCHUNKS * 16 + i * 1024));
         }
     };
     auto dma_keys = [&](int kb, int slot) __attribute__((always_inline)) {
@@ -1722,7 +1734,6 @@ __global__ void __launch_bounds__(D) attention_combine_kernel(AttnArgs a) {
     const int b = unit / nkv, kvh = unit % nkv, k = a.k_blk;
     // parts: a batch's work items, or one sequence's prefix splits and the block part
     const int ns = a.items ? attn_items(a, attn_length(a, b)) : a.n_splits + 1;
-    auto pidx = [](int j) { return j; };
     const size_t ubase = (size_t)unit * a.n_parts * a.rows_pad + rw;
     // With at most FAST parts every load of the workgroup is issued at once: thread d's part
     // statistics and its column of every part's output.  More parts take the looped path.
@@ -1731,10 +1742,10 @@ __global__ void __launch_bounds__(D) attention_combine_kernel(AttnArgs a) {
     float2 ml0 = float2{-INFINITY, 0.f};
     float os[FAST];
     if (fast) {
-        if (d < ns) ml0 = *(const float2*)(a.part_ml + (ubase + (size_t)pidx(d) * a.rows_pad) * 2);
+        if (d < ns) ml0 = *(const float2*)(a.part_ml + (ubase + (size_t)d * a.rows_pad) * 2);
 #pragma unroll
         for (int e = 0; e < FAST; ++e)
-            os[e] = e < ns ? a.part_o[(ubase + (size_t)pidx(e) * a.rows_pad) * D + d] : 0.f;
+            os[e] = e < ns ? a.part_o[(ubase + (size_t)e * a.rows_pad) * D + d] : 0.f;
     }
     // split statistics -> weights exp2(m_s - max) in LDS (ns <= 256)
     float ms = -INFINITY, ls = 0.f;
@@ -1743,7 +1754,7 @@ __global__ void __launch_bounds__(D) attention_combine_kernel(AttnArgs a) {
         ms = ml0.x;
     } else {
         for (int sp = d; sp < ns; sp += D) {
-            const float2 ml = *(const float2*)(a.part_ml + (ubase + (size_t)pidx(sp) * a.rows_pad) * 2);
+            const float2 ml = *(const float2*)(a.part_ml + (ubase + (size_t)sp * a.rows_pad) * 2);
             wsh[sp] = ml.x;
             ms = fmaxf(ms, ml.x);
         }
@@ -1769,7 +1780,7 @@ __global__ void __launch_bounds__(D) attention_combine_kernel(AttnArgs a) {
         for (int sp = d; sp < ns; sp += D) {
             const float msp = wsh[sp];
             const float w = (msp == -INFINITY) ? 0.f : exp2f(msp - mx);
-            ls += w * a.part_ml[(ubase + (size_t)pidx(sp) * a.rows_pad) * 2 + 1];
+            ls += w * a.part_ml[(ubase + (size_t)sp * a.rows_pad) * 2 + 1];
             wsh[sp] = w;
         }
     }
@@ -1795,11 +1806,11 @@ __global__ void __launch_bounds__(D) attention_combine_kernel(AttnArgs a) {
         for (; sp + 8 <= ns; sp += 8) {
             float o8[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o8[e] = a.part_o[(ubase + (size_t)pidx(sp + e) * a.rows_pad) * D + d];
+            for (int e = 0; e < 8; ++e) o8[e] = a.part_o[(ubase + (size_t)(sp + e) * a.rows_pad) * D + d];
 #pragma unroll
             for (int e = 0; e < 8; ++e) num += wsh[sp + e] * o8[e];
         }
-        for (; sp < ns; ++sp) num += wsh[sp] * a.part_o[(ubase + (size_t)pidx(sp) * a.rows_pad) * D + d];
+        for (; sp < ns; ++sp) num += wsh[sp] * a.part_o[(ubase + (size_t)sp * a.rows_pad) * D + d];
     }
     const int hl = rw / k, j = rw % k;
     store_split(a.o, split_index(b * k + j, (kvh * G + hl) * D + d, a.n_q_heads * D / 32), num * inv_den,
