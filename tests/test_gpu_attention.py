@@ -73,3 +73,12 @@ def test_ragged_batch(R, model, monkeypatch, k, keys):
     monkeypatch.setenv("NLD_ATTN_ITEM_KEYS", str(keys))
     check(R, model, [0, 64, 1, CAP - 64, 63, 129, 192], k, O.VERIFY)
     check(R, model, [65, 0, 128], k, O.DRAFT)
+
+
+@pytest.mark.parametrize("batch,k", [(515, 1), (200, 17)])
+def test_merge_of_many_rows(R, model, monkeypatch, batch, k):
+    """The merge that takes a row to D / 8 lanes (from 512 workgroups on): rows that do not fill its last
+    workgroup, one to seven parts a row, sequences without a prefix."""
+    monkeypatch.setenv("NLD_ATTN_ITEM_KEYS", "64")
+    lens = [(i * 53) % (CAP - 17) for i in range(batch)]
+    check(R, model, lens, k, O.VERIFY)
