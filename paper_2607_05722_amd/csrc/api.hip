@@ -150,8 +150,8 @@ Layout make_layout(const nld_config& c, int batch, int k, int max_len, int quad_
     // 256 partials per row.  A batch: workgroups as wide as the rows need, and items of about 1024 keys where
     // the capacity has at least four of those per CU, else of 384, so that the CUs share few sequences evenly
     // (an item's own start, its place in the list, queries and first stage, is about 6 us, or five stages);
-    // never more than fit the room at 16 rows per row tile.  Attention and merge at 1024 / 384 keys: batch 32
-    // at 8064 keys, k = 1 200 / 214 us; batch 5 at 3000 keys, k = 24 45 / 28 us; batch 2 at 4000 keys, k = 16
+    // never more than fit the room at 16 rows per row tile.  Attention and merge at 1024 / 384 keys: batch 8
+    // at 16000 keys, k = 8 104 / 123 us; batch 5 at 3000 keys, k = 24 45 / 28 us; batch 2 at 4000 keys, k = 16
     // 31 / 20 us.  NLD_ATTN_ITEM_KEYS overrides.
     const int zmax = L.attn_kh == 2 ? 4 : 12;
     L.attn_z = cdiv(L.row_tiles, zmax);
