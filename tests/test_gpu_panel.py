@@ -8,7 +8,8 @@ at most 15 * 2^-17 = 1.2e-4 where nothing amplifies them; the oracle's own f32 s
 import numpy as np
 import pytest
 
-from gpu_common import log, rel_err
+from gpu_common import ArraySource, BF16_ONE, int_to_bf16_bits, log, rel_err
+import synth
 from oracle import nld_oracle as O
 from synth.workloads import LazyWeights, ModelShape, SHAPE_TINY, tokens as synth_tokens
 
@@ -77,3 +78,58 @@ def test_planned(R, model, batch, k):
     """The plans the library picks, on both sides of each row-tile boundary."""
     for mode in (O.VERIFY, O.DRAFT):
         assert run(R, model, batch, k, mode) <= TOL
+
+
+def bf16_parts(v):
+    """v as a sum of three bf16 values (bits)."""
+    parts, rest = [], np.float64(v)
+    for _ in range(3):
+        bits = np.uint16(np.float32(rest).view(np.uint32) >> 16)   # truncated, so that the rest is exact
+        parts.append(bits)
+        rest -= np.float64(np.array(np.uint32(bits) << 16, np.uint32).view(np.float32))
+    return parts
+
+
+@pytest.mark.parametrize("batch,k", [(1, 1), (1, 8), (1, 32), (1, 64), (2, 64)])
+@pytest.mark.parametrize("large", [False, True])
+def test_swiglu_of_large_gates(R, batch, k, large):
+    """Gates past the point where exp(-gate) overflows (88.73) give -0 like any other large negative gate,
+    large positive ones the gate itself.  Every token's embedding is one and the gates are set by
+    the weights: gate f goes to column f of the residual.  One gate in eight is ordinary."""
+    shape = ModelShape(n_layers=1, hidden=128, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=96, vocab=200, rms_eps=0.0)
+    h, f = shape.hidden, shape.ffn
+    gates = list(np.linspace(-104.0, -88.73, 72)) + [-80.0, -88.7, -88.72, -88.8, -93.0, -95.0, -97.0, -99.0, -101.0,
+                                                     -103.97, -110.0, -1e4]
+    gates += [1e4] * 2 if large else [-1e30] * 2
+    gates += [0.5, -0.5, 2.0, -2.0, 5.0, -5.0, 20.0, -20.0, 1.0, -1.0]
+    zero = lambda o, i: np.zeros((o, i), dtype=np.uint16)   # noqa: E731
+    gate, up, down = zero(f, h), zero(f, h), zero(h, f)
+    for i, g in enumerate(gates):
+        gate[i, :3] = bf16_parts(g)
+        up[i, 0] = down[i, i] = BF16_ONE
+    ones = lambda n: np.full(n, BF16_ONE, dtype=np.uint16)   # noqa: E731
+    layer = {"attn_norm": ones(h), "wq": zero(shape.q_dim, h), "wk": zero(shape.kv_dim, h), "wv": zero(shape.kv_dim, h),
+             "wo": zero(h, shape.q_dim), "ffn_norm": ones(h), "w_gate": gate, "w_up": up, "w_down": down}
+    lm = int_to_bf16_bits(synth.uniform_int(3, "swiglu.lm", (shape.vocab, h), -8, 8))
+    src = ArraySource([layer], np.full((shape.vocab, h), BF16_ONE, dtype=np.uint16), lm, ones(h))
+    t = {"shape": shape, "w": O.OracleWeights(shape, src, np.float64), "m": R.DeviceModel(shape, src)}
+    with np.errstate(over="ignore"):
+        for mode in (O.VERIFY, O.DRAFT):
+            assert run(R, t, batch, k, mode) <= TOL   # false for a NaN
+
+
+@pytest.mark.parametrize("k", [8, 32, 64])
+@pytest.mark.parametrize("bits", [0x7FC0, 0xFFC0])
+def test_nan_logit_reaches_the_confidence(R, k, bits):
+    """A NaN logit of either sign is part of its row's softmax sum: the confidence is NaN."""
+    shape = ModelShape(n_layers=1, hidden=128, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=96, vocab=200)
+    src = LazyWeights(shape, 5)
+    lm = np.array(src.lm_head, copy=True)
+    lm[17] = bits
+    model = R.DeviceModel(shape, ArraySource([src.layer(0)], src.embed, lm, src.final_norm))
+    cache, ws = R.DeviceCache(shape, 1, 128), R.Workspace(model, 1, k, 128)
+    block = torch.from_numpy(synth_tokens(shape, 5, "panel.nan", (1, k))).cuda()
+    block[:, 1:] = shape.mask_token_id
+    out = R.denoise_step(model, cache, ws, block, 0.5)
+    assert torch.isnan(out["confidence"]).all()
+    assert R.read_device_status(ws) == 0
