@@ -474,7 +474,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
         HIP_TRY(launch_embed(e, s));
     }
 
-    int n_ss = EMBED_SS;   // sums of squares per row in part_ss, as its latest producer wrote them
+    int n_ss = embed_sums(c.hidden);   // sums of squares per row in part_ss, as its latest producer wrote them
     const int ks_h = cdiv(c.hidden, 32), ks_q = cdiv(nq * D, 32), ks_f = cdiv(c.ffn, 32);
     const bool lora = io.mode == NLD_MODE_DRAFT && c.lora_rank > 0;
     PanelPlan plans[N_PROJ];   // the same for every layer

@@ -1962,11 +1962,12 @@ __global__ void __launch_bounds__(256) embed_kernel(EmbedArgs a) {
         row_ss += ss;
     }
     row_ss = wave_sum(row_ss);
-    if ((threadIdx.x & 63) == 0) a.part_ss[m * EMBED_SS + (threadIdx.x >> 6)] = row_ss;
+    const int sums = embed_sums(a.hidden), wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0 && wave < sums) a.part_ss[(size_t)m * sums + wave] = row_ss;
 }
 
 hipError_t launch_embed(const EmbedArgs& a, hipStream_t s) {
-    launch(embed_kernel, dim3(a.M), dim3(64 * EMBED_SS), s, a);
+    launch(embed_kernel, dim3(a.M), dim3(64 * EMBED_WAVES), s, a);
     return hipGetLastError();
 }
 

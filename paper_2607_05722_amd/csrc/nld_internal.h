@@ -197,7 +197,11 @@ struct AttnArgs {
     uint32_t plain;      // PlainSite bits: SITE_P (probabilities), SITE_O (the merged output)
 };
 
-constexpr int EMBED_SS = 4;   // sums of squares per row the embedding kernel writes (one per wavefront)
+// Wavefronts of the embedding kernel, and the sums of squares per row that it writes: one per wavefront, but no more
+// than one per 16 columns, which is what the buffer has room for.  (A thread takes 16 columns, so wavefronts past that
+// count have none.)
+constexpr int EMBED_WAVES = 4;
+constexpr int embed_sums(int hidden) { return hidden / 16 < EMBED_WAVES ? hidden / 16 : EMBED_WAVES; }
 
 struct EmbedArgs {
     const int32_t* tokens;  // source 0: [batch][k]
@@ -209,7 +213,7 @@ struct EmbedArgs {
     const uint16_t* gain;   // first layer's attention RMSNorm gain
     float* x;
     uint16_t* xg;           // split x * gain, split_index with hidden/32 steps
-    float* part_ss;         // [M][EMBED_SS]
+    float* part_ss;         // [M][embed_sums(hidden)]
     uint32_t* status;
     unsigned* tile_ctr;     // [n_tile_ctr] dynamic tile counters of this pass's GEMMs, zeroed here
     int n_tile_ctr;

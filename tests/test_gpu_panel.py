@@ -133,3 +133,15 @@ def test_nan_logit_reaches_the_confidence(R, k, bits):
     out = R.denoise_step(model, cache, ws, block, 0.5)
     assert torch.isnan(out["confidence"]).all()
     assert R.read_device_status(ws) == 0
+
+
+@pytest.mark.parametrize("batch,k", [(1, 1), (1, 33), (1, 64), (4, 25), (2, 64)])
+def test_narrowest_model(R, batch, k):
+    """Hidden 32, the smallest there is: two sums of squares per row are all that its statistics have room for."""
+    shape = ModelShape(n_layers=2, hidden=32, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=40, vocab=77)
+    src = LazyWeights(shape, 13)
+    t = {"shape": shape, "w": O.OracleWeights(shape, src, np.float32), "m": R.DeviceModel(shape, src)}
+    for mode in (O.VERIFY, O.DRAFT):
+        e = run(R, t, batch, k, mode)
+        log("hidden 32 rows %d %s: rel err %.2e" % (batch * k, mode, e))
+        assert e <= TOL
