@@ -1537,19 +1537,24 @@ attention_kernel(AttnArgs a) {
         f32x4_t s[TPW];
 #pragma unroll
         for (int tt = 0; tt < TPW; ++tt) s[tt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        // A tile's products with the lo halves (2^-8 of the score) come first, so that only the hi products round
+        // at the score's size, as with two accumulators and without the second one's registers.
         // The scheduling barriers keep the compiler from reading a whole stage's operands ahead, which takes
         // more registers than a wavefront has here.
 #pragma unroll
-        for (int c = 0; c < DC; ++c) {
+        for (int tt = 0; tt < TPW; ++tt) {
+            const int row = (32 * (tt >> 1) + 4 * (tt & 1)) * C::KCH;
+            uint4 kop[DC];
 #pragma unroll
-            for (int tt = 0; tt < TPW; ++tt) {
-                const int at = kidx[c] + (32 * (tt >> 1) + 4 * (tt & 1)) * C::KCH;
-                const uint4 kop = kv[at];
-                s[tt] = mfma_16x16x32(kop, qb[c], s[tt]);
-                s[tt] = mfma_16x16x32(kop, ql[c], s[tt]);
-                if constexpr (own) s[tt] = mfma_16x16x32(kvl[at], qb[c], s[tt]);
+            for (int c = 0; c < DC; ++c) kop[c] = kv[kidx[c] + row];
+#pragma unroll
+            for (int c = 0; c < DC; ++c) {
+                s[tt] = mfma_16x16x32(kop[c], ql[c], s[tt]);
+                if constexpr (own) s[tt] = mfma_16x16x32(kvl[kidx[c] + row], qb[c], s[tt]);
             }
-            if ((c & 1) || own) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int c = 0; c < DC; ++c) s[tt] = mfma_16x16x32(kop[c], qb[c], s[tt]);
+            __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (edge) {
 #pragma unroll
