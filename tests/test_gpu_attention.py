@@ -8,7 +8,7 @@ hardware exp2 of 1 ulp on arguments below 2^4 in magnitude: 2^-20.
 import numpy as np
 import pytest
 
-from gpu_common import log, rel_err
+from gpu_common import ArraySource, BF16_ONE, log, rel_err
 from oracle import nld_oracle as O
 from synth.workloads import LazyWeights, ModelShape, prefix_kv, tokens as synth_tokens
 
@@ -82,3 +82,42 @@ def test_merge_of_many_rows(R, model, monkeypatch, batch, k):
     monkeypatch.setenv("NLD_ATTN_ITEM_KEYS", "64")
     lens = [(i * 53) % (CAP - 17) for i in range(batch)]
     check(R, model, lens, k, O.VERIFY)
+
+
+@pytest.mark.parametrize("D,k", [(64, 4), (128, 4), (64, 32), (128, 32)])
+def test_long_items_lose_nothing(R, monkeypatch, D, k):
+    """Work items of 1024 keys against 64-bit sums, beside items of 64: where a row's reference is its largest score
+    so far, the largest weight of an item is 1 and has no split error, however long the item.  (With a reference
+    that lags behind the maximum the long items are further off than the short ones, in whose only stage it is
+    the maximum.)  One layer without an FFN whose output is the attention's, rows that a few keys decide.  The ratio
+    of the two errors measured 1.00 to 1.013 over the four shapes, and 1.035 to 1.045 with a reference that lags by up
+    to 2^8: the line is between.  The bound on the error itself is that of the file."""
+    s = ModelShape(n_layers=1, hidden=128, n_q_heads=4, n_kv_heads=1, head_dim=D, ffn=8, vocab=160, rms_eps=0.0)
+    rng = np.random.default_rng(5)
+
+    def w(std, *n):
+        return ((rng.standard_normal(n, dtype=np.float32) * np.float32(std)).view(np.uint32) >> 16).astype(np.uint16)
+
+    ones = np.full(s.hidden, BF16_ONE, dtype=np.uint16)
+    layer = {"attn_norm": ones, "wq": w(0.25, s.q_dim, s.hidden), "wk": w(0.1, s.kv_dim, s.hidden),
+             "wv": w(0.1, s.kv_dim, s.hidden), "wo": w(0.1, s.hidden, s.q_dim), "ffn_norm": ones,
+             "w_gate": w(0, s.ffn, s.hidden), "w_up": w(0, s.ffn, s.hidden), "w_down": w(0, s.hidden, s.ffn)}
+    src = ArraySource([layer], w(1e-3, s.vocab, s.hidden), w(0.1, s.vocab, s.hidden), ones)
+    batch, cap = 32, 1152
+    lens = [1024 + i for i in range(batch)]
+    okv, cache = O.OracleKV(s, batch, cap, np.float64), R.DeviceCache(s, batch, cap)
+    kb, vb = prefix_kv(s, 21, 0, batch, cap)
+    okv.set_prefix_bf16(0, kb, vb, np.asarray(lens))
+    cache.load_prefix(0, kb, vb)
+    cache.set_lengths(lens)
+    model, tok = R.DeviceModel(s, src), synth_tokens(s, 21, "attn.long%d" % k, (batch, k))
+    ref, _, _ = O.block_forward(O.OracleWeights(s, src, np.float64), okv, tok, O.VERIFY)
+    e = {}
+    for keys in (64, 1024):
+        monkeypatch.setenv("NLD_ATTN_ITEM_KEYS", str(keys))
+        ws = R.Workspace(model, batch, k, cap)
+        g = R.block_forward(model, cache, ws, torch.from_numpy(tok).cuda(), R.VERIFY)[0].cpu().numpy().astype(np.float64)
+        assert R.read_device_status(ws) == 0
+        e[keys] = np.linalg.norm(g - ref) / np.linalg.norm(ref)
+    log("attention D %d k %d: error %.3e with items of 64 keys, %.3e with items of 1024" % (D, k, e[64], e[1024]))
+    assert e[1024] <= 1.025 * e[64] and e[1024] <= TOL
