@@ -826,15 +826,25 @@ gemm_panel_kernel(GemmArgs a, int R, int C, int ksplit, float* part, unsigned* c
     const int nst_all = full / KB;
     const int st0 = ksl * nst_all / ksplit, nst = (ksl + 1) * nst_all / ksplit - st0;
 
-    f32x4_t acc[RT][CT];
+    // The lo products have accumulators of their own where the registers allow it (at most 12 tiles), so that they
+    // do not round at the hi sum's size; elsewhere they share the hi products'.
+    constexpr bool TWO = RT == 1 || (RT == 2 && (EPI == EPI_QKV || EPI == EPI_RESID)) || EPI == EPI_SPLIT;
+    f32x4_t acc[RT][CT], accl[TWO ? RT : 1][TWO ? CT : 1];
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int j = 0; j < CT; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < CT; ++j) {
+            acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if constexpr (TWO) accl[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
 
     // LM head: rows 4g+i of column r instead, so that a logits store is 64 contiguous bytes per row
     auto mm = [](uint4 w, uint4 x, f32x4_t c) __attribute__((always_inline)) {
         return EPI == EPI_LMHEAD ? mfma_16x16x32(x, w, c) : mfma_16x16x32(w, x, c);
+    };
+    auto mm_lo = [&](uint4 w, uint4 x, int i, int c) __attribute__((always_inline)) {
+        if constexpr (TWO) accl[i][c] = mm(w, x, accl[i][c]);
+        else acc[i][c] = mm(w, x, acc[i][c]);
     };
 
     // this wavefront's operand blocks of a stage: blocks wave*APW .. +APW of [row tile][k-step][hi, lo]
@@ -892,7 +902,7 @@ gemm_panel_kernel(GemmArgs a, int R, int C, int ksplit, float* part, unsigned* c
 #pragma unroll
                         for (int c = 0; c < CT; ++c) acc[i][c] = mm(wr[u][kk][c], ah, acc[i][c]);
 #pragma unroll
-                        for (int c = 0; c < CT; ++c) acc[i][c] = mm(wr[u][kk][c], al, acc[i][c]);
+                        for (int c = 0; c < CT; ++c) mm_lo(wr[u][kk][c], al, i, c);
                     }
                     NLD_PANEL_LDW(st + u + 2, u, kk);
                     if (kk == 0) {
@@ -930,11 +940,17 @@ gemm_panel_kernel(GemmArgs a, int R, int C, int ksplit, float* part, unsigned* c
 #pragma unroll
                 for (int c = 0; c < CT; ++c) acc[i][c] = mm(w[c], ah, acc[i][c]);
 #pragma unroll
-                for (int c = 0; c < CT; ++c) acc[i][c] = mm(w[c], al, acc[i][c]);
+                for (int c = 0; c < CT; ++c) mm_lo(w[c], al, i, c);
             }
         }
     }
     NLD_TS(TLC, 1);   // main loop done
+    if constexpr (TWO) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int j = 0; j < CT; ++j) acc[i][j] += accl[i][j];
+    }
 
     // The k groups meet in LDS (fixed order); group wk keeps tiles wk, wk + WK, ... of its column wavefront.
     if constexpr (WK > 1) {

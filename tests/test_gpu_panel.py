@@ -145,3 +145,29 @@ def test_narrowest_model(R, batch, k):
         e = run(R, t, batch, k, mode)
         log("hidden 32 rows %d %s: rel err %.2e" % (batch * k, mode, e))
         assert e <= TOL
+
+
+@pytest.mark.parametrize("shape_env", ["", "15,1"])
+def test_small_products_are_not_lost(R, monkeypatch, shape_env):
+    """At up to 16 rows the lo halves' products have a sum of their own.  One value in 32 is
+    (1 + 2^-7)^2 = (1 + 2^-6) + 2^-14 and the others are 1, against weights of 1: the hi sums are exact, and of one
+    wavefront's 128 lo products of 2^-14 the half that meets a hi sum above 2048 would round away, 1e-6 of the
+    result.  What is left is the rounding of 1/rms, the scaling and the sum: 4 * 2^-24, taken twice."""
+    shape = ModelShape(n_layers=1, hidden=4096, n_q_heads=1, n_kv_heads=1, head_dim=64, ffn=8, vocab=256, rms_eps=0.0)
+    h = shape.hidden
+    v = np.full(h, BF16_ONE, dtype=np.uint16)
+    v[::32] += 1   # the next bf16 value, 1 + 2^-7
+    zero = lambda o, i: np.zeros((o, i), dtype=np.uint16)   # noqa: E731
+    layer = {"attn_norm": v, "wq": zero(64, h), "wk": zero(64, h), "wv": zero(64, h), "wo": zero(h, 64), "ffn_norm": v,
+             "w_gate": zero(8, h), "w_up": zero(8, h), "w_down": zero(h, 8)}
+    src = ArraySource([layer], np.tile(v, (shape.vocab, 1)), np.full((shape.vocab, h), BF16_ONE, dtype=np.uint16), v)
+    if shape_env:
+        monkeypatch.setenv("NLD_PANEL_LM", shape_env)
+    model, cache = R.DeviceModel(shape, src), R.DeviceCache(shape, 1, 64)
+    ws = R.Workspace(model, 1, 8, 64)
+    logits, _ = R.block_forward(model, cache, ws, torch.zeros(1, 8, dtype=torch.int32, device="cuda"), R.VERIFY)
+    a = 1 + 2.0 ** -7
+    ref = h / 32 * (31 + a * a) / np.sqrt((31 + a * a) / 32)
+    e = np.max(np.abs(logits.cpu().numpy().astype(np.float64) / ref - 1))
+    log("small products: rel err %.2e" % e)
+    assert e <= 8 * 2.0 ** -24
