@@ -310,7 +310,9 @@ hipError_t launch_gemm_norm(int ks, int waves, int grid, const GemmArgs& a, hipS
 // split the reduction, each streaming its slice of the weights and of the split activations with one batch
 // in flight ahead of the MFMAs (two per weight operand).  No slices meet and rows past M are not read: 8.2 us
 // at 8 rows of the 8B shapes against 10.6 us for the panel GEMM, 8.0 against 11.0 at 16.  XK: the reduction
-// continues over a second source (the LoRA up-projection).
+// continues over a second source (the LoRA up-projection): 9.3 us with rank 128 at 16 rows of the 8B shapes.  The
+// zeros past the ends are written as values: a conditional between a named zero quad and a loaded one chooses an
+// address, and the quad then lives in private memory (13.5 us).
 // =====================================================================================
 // Operand and weight registers of one batch: U k-steps of CT column tiles.
 template <int CT, int U>
@@ -335,7 +337,6 @@ __global__ void __launch_bounds__(NW * 64) gemm_stream_kernel(GemmArgs a) {
     const uint4* wp = a.W + (size_t)t * a.ksteps * 64 + lane;
     const uint16_t* ap = a.A + (size_t)lane * 8;
     const bool aok = r < a.M;
-    const uint4 zero4 = {0u, 0u, 0u, 0u};
 
     // XK: the second source's k-steps (W2 against A2) go one to a wavefront (wavefront w takes step
     // w, then w + NW).  They are loaded before the main stream and multiplied after it, so the
@@ -348,9 +349,9 @@ __global__ void __launch_bounds__(NW * 64) gemm_stream_kernel(GemmArgs a) {
             const int s2 = wave + i * NW;
             const bool in = s2 < a.ksteps2;
             const uint16_t* ap2 = a.A2 + (size_t)s2 * 1024 + (size_t)lane * 8;
-            xw[i] = in ? a.W2[((size_t)t * a.ksteps2 + s2) * 64 + lane] : zero4;
-            xa[i] = in && aok ? *(const uint4*)ap2 : zero4;
-            xal[i] = in && aok ? *(const uint4*)(ap2 + SPLIT_LO) : zero4;
+            xw[i] = in ? a.W2[((size_t)t * a.ksteps2 + s2) * 64 + lane] : uint4{0u, 0u, 0u, 0u};
+            xa[i] = in && aok ? *(const uint4*)ap2 : uint4{0u, 0u, 0u, 0u};
+            xal[i] = in && aok ? *(const uint4*)(ap2 + SPLIT_LO) : uint4{0u, 0u, 0u, 0u};
         }
     }
 
@@ -369,9 +370,9 @@ __global__ void __launch_bounds__(NW * 64) gemm_stream_kernel(GemmArgs a) {
         for (int u = 0; u < U; ++u) {
             const int ss = s + u;
             const bool in = ss < s_end, ok = in && aok && ss * 32 + 8 * g < a.K;
-            buf.w[u][0] = in ? wp[(size_t)ss * 64] : zero4;
-            buf.x[u] = ok ? *(const uint4*)(ap + (size_t)ss * 1024) : zero4;
-            buf.xl[u] = ok ? *(const uint4*)(ap + (size_t)ss * 1024 + SPLIT_LO) : zero4;
+            buf.w[u][0] = in ? wp[(size_t)ss * 64] : uint4{0u, 0u, 0u, 0u};
+            buf.x[u] = ok ? *(const uint4*)(ap + (size_t)ss * 1024) : uint4{0u, 0u, 0u, 0u};
+            buf.xl[u] = ok ? *(const uint4*)(ap + (size_t)ss * 1024 + SPLIT_LO) : uint4{0u, 0u, 0u, 0u};
         }
     };
     auto compute = [&](const B& buf) __attribute__((always_inline)) {
