@@ -2009,6 +2009,96 @@ __device__ __forceinline__ float argmax_key_value(unsigned long long key) {
     return __uint_as_float((ord & 0x80000000u) ? (ord ^ 0x80000000u) : ~ord);
 }
 
+// max over the wavefront, in every lane: register moves within the rows of 16 lanes, then across them
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+    v = max(v, row_ror<8>(v));
+    v = max(v, row_ror<4>(v));
+    v = max(v, row_ror<2>(v));
+    v = max(v, row_ror<1>(v));
+    const auto a = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = max((uint32_t)a[0], (uint32_t)a[1]);
+    const auto b = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return max((uint32_t)b[0], (uint32_t)b[1]);
+}
+__device__ __forceinline__ float wave_max(float v) {
+    v = fmaxf(v, row_ror<8>(v));
+    v = fmaxf(v, row_ror<4>(v));
+    v = fmaxf(v, row_ror<2>(v));
+    return rows_max(fmaxf(v, row_ror<1>(v)));
+}
+__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long key) {
+    const uint32_t ord = (uint32_t)(key >> 32), top = wave_max_u32(ord);
+    return ((unsigned long long)top << 32) | wave_max_u32(ord == top ? (uint32_t)key : 0u);
+}
+
+// A row's LM-head partials, a lane taking every 64th.  The panel GEMM leaves one per column group, 792 for the 8B
+// vocabulary, where the normed GEMM leaves one per CU.  Eight loads a row are under way per lane, through a buffer
+// descriptor that ends with the row (past it: zeros, the empty key and an empty sum, without a branch or an address per
+// load), and the softmax sums take the maximum of a round first.  A finish runs once a pass, from a cold instruction
+// cache, so short code counts as much: sixteen loads ahead took 8.2 us at 32 rows.  One load and one merge after the
+// other the quadratic finish took 7.8 us and the ensemble 12.0 (8B vocabulary, chain length 7), now 4.9 and 8.1; the
+// finish of 32 rows took 6.6 us and now 6.1, of a denoising step 27.1 and now 14.6.
+constexpr int PARTS_AHEAD = 8;
+struct PartRow {
+    __amdgpu_buffer_rsrc_t rs;
+    // base uniform; on = false: an empty row
+    __device__ __forceinline__ PartRow(const void* base, int n, bool on) {
+        rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, on ? 8 * n : 0, 0x00027000);
+    }
+    __device__ __forceinline__ uint2 load(int p) const {
+        typedef uint32_t u32x2_b __attribute__((ext_vector_type(2)));
+        const u32x2_b v = __builtin_bit_cast(u32x2_b, __builtin_amdgcn_raw_buffer_load_b64(rs, 8 * p, 0, 0));
+        return uint2{v[0], v[1]};
+    }
+};
+
+// the argmax keys of rows m and m2 (m2 < 0: none, the empty key), in every lane of the wavefront
+__device__ __forceinline__ void row_keys(const FinishArgs& a, int m, int m2, int lane, unsigned long long (&best)[2]) {
+    const PartRow row[2] = {PartRow(a.part_keys + (size_t)m * a.n_parts, a.n_parts, true),
+                            PartRow(a.part_keys + (size_t)max(m2, 0) * a.n_parts, a.n_parts, m2 >= 0)};
+    best[0] = best[1] = 0ull;
+    for (int p0 = lane; p0 - lane < a.n_parts; p0 += 64 * PARTS_AHEAD) {
+        uint2 v[2][PARTS_AHEAD];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int u = 0; u < PARTS_AHEAD; ++u) v[q][u] = row[q].load(p0 + 64 * u);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int u = 0; u < PARTS_AHEAD; ++u)
+                best[q] = umax64(best[q], ((unsigned long long)v[q][u].y << 32) | v[q][u].x);
+    }
+    best[0] = wave_max_key(best[0]);
+    best[1] = wave_max_key(best[1]);
+}
+
+// the softmax statistics (max, sum of exp(z - max)) of row m, in every lane of the wavefront; empty partials (a maximum
+// of -inf, or past the row's end a sum of 0) take no part, as in lse_merge
+__device__ __forceinline__ float2 row_lse(const FinishArgs& a, int m, int lane) {
+    const PartRow row(a.part_lse + (size_t)m * a.n_parts, a.n_parts, true);
+    float2 st = float2{-INFINITY, 0.f};
+    for (int p0 = lane; p0 - lane < a.n_parts; p0 += 64 * PARTS_AHEAD) {
+        float2 v[PARTS_AHEAD];
+        float mx = -INFINITY, sum = 0.f;
+#pragma unroll
+        for (int u = 0; u < PARTS_AHEAD; ++u) {
+            const uint2 w = row.load(p0 + 64 * u);
+            v[u] = float2{__uint_as_float(w.x), __uint_as_float(w.y)};
+        }
+#pragma unroll
+        for (int u = 0; u < PARTS_AHEAD; ++u) {
+            if (v[u].y == 0.f) v[u].x = -INFINITY;
+            mx = fmaxf(mx, v[u].x);
+        }
+        mx = wave_max(mx);
+#pragma unroll
+        for (int u = 0; u < PARTS_AHEAD; ++u) sum += v[u].x != -INFINITY ? v[u].y * expf(v[u].x - mx) : 0.f;
+        st = lse_merge(st, float2{mx, wave_sum(sum)});
+    }
+    return st;
+}
+
 // Commit n more rows of sequence b.  Rows at or past max_len were never written (the QKV epilogue
 // skipped them and set DEV_CAPACITY), so the length stops at max_len: every row below it is valid.
 __device__ __forceinline__ void advance_length(const FinishArgs& a, int b, int n) {
@@ -2022,10 +2112,10 @@ __device__ __forceinline__ void advance_length(const FinishArgs& a, int b, int n
 }
 
 __global__ void __launch_bounds__(1024) finish_kernel(FinishArgs a) {
-    __shared__ int32_t am[64];
+    __shared__ int32_t am[64], in_s[64];
     __shared__ float cf[64];
     const int b = blockIdx.x, k = a.k_blk;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
     const bool denoise = a.finish == FINISH_DENOISE;
     if (a.finish == FINISH_REFRESH) {
         if (threadIdx.x != 0) return;
@@ -2036,75 +2126,88 @@ __global__ void __launch_bounds__(1024) finish_kernel(FinishArgs a) {
         advance_length(a, b, k - 1);
         return;
     }
-    for (int jr = wave; jr < k; jr += nw) {
-        const int m = b * k + jr;
-        unsigned long long best = 0ull;
-        float2 st = float2{-INFINITY, 0.f};   // softmax statistics (denoising only)
-        if (a.part_keys) {
-            const unsigned long long* pk = a.part_keys + (size_t)m * a.n_parts;
-            int p = lane;
-            for (; p + 192 < a.n_parts; p += 256)
-                best = umax64(umax64(best, pk[p]), umax64(umax64(pk[p + 64], pk[p + 128]), pk[p + 192]));
-            for (; p < a.n_parts; p += 64) best = umax64(best, pk[p]);
-            if (denoise)
-                for (int q = lane; q < a.n_parts; q += 64) st = lse_merge(st, a.part_lse[(size_t)m * a.n_parts + q]);
-        } else {
-            const float* lg = a.logits + (size_t)m * a.vocab;
-            const int excl = denoise ? a.mask_id : -1;
+    // the block (denoising) or the drafts to accept, read beside the partials: one thread reading them one by one at the
+    // end took longer than all the rest of a denoising finish
+    const int32_t* in = denoise ? a.block + (size_t)b * k : a.draft_in + (size_t)b * (k - 1);
+    if ((denoise || a.finish == FINISH_ACCEPT) && (int)threadIdx.x < (denoise ? k : k - 1)) in_s[threadIdx.x] = in[threadIdx.x];
+    auto row_done = [&](int jr, unsigned long long best, float2 st) __attribute__((always_inline)) {
+        if (lane != 0) return;
+        const int m = b * k + jr, idx = argmax_key_index(best);
+        am[jr] = idx;
+        if (a.argmax_out) a.argmax_out[m] = idx;
+        if (denoise) {
+            // probability of the argmax token: exp(z_best - max) / sum (the max is z_best)
+            const float c = expf(argmax_key_value(best) - st.x) / st.y;
+            cf[jr] = c;
+            if (a.conf_out) a.conf_out[m] = c;
+        }
+    };
+    if (a.part_keys) {
+        for (int jr = wave; jr < k; jr += 2 * nw) {   // two rows of a wavefront at a time
+            const int m = b * k + jr, m2 = jr + nw < k ? m + nw : -1;
+            unsigned long long best[2];
+            row_keys(a, m, m2, lane, best);
+#pragma unroll 1
+            for (int q = 0; q < (m2 >= 0 ? 2 : 1); ++q) {
+                float2 st = float2{-INFINITY, 0.f};
+                if (denoise) st = row_lse(a, q ? m2 : m, lane);
+                row_done(q ? jr + nw : jr, q ? best[1] : best[0], st);
+            }
+        }
+    } else {   // from given logits
+        const int excl = denoise ? a.mask_id : -1;
+        for (int jr = wave; jr < k; jr += nw) {
+            const float* lg = a.logits + (size_t)(b * k + jr) * a.vocab;
+            unsigned long long best = 0ull;
+            float2 st = float2{-INFINITY, 0.f};   // softmax statistics (denoising only)
             for (int n = lane; n < a.vocab; n += 64) {
                 if (n == excl) continue;
                 const float v = lg[n];
                 best = umax64(best, argmax_key(v, (uint32_t)n));
                 if (denoise) st = lse_merge(st, float2{v, 1.f});
             }
-        }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) best = umax64(best, __shfl_xor(best, off));
-        if (denoise) {
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                const float2 o = float2{__shfl_xor(st.x, off), __shfl_xor(st.y, off)};
-                st = lse_merge(st, o);
-            }
-        }
-        if (lane == 0) {
-            const int idx = argmax_key_index(best);
-            am[jr] = idx;
-            if (a.argmax_out) a.argmax_out[m] = idx;
+            best = wave_max_key(best);
             if (denoise) {
-                // probability of the argmax token: exp(z_best - max) / sum (the max is z_best)
-                const float c = expf(argmax_key_value(best) - st.x) / st.y;
-                cf[jr] = c;
-                if (a.conf_out) a.conf_out[m] = c;
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) st = lse_merge(st, float2{__shfl_xor(st.x, off), __shfl_xor(st.y, off)});
             }
+            row_done(jr, best, st);
         }
     }
     __syncthreads();
-    if (threadIdx.x != 0 || a.finish == FINISH_NONE) return;
+    if (threadIdx.x >= 64 || a.finish == FINISH_NONE) return;
+    // the decision: one wavefront, a lane per row (k <= 64)
+    const int j = lane;
     if (a.finish == FINISH_DRAFT) {
-        for (int jj = 1; jj < k; ++jj) a.draft_out[(size_t)b * (k - 1) + jj - 1] = am[jj];
+        if (j >= 1 && j < k) a.draft_out[(size_t)b * (k - 1) + j - 1] = am[j];
     } else if (denoise) {
-        int32_t* blk = a.block + (size_t)b * k;
-        int n_mask = 0, n_above = 0, top = -1;
-        for (int j = 1; j < k; ++j) {
-            if (blk[j] != a.mask_id) continue;
-            ++n_mask;
-            if (cf[j] > a.threshold) ++n_above;
-            if (top < 0 || cf[j] > cf[top]) top = j;   // first of the most confident
+        const bool masked = j >= 1 && j < k && in_s[j] == a.mask_id;
+        const float c = masked ? cf[j] : 0.f;
+        const unsigned long long left = __ballot(masked), above = __ballot(masked && c > a.threshold);
+        int top = -1;   // first of the most confident
+        float c_top = 0.f;
+        for (unsigned long long w = above ? 0ull : left; w; w &= w - 1) {
+            const int i = __ffsll((long long)w) - 1;
+            const float ci = __shfl(c, i);
+            if (top < 0 || ci > c_top) {
+                top = i;
+                c_top = ci;
+            }
         }
-        for (int j = 1; j < k; ++j)
-            if (blk[j] == a.mask_id && (n_above > 0 ? cf[j] > a.threshold : j == top)) blk[j] = am[j];
-        const int n_commit = n_above > 0 ? n_above : (n_mask > 0 ? 1 : 0);
-        a.n_committed[b] = n_commit;
-        a.n_masked[b] = n_mask - n_commit;
+        if (masked && (above ? c > a.threshold : j == top)) a.block[(size_t)b * k + j] = am[j];
+        if (j == 0) {
+            const int n_mask = __popcll(left), n_commit = above ? __popcll(above) : (n_mask > 0 ? 1 : 0);
+            a.n_committed[b] = n_commit;
+            a.n_masked[b] = n_mask - n_commit;
+        }
     } else {
-        const int32_t* dr = a.draft_in + (size_t)b * (k - 1);
-        int L = 0;
-        while (L < k - 1 && dr[L] == am[L]) ++L;
-        a.accept_len[b] = L;
-        for (int i = 0; i < k; ++i) a.committed[(size_t)b * k + i] = i < L ? dr[i] : (i == L ? am[L] : -1);
-        a.next_anchor[b] = am[L];
-        if (a.lengths) advance_length(a, b, L + 1);
+        const int L = __ffsll((long long)~__ballot(j < k - 1 && in_s[j] == am[j])) - 1;   // at most k - 1
+        if (j < k) a.committed[(size_t)b * k + j] = j < L ? in_s[j] : (j == L ? am[j] : -1);
+        if (j == 0) {
+            a.accept_len[b] = L;
+            a.next_anchor[b] = am[L];
+            if (a.lengths) advance_length(a, b, L + 1);
+        }
     }
 }
 
@@ -2122,26 +2225,6 @@ hipError_t launch_finish(const FinishArgs& a, hipStream_t s) {
 // lambda * softmax(AR) + (1 - lambda) * softmax(diffusion).  Acceptance is Mode 3's; the
 // next speculative tokens are the argmax of masks 2..qk of group L.
 // =====================================================================================
-// argmax of row m from the LM head's per-workgroup keys, in every lane of the wavefront
-__device__ __forceinline__ int32_t row_argmax(const FinishArgs& a, int m, int lane) {
-    const unsigned long long* pk = a.part_keys + (size_t)m * a.n_parts;
-    unsigned long long best = 0ull;
-    for (int p = lane; p < a.n_parts; p += 64) best = umax64(best, pk[p]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) best = umax64(best, __shfl_xor(best, off));
-    return argmax_key_index(best);
-}
-
-// softmax statistics (max, sum of exp(z - max)) of row m, merged over the LM head's
-// workgroups, in every lane of the wavefront
-__device__ __forceinline__ float2 row_lse(const FinishArgs& a, int m, int lane) {
-    float2 st = float2{-INFINITY, 0.f};
-    for (int p = lane; p < a.n_parts; p += 64) st = lse_merge(st, a.part_lse[(size_t)m * a.n_parts + p]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) st = lse_merge(st, float2{__shfl_xor(st.x, off), __shfl_xor(st.y, off)});
-    return st;
-}
-
 // Workgroup (sequence b and position i, vocabulary chunk ch): the argmax key over the chunk
 // of lambda * exp(a_n - A) / SA + (1 - lambda) * exp(d_n - D) / SD (lowest index on ties),
 // into ens_keys[(b * quad_k + i) * ens_chunks + ch].  Each thread has eight columns of both
@@ -2151,7 +2234,7 @@ __global__ void __launch_bounds__(512) quad_ensemble_kernel(FinishArgs a) {
     __shared__ unsigned long long key_s[8];
     const int qk = a.quad_k, R = a.k_blk, V = a.vocab;
     const int bi = blockIdx.x, b = bi / qk, i = bi % qk, ch = blockIdx.y;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
     if (wave < 2) {
         const float2 st = row_lse(a, b * R + (wave == 0 ? i : qk + i * qk), lane);
         if (lane == 0) st_s[wave] = st;
@@ -2196,7 +2279,7 @@ __global__ void __launch_bounds__(1024) quad_finish_kernel(FinishArgs a) {
     __shared__ int32_t v_s[64];
     __shared__ int L_s;
     const int b = blockIdx.x, qk = a.quad_k, R = a.k_blk;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
     for (int i = wave; i < qk; i += nw) {
         int32_t v;
         if (a.lambda > 0.0f && a.lambda < 1.0f) {   // the ensemble kernel's per-chunk keys
@@ -2206,7 +2289,9 @@ __global__ void __launch_bounds__(1024) quad_finish_kernel(FinishArgs a) {
             for (int off = 32; off >= 1; off >>= 1) best = umax64(best, __shfl_xor(best, off));
             v = argmax_key_index(best);
         } else {
-            v = row_argmax(a, b * R + (a.lambda >= 1.0f ? i : qk + i * qk), lane);
+            unsigned long long best[2];
+            row_keys(a, b * R + (a.lambda >= 1.0f ? i : qk + i * qk), -1, lane, best);
+            v = argmax_key_index(best[0]);
         }
         if (lane == 0) v_s[i] = v;
     }
@@ -2224,8 +2309,9 @@ __global__ void __launch_bounds__(1024) quad_finish_kernel(FinishArgs a) {
     __syncthreads();
     const int L = L_s;
     for (int r = 2 + wave; r <= qk; r += nw) {
-        const int32_t v = row_argmax(a, b * R + qk + L * qk + r - 1, lane);
-        if (lane == 0) a.draft_out[(size_t)b * (qk - 1) + r - 2] = v;
+        unsigned long long best[2];
+        row_keys(a, b * R + qk + L * qk + r - 1, -1, lane, best);
+        if (lane == 0) a.draft_out[(size_t)b * (qk - 1) + r - 2] = argmax_key_index(best[0]);
     }
 }
 

@@ -17,7 +17,7 @@ import torch
 
 import synth
 from oracle import nld_oracle as O
-from synth.workloads import LazyWeights, WORKLOADS, prefix_kv, tokens as synth_tokens
+from synth.workloads import LazyWeights, ModelShape, WORKLOADS, prefix_kv, tokens as synth_tokens
 
 from gpu_common import decision_near_tie, log, log_conf_bound, own_commit, rel_err
 
@@ -207,7 +207,7 @@ def layer8b2(R):
 @pytest.mark.parametrize("batch", [1, 2])
 def test_8b_layer_denoising_and_refresh(R, layer8b2, batch):
     """One 8B-shaped layer + the 151936-token LM head, k=16: two denoising steps and the refresh.  Batch 1
-    runs the LM head on the normed multi-tile kernel, batch 2 (32 rows) on the streamed kernel."""
+    runs the LM head on the normed multi-tile kernel, batch 2 (32 rows) on the panel GEMM."""
     t = layer8b2
     shape, k, P = t["shape"], 16, t["P"]
     mask = shape.mask_token_id
@@ -235,4 +235,25 @@ def test_8b_layer_denoising_and_refresh(R, layer8b2, batch):
     kg, vg = cache.read_kv(0, P, P + k - 1)
     assert rel_err(O.bf16_bits_to_float(kg), okv.k[0][:, :, P:P + k - 1]) < TOL
     assert rel_err(O.bf16_bits_to_float(vg), okv.v[0][:, :, P:P + k - 1]) < TOL
+    assert R.read_device_status(ws) == 0
+
+
+@pytest.mark.parametrize("vocab,k", [(15, 8), (1000, 24), (16400, 64), (70000, 32)])
+def test_finish_over_any_number_of_partials(R, monkeypatch, vocab, k):
+    """The finish reads a row's LM-head partials sixteen loads at a time: 1 to 1094 of them (column groups of 64), with
+    remainders.  Confidences and commit of a denoising step and the drafts of a draft pass, against the device's own
+    logits."""
+    shape = ModelShape(n_layers=1, hidden=128, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=96, vocab=vocab)
+    monkeypatch.setenv("NLD_PANEL_LM", "%d,1" % (14 if k <= 16 else 1 if k <= 32 else 6))
+    model, cache = R.DeviceModel(shape, LazyWeights(shape, 31)), R.DeviceCache(shape, 1, 128)
+    ws, mask = R.Workspace(model, 1, k, 128), shape.mask_token_id
+    before = np.full((1, k), mask, dtype=np.int32)
+    before[0, 0] = 3
+    block = torch.from_numpy(before).cuda()
+    out = R.denoise_step(model, cache, ws, block, 0.0, want_logits=True)
+    logits, conf = out["logits"].cpu().numpy(), out["confidence"].cpu().numpy()
+    np.testing.assert_allclose(conf, O.top1_confidence(O.denoising_logits(logits, mask)), rtol=CONF_SELF_RTOL)
+    assert np.array_equal(block.cpu().numpy(), own_commit(before, logits, conf, 0.0, mask)[0])
+    drafts, logits = R.draft(model, cache, ws, torch.from_numpy(before[:, 0].copy()).cuda(), k, want_logits=True)
+    assert np.array_equal(drafts.cpu().numpy(), np.argmax(logits.cpu().numpy(), axis=-1)[:, 1:])
     assert R.read_device_status(ws) == 0

@@ -10,7 +10,7 @@ import pytest
 import torch
 
 from oracle import nld_oracle as O
-from synth.workloads import LazyWeights, WORKLOADS, tokens as synth_tokens, prefix_kv
+from synth.workloads import LazyWeights, ModelShape, WORKLOADS, tokens as synth_tokens, prefix_kv
 
 from gpu_common import log, rel_err
 
@@ -205,4 +205,21 @@ def test_8b_layer_quad_step(R, layer8b, batch, lam):
         kg, vg = cache.read_kv(0, Pb, Pb + k)
         assert rel_err(O.bf16_bits_to_float(kg[b:b + 1]), nk[0][b:b + 1, :, :k]) < TOL
         assert rel_err(O.bf16_bits_to_float(vg[b:b + 1]), nv[0][b:b + 1, :, :k]) < TOL
+    assert R.read_device_status(ws) == 0
+
+
+@pytest.mark.parametrize("vocab,lam", [(1000, 0.5), (70000, 0.5), (70000, 1.0), (70000, 0.0)])
+def test_quad_finish_over_any_number_of_partials(R, monkeypatch, vocab, lam):
+    """The verifier, the ensemble and the next speculative tokens from 16 to 1094 LM-head partials per row (column
+    groups of 64), against the rule on the device's own logits."""
+    k = 7
+    shape = ModelShape(n_layers=1, hidden=128, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=96, vocab=vocab)
+    monkeypatch.setenv("NLD_PANEL_LM", "9,1")
+    model, cache = R.DeviceModel(shape, LazyWeights(shape, 33)), R.DeviceCache(shape, 2, 128)
+    ws = R.QuadWorkspace(model, 2, k, 128)
+    anchor = synth_tokens(shape, 33, "quad.parts.anchor", (2,))
+    spec = synth_tokens(shape, 33, "quad.parts.spec", (2, k - 1))
+    res = R.quad_step(model, cache, ws, torch.from_numpy(anchor).cuda(), torch.from_numpy(spec).cuda(), k, lam=lam,
+                      want_logits=True)
+    check_step(res, res["logits"].cpu().numpy(), spec, k, lam, [0, 0], cache)
     assert R.read_device_status(ws) == 0
