@@ -398,11 +398,15 @@ PanelPlan plan_panel(int kind, int M, int n_tiles, int K, const Layout& L) {
     return best;
 }
 
+int panel_groups(const PanelPlan& p, int n_tiles) {
+    const PanelShape sh = gemm_panel_shape(p.shape);
+    return cdiv(n_tiles, sh.wc * sh.ct);
+}
+
 // groups (optional): column groups, the LM head's argmax partials and a residual projection's sums of
 // squares per row
 hipError_t panel_gemm(int epi, const PanelPlan& p, GemmArgs& g, void* ws, const Layout& L, hipStream_t s, int* groups) {
-    const PanelShape sh = gemm_panel_shape(p.shape);
-    g.n_parts = cdiv(g.n_tiles, sh.wc * sh.ct);
+    g.n_parts = panel_groups(p, g.n_tiles);
     if (groups) *groups = g.n_parts;
     return launch_gemm_panel(epi, p.shape, g, p.ksplit, at<float>(ws, L.part), at<unsigned>(ws, L.tile_ctr) + L.ctr0, s);
 }
@@ -419,19 +423,23 @@ hipError_t resid_gemm(int kind, const PanelPlan* plans, GemmArgs& g, void* ws, c
     return panel_gemm(EPI_RESID, plans[kind], g, ws, L, s, n_ss);
 }
 
-// One projection whose operand is RMSNorm(x) (QKV, gate/up, LM head): the panel GEMM, or, for the LM head of
-// up to 16 rows with at least four column tiles per CU (both sides measured at that kernel; 64 tiles: 13.1
-// against 5.7 us), the normed multi-tile kernel where it divides the reduction.  Both read the split operand and the row statistics the producer of x wrote.
-hipError_t normed_gemm(int kind, int epi, const PanelPlan* plans, GemmArgs g, void* ws, const Layout& L, hipStream_t s,
-                       int* parts_out) {
+// The LM head of up to 16 rows with at least four column tiles per CU runs on the normed multi-tile kernel where that
+// divides the reduction (both sides measured at that kernel; 64 tiles: 13.1 against 5.7 us).
+bool lm_normed(int M, int n_tiles, int ksteps, int* ks, int* waves) {
+    return n_tiles >= 4 * device_cus() && plan_norm(M, ksteps, ks, waves);
+}
+
+// One projection whose operand is RMSNorm(x) (QKV, gate/up, LM head): the panel GEMM, or for the LM head the normed
+// kernel.  Both read the split operand and the row statistics the producer of x wrote.
+hipError_t normed_gemm(int kind, int epi, const PanelPlan* plans, GemmArgs g, void* ws, const Layout& L, hipStream_t s) {
     g.A = at<uint16_t>(ws, L.xg);
     g.part_ss = at<float>(ws, L.part_ss);
     int ks = 0, waves = 0;
-    if (kind == PROJ_LM && g.n_tiles >= 4 * device_cus() && plan_norm(g.M, g.ksteps, &ks, &waves)) {
-        g.n_parts = *parts_out = device_cus();   // tiles beyond the first one per workgroup are handed out dynamically
+    if (kind == PROJ_LM && lm_normed(g.M, g.n_tiles, g.ksteps, &ks, &waves)) {
+        g.n_parts = device_cus();   // tiles beyond the first one per workgroup are handed out dynamically
         return launch_gemm_norm(ks, waves, g.n_parts, g, s);
     }
-    return panel_gemm(epi, plans[kind], g, ws, L, s, parts_out);
+    return panel_gemm(epi, plans[kind], g, ws, L, s, nullptr);
 }
 
 nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int k, const PassIO& io, void* ws,
@@ -468,6 +476,15 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
     e.quad_k = io.quad_k;
     const uint32_t plain = plain_sites();
     e.plain = plain & SITE_NORM;
+    // The LM head's partials per row, and its argmax keys (the normed GEMM's are one per workgroup).  Its plan alone stands
+    // before the first launch, which the others need not hold up.
+    PanelPlan plans[N_PROJ];   // the same for every layer
+    plans[PROJ_LM] = plan_panel(PROJ_LM, M, L.lm_tiles, c.hidden, L);
+    int ks_lm = 0, waves_lm = 0;
+    const bool normed = lm_normed(M, L.lm_tiles, cdiv(c.hidden, 32), &ks_lm, &waves_lm);
+    const int parts = normed ? device_cus() : panel_groups(plans[PROJ_LM], L.lm_tiles);
+    const int n_keys = normed ? parts : std::min(parts, KEY_SLOTS);
+    e.keys = n_keys < parts && !io.kv_only ? at<unsigned long long>(ws, L.keys) : nullptr;
     for (int i = 0; i < c.head_dim / 2; ++i) e.inv_freq[i] = pow((double)c.rope_base, -2.0 * i / (double)c.head_dim);
     {
         TraceScope ts(NLD_TRACE_EMBED, s);
@@ -477,12 +494,10 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
     int n_ss = embed_sums(c.hidden);   // sums of squares per row in part_ss, as its latest producer wrote them
     const int ks_h = cdiv(c.hidden, 32), ks_q = cdiv(nq * D, 32), ks_f = cdiv(c.ffn, 32);
     const bool lora = io.mode == NLD_MODE_DRAFT && c.lora_rank > 0;
-    PanelPlan plans[N_PROJ];   // the same for every layer
     plans[PROJ_O] = plan_panel(PROJ_O, M, c.hidden / 16, nq * D, L);
     plans[PROJ_DOWN] = plan_panel(PROJ_DOWN, M, c.hidden / 16, c.ffn, L);
     plans[PROJ_QKV] = plan_panel(PROJ_QKV, M, (nq + 2 * nkv) * D / 16, c.hidden, L);
     plans[PROJ_GU] = plan_panel(PROJ_GU, M, cdiv(c.ffn, 8), c.hidden, L);
-    plans[PROJ_LM] = plan_panel(PROJ_LM, M, L.lm_tiles, c.hidden, L);
     if (lora) plans[PROJ_LORA] = plan_panel(PROJ_LORA, M, c.lora_rank / 16, nq * D, L);
     for (int l = 0; l < c.n_layers; ++l) {
         const nld_layer_weights& W = mdl->layers[l];
@@ -517,7 +532,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
         g.plain = plain & (SITE_Q | SITE_KV);
         {
             TraceScope ts(NLD_TRACE_QKV, s);
-            HIP_TRY(normed_gemm(PROJ_QKV, EPI_QKV, plans, g, ws, L, s, nullptr));
+            HIP_TRY(normed_gemm(PROJ_QKV, EPI_QKV, plans, g, ws, L, s));
         }
         if (io.kv_only && l == c.n_layers - 1) break;   // every layer's K/V rows are written
 
@@ -604,7 +619,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
         gu.plain = plain & SITE_ACT;
         {
             TraceScope ts(NLD_TRACE_GATE_UP, s);
-            HIP_TRY(normed_gemm(PROJ_GU, EPI_SWIGLU, plans, gu, ws, L, s, nullptr));
+            HIP_TRY(normed_gemm(PROJ_GU, EPI_SWIGLU, plans, gu, ws, L, s));
         }
 
         GemmArgs gd{};
@@ -654,20 +669,21 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
     gl.ksteps = ks_h;
     gl.logits = io.logits;
     gl.part_keys = at<unsigned long long>(ws, L.keys);
+    gl.n_keys = n_keys;
     gl.part_lse = (denoise || ensemble) ? at<float2>(ws, L.lse) : nullptr;
     gl.exclude_id = denoise ? c.mask_token_id : -1;
     gl.k_blk = k;
     gl.quad_k = io.quad_k;
     gl.ens_logits = ensemble ? at<float>(ws, L.ens_logits) : nullptr;
     gl.vocab = c.vocab;
-    int parts = 0;
     {
         TraceScope ts(NLD_TRACE_LM_HEAD, s);
-        HIP_TRY(normed_gemm(PROJ_LM, EPI_LMHEAD, plans, gl, ws, L, s, &parts));
+        HIP_TRY(normed_gemm(PROJ_LM, EPI_LMHEAD, plans, gl, ws, L, s));
     }
 
     fa.part_keys = at<unsigned long long>(ws, L.keys);
     fa.part_lse = at<float2>(ws, L.lse);
+    fa.n_keys = n_keys;
     fa.n_parts = parts;
     fa.vocab = c.vocab;
     fa.argmax_out = io.argmax_out;

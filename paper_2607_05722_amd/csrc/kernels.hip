@@ -280,7 +280,7 @@ __global__ void __launch_bounds__(KS >= 16 ? 512 : 1024) gemm_norm_kernel(GemmAr
     if ((int)threadIdx.x < a.M && threadIdx.x < 16) {
         unsigned long long best = 0ull;
         for (int w = 0; w < NW; ++w) best = umax64(best, key_s[w][threadIdx.x]);
-        a.part_keys[(size_t)threadIdx.x * a.n_parts + blockIdx.x] = best;
+        a.part_keys[(size_t)threadIdx.x * a.n_keys + blockIdx.x] = best;
         if (a.part_lse) {
             float2 st = float2{-INFINITY, 0.f};
             for (int w = 0; w < NW; ++w) st = lse_merge(st, lse_s[w][threadIdx.x]);
@@ -1138,7 +1138,9 @@ gemm_panel_kernel(GemmArgs a, int R, int C, int ksplit, float* part, unsigned* c
                     best = umax64(best, key_s[w][threadIdx.x]);
                     if (a.part_lse) st = lse_merge(st, lse_s[w][threadIdx.x]);
                 }
-                a.part_keys[(size_t)m * a.n_parts + cg] = best;
+                if (a.n_keys < a.n_parts)
+                    __hip_atomic_fetch_max(a.part_keys + (size_t)m * a.n_keys + cg % a.n_keys, best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                else a.part_keys[(size_t)m * a.n_keys + cg] = best;
                 if (a.part_lse) a.part_lse[(size_t)m * a.n_parts + cg] = st;
             }
         }
@@ -1929,6 +1931,8 @@ __global__ void __launch_bounds__(256) embed_kernel(EmbedArgs a) {
     const int b = m / a.k_blk, j = m % a.k_blk;
     if (m == 0)
         for (int i = threadIdx.x; i < a.n_tile_ctr; i += blockDim.x) a.tile_ctr[i] = 0u;
+    if (a.keys)
+        for (int i = threadIdx.x; i < KEY_SLOTS; i += blockDim.x) a.keys[(size_t)m * KEY_SLOTS + i] = 0ull;
     // RoPE table of this row (used by every layer's QKV epilogue): angle pos * theta_i
     // reduced to [-pi, pi] and evaluated in fp64, stored as fp32 (cos, sin).
     if ((int)threadIdx.x < a.head_dim / 2) {
@@ -2054,10 +2058,10 @@ struct PartRow {
 
 // the argmax keys of rows m and m2 (m2 < 0: none, the empty key), in every lane of the wavefront
 __device__ __forceinline__ void row_keys(const FinishArgs& a, int m, int m2, int lane, unsigned long long (&best)[2]) {
-    const PartRow row[2] = {PartRow(a.part_keys + (size_t)m * a.n_parts, a.n_parts, true),
-                            PartRow(a.part_keys + (size_t)max(m2, 0) * a.n_parts, a.n_parts, m2 >= 0)};
+    const PartRow row[2] = {PartRow(a.part_keys + (size_t)m * a.n_keys, a.n_keys, true),
+                            PartRow(a.part_keys + (size_t)max(m2, 0) * a.n_keys, a.n_keys, m2 >= 0)};
     best[0] = best[1] = 0ull;
-    for (int p0 = lane; p0 - lane < a.n_parts; p0 += 64 * PARTS_AHEAD) {
+    for (int p0 = lane; p0 - lane < a.n_keys; p0 += 64 * PARTS_AHEAD) {
         uint2 v[2][PARTS_AHEAD];
 #pragma unroll
         for (int q = 0; q < 2; ++q)

@@ -149,7 +149,10 @@ struct GemmArgs {
     int ffn;
     // EPI_LMHEAD
     float* logits;                   // optional f32 [M][vocab]
-    unsigned long long* part_keys;   // [M][n_parts]: one argmax key per row per workgroup
+    // [M][n_keys] argmax keys: one per row per workgroup (n_keys = n_parts), or, of more than KEY_SLOTS workgroups,
+    // KEY_SLOTS that they share by atomic maximum (the same whatever the order), zeroed by the embedding kernel
+    unsigned long long* part_keys;
+    int n_keys;
     float2* part_lse;                // optional [M][n_parts]: (max, sum of exp(z - max)) per row per workgroup
     int exclude_id;                  // column left out of the argmax and the sums (-1: none)
     int n_parts;
@@ -201,6 +204,10 @@ struct AttnArgs {
 // than one per 16 columns, which is what the buffer has room for.  (A thread takes 16 columns, so wavefronts past that
 // count have none.)
 constexpr int EMBED_WAVES = 4;
+// Argmax keys per row that the finish reads at most: as many as one workgroup per CU leaves.  One workgroup reads all rows
+// of a sequence from beyond its L2, at about 70 GB/s: with 792 keys a row the finish of 32 rows takes 6.1 us and of 64 rows
+// 10.4, with 256 it takes 4.6 and 6.4.  The LM head takes the same time (238.3 us at 32 rows, 237.5 with plain stores).
+constexpr int KEY_SLOTS = 256;
 constexpr int embed_sums(int hidden) { return hidden / 16 < EMBED_WAVES ? hidden / 16 : EMBED_WAVES; }
 
 struct EmbedArgs {
@@ -215,6 +222,7 @@ struct EmbedArgs {
     uint16_t* xg;           // split x * gain, split_index with hidden/32 steps
     float* part_ss;         // [M][embed_sums(hidden)]
     uint32_t* status;
+    unsigned long long* keys;   // optional [M][KEY_SLOTS]: zeroed here
     unsigned* tile_ctr;     // [n_tile_ctr] dynamic tile counters of this pass's GEMMs, zeroed here
     int n_tile_ctr;
     // RoPE table: rope[m][i] = (cos, sin) of (P_b + j) * inv_freq[i], i < head_dim/2
@@ -231,7 +239,8 @@ enum FinishKind {
 };
 
 struct FinishArgs {
-    const unsigned long long* part_keys;  // [M][n_parts] (or NULL: reduce `logits`)
+    const unsigned long long* part_keys;  // [M][n_keys] (or NULL: reduce `logits`)
+    int n_keys;
     int n_parts;
     const float* logits;                  // [M][vocab]
     int vocab;
