@@ -91,7 +91,9 @@ def test_long_items_lose_nothing(R, monkeypatch, D, k):
     that lags behind the maximum the long items are further off than the short ones, in whose only stage it is
     the maximum.)  One layer without an FFN whose output is the attention's, rows that a few keys decide.  The ratio
     of the two errors measured 1.00 to 1.013 over the four shapes, and 1.035 to 1.045 with a reference that lags by up
-    to 2^8: the line is between.  The bound on the error itself is that of the file."""
+    to 2^8: the line is between.  Items of 384 keys, whose reference follows every stage's own maximum, measured 0.996 to
+    1.0012, and 1.004 to 1.011 in three of the shapes with the running maximum alone.  The bound on the error itself is
+    that of the file."""
     s = ModelShape(n_layers=1, hidden=128, n_q_heads=4, n_kv_heads=1, head_dim=D, ffn=8, vocab=160, rms_eps=0.0)
     rng = np.random.default_rng(5)
 
@@ -113,11 +115,12 @@ def test_long_items_lose_nothing(R, monkeypatch, D, k):
     model, tok = R.DeviceModel(s, src), synth_tokens(s, 21, "attn.long%d" % k, (batch, k))
     ref, _, _ = O.block_forward(O.OracleWeights(s, src, np.float64), okv, tok, O.VERIFY)
     e = {}
-    for keys in (64, 1024):
+    for keys in (64, 384, 1024):
         monkeypatch.setenv("NLD_ATTN_ITEM_KEYS", str(keys))
         ws = R.Workspace(model, batch, k, cap)
         g = R.block_forward(model, cache, ws, torch.from_numpy(tok).cuda(), R.VERIFY)[0].cpu().numpy().astype(np.float64)
         assert R.read_device_status(ws) == 0
         e[keys] = np.linalg.norm(g - ref) / np.linalg.norm(ref)
-    log("attention D %d k %d: error %.3e with items of 64 keys, %.3e with items of 1024" % (D, k, e[64], e[1024]))
+    log("attention D %d k %d: error %.3e with items of 64 keys, %.3e of 384, %.3e of 1024" % (D, k, e[64], e[384], e[1024]))
     assert e[1024] <= 1.025 * e[64] and e[1024] <= TOL
+    assert e[384] <= 1.003 * e[64]
