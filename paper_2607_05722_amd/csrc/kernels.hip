@@ -1105,9 +1105,9 @@ gemm_panel_kernel(GemmArgs a, int R, int C, int ksplit, float* part, unsigned* c
                 first = min(first, row_ror<2>(first));
                 first = min(first, row_ror<1>(first));
                 if (a.part_lse) {
-                    float mx = -INFINITY;
+                    float mx = ord[0] != INT32_MIN ? y[0] : -INFINITY;   // NaN, and not the empty set's -inf, where all are NaN
 #pragma unroll
-                    for (int c = 0; c < CT; ++c) mx = fmaxf(mx, ord[c] != INT32_MIN ? y[c] : -INFINITY);
+                    for (int c = 1; c < CT; ++c) mx = fmaxf(mx, ord[c] != INT32_MIN ? y[c] : -INFINITY);
                     mx = fmaxf(mx, row_ror<8>(mx));
                     mx = fmaxf(mx, row_ror<4>(mx));
                     mx = fmaxf(mx, row_ror<2>(mx));

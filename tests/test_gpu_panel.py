@@ -118,17 +118,20 @@ def test_swiglu_of_large_gates(R, batch, k, large):
             assert run(R, t, batch, k, mode) <= TOL   # false for a NaN
 
 
-@pytest.mark.parametrize("k", [8, 32, 64])
+@pytest.mark.parametrize("k", [8, 32, 64, 100])
 @pytest.mark.parametrize("bits", [0x7FC0, 0xFFC0])
-def test_nan_logit_reaches_the_confidence(R, k, bits):
-    """A NaN logit of either sign is part of its row's softmax sum: the confidence is NaN."""
+@pytest.mark.parametrize("columns", [slice(17, 18), slice(0, 48)])
+def test_nan_logit_reaches_the_confidence(R, k, bits, columns):
+    """A NaN logit of either sign is part of its row's softmax sum: the confidence is NaN, also where every column that
+    a wavefront takes (16, 32 or 48 of them) is NaN."""
     shape = ModelShape(n_layers=1, hidden=128, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=96, vocab=200)
     src = LazyWeights(shape, 5)
     lm = np.array(src.lm_head, copy=True)
-    lm[17] = bits
+    lm[columns] = bits
     model = R.DeviceModel(shape, ArraySource([src.layer(0)], src.embed, lm, src.final_norm))
-    cache, ws = R.DeviceCache(shape, 1, 128), R.Workspace(model, 1, k, 128)
-    block = torch.from_numpy(synth_tokens(shape, 5, "panel.nan", (1, k))).cuda()
+    batch, k = (2, 50) if k > 64 else (1, k)
+    cache, ws = R.DeviceCache(shape, batch, 128), R.Workspace(model, batch, k, 128)
+    block = torch.from_numpy(synth_tokens(shape, 5, "panel.nan", (batch, k))).cuda()
     block[:, 1:] = shape.mask_token_id
     out = R.denoise_step(model, cache, ws, block, 0.5)
     assert torch.isnan(out["confidence"]).all()
