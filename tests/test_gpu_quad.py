@@ -178,8 +178,8 @@ def layer8b(R):
 
 @pytest.mark.parametrize("batch,lam", [(1, 1.0), (1, 0.5), (2, 0.5)])
 def test_8b_layer_quad_step(R, layer8b, batch, lam):
-    """One 8B-shaped layer + LM head, k = 7 (56 block rows per sequence: the streamed GEMMs at batch 1,
-    the tiled GEMMs at batch 2 with ragged prefixes): logits, chain K/V rows and decisions."""
+    """One 8B-shaped layer + LM head, k = 7 (56 block rows per sequence: four row tiles at batch 1,
+    eight at batch 2 with ragged prefixes): logits, chain K/V rows and decisions."""
     t = layer8b
     shape, k, P = t["shape"], 7, t["P"]
     lengths = np.array([P, 1111][:batch])
