@@ -114,11 +114,12 @@ bool nld::trace_launch_events(hipEvent_t* start, hipEvent_t* stop) {
 namespace {
 
 // ---------------------------------------------------------------- workspace layout
+constexpr int CTR0 = 1;   // tile counter 0 hands out the LM head's tiles
 struct Layout {
     int M, Mpad, units, n_splits, chunk, row_tiles, attn_kh, attn_waves, attn_z, n_parts, rows_pad, lm_tiles, lm_parts;
     bool attn_items;         // length-aware attention work (batches)
     int n_tile_ctr;          // tile counters in all, zeroed by the embedding kernel at the start of a pass
-    int n_ctr, ctr0;         // K slices: counters (one per group of tiles) from tile counter ctr0
+    int n_ctr;               // K slices: counters (one per group of tiles) from tile counter CTR0
     size_t part_floats;      // K slices: room for their partials
     size_t status, x, xg, part_ss, q, o, act, keys, lse, rope, po, pml, blk_k, blk_v, tile_ctr, part, lora_t, drafts,
         ens_logits, ens_v, total;
@@ -184,24 +185,27 @@ Layout make_layout(const nld_config& c, int batch, int k, int max_len, int quad_
     L.keys = take(8 * L.Mpad * (size_t)L.lm_parts);
     L.lse = take(8 * L.Mpad * (size_t)L.lm_parts);   // softmax statistics per argmax partial (denoising)
     L.rope = take(8 * L.Mpad * (size_t)(c.head_dim / 2));
-    // K slices of a projection: counters (one per group of tiles) and room for the slices' partials.  Up to
-    // 64 rows the groups are at least one column tile, above 128 rows x 8 column tiles.
-    const int H32 = cdiv((int)H, 32);
+    // K slices of a projection: counters (one per group of tiles) and room for the slices' partials.  Up to 16 rows
+    // the split-K GEMM's groups hold at least two column tiles.  The panel GEMM takes slices only where groups x slices is
+    // at most two per CU, so from 17 to 64 rows it needs no more than a counter per CU and the partials of two groups
+    // of 12 column tiles per CU, and less for a small model.  Above, a group is 128 rows x 8 column tiles.
     const int sk_tiles = std::max((int)H / 16, (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim / 16);
-    const int wide = std::max(std::max(L.lm_tiles, cdiv(c.ffn, 8)), sk_tiles);
-    const int sk_groups = cdiv(sk_tiles, 2);   // the split-K GEMM's column groups hold at least two tiles
-    L.ctr0 = 2 * c.n_layers + 1;               // after the normed GEMM's hand-out counters
-    size_t nk_floats = 0;
+    const int sk_groups = cdiv(sk_tiles, 2);
     if (L.M <= 64) {
-        const size_t sk_floats = (size_t)(2 * sk_groups + 4) * 16 * (L.M <= 32 ? 32 : 64) * SPLITK_MAX;
-        if (L.M > 16) nk_floats = (size_t)wide * cdiv(H32, L.M > 32 ? 32 : 64) * (L.M > 32 ? 4 : 2) * 256;
-        L.n_ctr = sk_groups + (L.M > 16 ? wide : 0);
-        L.part_floats = nk_floats + sk_floats;
+        const int rt = L.M <= 32 ? 2 : 4;
+        L.n_ctr = sk_groups;
+        L.part_floats = (size_t)(2 * sk_groups + 4) * 256 * rt * SPLITK_MAX;
+        if (L.M > 16) {
+            const int wide = std::max(std::max(L.lm_tiles, cdiv(c.ffn, 8)), sk_tiles);
+            L.n_ctr = std::min(L.n_ctr + wide, device_cus());
+            L.part_floats = std::min(L.part_floats + (size_t)wide * cdiv((int)H, rt == 2 ? 2048 : 1024) * rt * 256,
+                                     (size_t)2 * device_cus() * 256 * rt * 12);
+        }
     } else {
         L.n_ctr = cdiv(L.M, 128) * cdiv(std::max(sk_tiles, cdiv(c.ffn, 8)), 8);
         L.part_floats = (size_t)4 * device_cus() * 16384;
     }
-    L.n_tile_ctr = L.ctr0 + L.n_ctr;
+    L.n_tile_ctr = CTR0 + L.n_ctr;
     L.tile_ctr = take(4 * (size_t)L.n_tile_ctr);
     L.part = take(4 * L.part_floats);
     L.po = take(4 * (size_t)L.units * room * c.head_dim);
@@ -353,7 +357,7 @@ bool plan_splitk(int kind, const GemmArgs& g, const Layout& L, int* ct, int* ksp
 // 8B shapes (8, 16, 32, 64, 100, 512 rows) and the 14B ones (256) the picked plan is within 4% of the fastest one, for the LM
 // head of a short vocabulary within 10%.
 // NLD_PANEL_<O|DOWN|QKV|GU|LM|LORA> = "shape,slices" overrides a plan; NLD_TILE_KSPLIT_<O|DOWN|QKV|GU> (more
-// than 64 rows) and NLD_SPLITK (17..64) the slices alone.
+// than 64 rows) and NLD_SPLITK (up to 64) the slices alone.
 struct PanelPlan {
     int shape = 0, ksplit = 1;
 };
@@ -408,7 +412,7 @@ int panel_groups(const PanelPlan& p, int n_tiles) {
 hipError_t panel_gemm(int epi, const PanelPlan& p, GemmArgs& g, void* ws, const Layout& L, hipStream_t s, int* groups) {
     g.n_parts = panel_groups(p, g.n_tiles);
     if (groups) *groups = g.n_parts;
-    return launch_gemm_panel(epi, p.shape, g, p.ksplit, at<float>(ws, L.part), at<unsigned>(ws, L.tile_ctr) + L.ctr0, s);
+    return launch_gemm_panel(epi, p.shape, g, p.ksplit, at<float>(ws, L.part), at<unsigned>(ws, L.tile_ctr) + CTR0, s);
 }
 
 // Residual projections (O, down).  Up to 16 rows O runs streamed and, up to 8, down on the split-K kernel (at
@@ -418,7 +422,7 @@ hipError_t resid_gemm(int kind, const PanelPlan* plans, GemmArgs& g, void* ws, c
     *n_ss = g.n_tiles;
     int ct = 0, ksplit = 0;
     if (g.M <= 16 && plan_splitk(kind, g, L, &ct, &ksplit))
-        return launch_gemm_splitk(ct, ksplit, g, at<float>(ws, L.part), at<unsigned>(ws, L.tile_ctr) + L.ctr0, s);
+        return launch_gemm_splitk(ct, ksplit, g, at<float>(ws, L.part), at<unsigned>(ws, L.tile_ctr) + CTR0, s);
     if (g.M <= 16 && kind == PROJ_O) return launch_gemm_stream(env_int("NLD_STREAM_NW_RESID", 16), g, s);
     return panel_gemm(EPI_RESID, plans[kind], g, ws, L, s, n_ss);
 }
@@ -527,7 +531,6 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
         g.head_dim = D;
         g.max_len = kv->max_len;
         g.rope = at<float2>(ws, L.rope);
-        g.tile_ctr = at<unsigned>(ws, L.tile_ctr) + 2 * l;
         g.status = status;
         g.plain = plain & (SITE_Q | SITE_KV);
         {
@@ -615,7 +618,6 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
         gu.ksteps = ks_h;
         gu.act = at<uint16_t>(ws, L.act);
         gu.ffn = c.ffn;
-        gu.tile_ctr = at<unsigned>(ws, L.tile_ctr) + 2 * l + 1;
         gu.plain = plain & SITE_ACT;
         {
             TraceScope ts(NLD_TRACE_GATE_UP, s);
@@ -659,7 +661,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
     const bool denoise = io.finish == FINISH_DENOISE;
     const bool ensemble = io.finish == FINISH_QUAD && io.lambda > 0.0f && io.lambda < 1.0f;
     GemmArgs gl{};
-    gl.tile_ctr = at<unsigned>(ws, L.tile_ctr) + 2 * c.n_layers;
+    gl.tile_ctr = at<unsigned>(ws, L.tile_ctr);
     gl.eps = c.rms_eps;
     gl.n_ss = n_ss;
     gl.M = M;

@@ -34,8 +34,8 @@ __device__ __forceinline__ f32x4_t mfma_16x16x32(uint4 a, uint4 b, f32x4_t c) {
 }
 
 // One 16-byte block of a weight matrix that is read once per pass, loaded with the non-temporal
-// hint (the `nt` bit).  The normed GEMMs use it for their weight streams, where it measured
-// faster; the O, down and attention streams measured slower with it and keep plain loads.
+// hint (the `nt` bit): the weight streams of the panel GEMM and the normed GEMM.  The streamed GEMM (O up to 16 rows) and
+// the split-K GEMM (down up to 8 rows) measured slower with it (11.2 and 12.8 us, 23.3 and 24.6 us) and keep plain loads.
 __device__ __forceinline__ uint4 load_stream(const uint4* p) {
     typedef uint32_t u32x4_nt __attribute__((ext_vector_type(4)));
     const u32x4_nt v = __builtin_nontemporal_load((const u32x4_nt*)p);
@@ -116,7 +116,7 @@ struct GemmArgs {
     const uint4* W;      // packed weights: [n_tiles][ksteps][64 lanes] x 16 bytes
     int n_tiles;
     int ksteps;          // ceil(K / 32)
-    unsigned* tile_ctr;  // normed GEMM: dynamic tile counter (zeroed by the embedding kernel each pass)
+    unsigned* tile_ctr;  // normed GEMM (the LM head): dynamic tile counter (zeroed by the embedding kernel each pass)
     // Second reduction source (streamed GEMM, ksteps2 <= 2 * wavefronts, and panel GEMM): the sum
     // continues over ksteps2 more k-steps of W2 (packed, ksteps2 steps per tile) against A2
     // (split, ksteps2 steps per row tile).  The draft pass's O projection uses it for the

@@ -8,14 +8,15 @@ phase boundaries of each kernel), runs five passes of the workload's block to wa
 recorded pass, and prints, for the last layer's kernels, when their workgroups started and ended and
 the median / p90 / max of each phase, in microseconds from the first workgroup start of that layer's
 QKV GEMM.  The passes are eager launches (no graph), so the gaps between kernels include the launch
-overhead of the host.  Phases:
+overhead of the host.  Timestamps, in the order they are taken (a kernel has some of them):
 
-    qkv, gate_up   0-1 operand, first weight tile and row statistics in; 1-2 tiles and epilogues
-                   (17..64 rows: 0-1 main loop; 1-2 completed tiles reduced and finished)
-    attention      0-1 committed length known; 1-2 first key stage in LDS; 2-3 stages; 3-4 partials out
-    combine        0-1 the whole merge
-    o_proj         0-1 main loop; 1-2 reduction and residual epilogue
-    down           0-1 main loop; 1-2 partial stored and counted in (the last arriver then finishes)
+    qkv, gate_up, down   0 start; 3 first stage in LDS; 1 main loop done; 2 K slices added (the last arriver; the
+                         others end when they are counted in); 4 end
+    attention            0 start; 1 committed length known; 2 first key stage in LDS; 3 stages done; 4 partials out
+    combine              0 start; 1 end
+    o_proj               0 start; 1 main loop done; 2 end (up to 16 rows; above, O is on down's kernel, and down's
+                         timestamps stand)
+    down, up to 8 rows   0 start; 1 main loop done; 2 counted in (the last arriver then finishes)
 """
 from __future__ import annotations
 
@@ -30,7 +31,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-CLASSES = [(0, "qkv", 3), (1, "attention", 5), (2, "combine", 2), (4, "o_proj", 3), (3, "gate_up", 3), (5, "down", 3)]
+PANEL = (0, 3, 1, 2, 4)
+CLASSES = [(0, "qkv", PANEL), (1, "attention", (0, 1, 2, 3, 4)), (2, "combine", (0, 1)), (4, "o_proj", (0, 1, 2)),
+           (3, "gate_up", PANEL), (5, "down", PANEL)]
 
 
 def main():
@@ -82,22 +85,21 @@ def main():
     t0 = int(ts[0][used[0]][:, 0].min())
     print("%s, batch 1, prefix %d, k=%d, %s pass: last layer, us from its QKV's first workgroup start "
           "(s_memrealtime, 10 ns ticks; eager launches)" % (wl.name, P, k, args.mode))
-    for c, name, nph in CLASSES:
+    for c, name, phases in CLASSES:
         a = ts[c][used[c]].astype(np.int64)
         if a.shape[0] == 0:
             continue
-        rel = (a[:, :nph] - t0) / 100.0
-        end = rel[:, nph - 1]
-        end = end[a[:, nph - 1] > 0]
+        phases = [p for p in phases if (a[:, p] > 0).any()]
+        start = (a[:, 0] - t0) / 100.0
+        end = (a[:, phases].max(axis=1) - t0) / 100.0   # each workgroup's last timestamp
         print("%-9s workgroups %4d  start min %7.2f med %7.2f max %7.2f | end min %7.2f med %7.2f max %7.2f" % (
-            name, a.shape[0], rel[:, 0].min(), np.median(rel[:, 0]), rel[:, 0].max(), end.min(), np.median(end),
-            end.max()))
-        for p in range(1, nph):
-            ok = (a[:, p] > 0) & (a[:, p - 1] > 0)
+            name, a.shape[0], start.min(), np.median(start), start.max(), end.min(), np.median(end), end.max()))
+        for q, p in zip(phases, phases[1:]):
+            ok = (a[:, p] >= a[:, q]) & (a[:, q] >= a[:, 0])   # not an earlier layer's (not every workgroup has every phase)
             if ok.any():
-                d = (a[ok, p] - a[ok, p - 1]) / 100.0
+                d = (a[ok, p] - a[ok, q]) / 100.0
                 print("    phase %d-%d: %4d workgroups  med %6.2f  p90 %6.2f  max %6.2f us" % (
-                    p - 1, p, ok.sum(), np.median(d), np.percentile(d, 90), d.max()))
+                    q, p, ok.sum(), np.median(d), np.percentile(d, 90), d.max()))
 
 
 if __name__ == "__main__":
