@@ -244,20 +244,6 @@ nld_status check_config(const nld_config* c) {
 }
 
 // ---------------------------------------------------------------- GEMM launch plans
-// Normed multi-tile GEMM (the LM head): k-steps per wavefront and wavefront count with ks * waves == ksteps.
-bool plan_norm(int M, int ksteps, int* ks, int* waves) {
-    if (M > 16 || env_int("NLD_NO_NORM_GEMM", 0)) return false;
-    const int cand[] = {env_int("NLD_NORM_KS_LM", 16), 8, 16, 20, 4};   // 16: 8 wavefronts, the epilogue needs registers
-    for (int c : cand) {
-        if (gemm_norm_supported(c) && ksteps % c == 0 && ksteps / c >= 1 && ksteps / c <= gemm_norm_max_waves(c)) {
-            *ks = c;
-            *waves = ksteps / c;
-            return true;
-        }
-    }
-    return false;
-}
-
 // Compute units of the current device (queried once per device; NLD_CUS overrides).
 int device_cus() {
     const int forced = env_int("NLD_CUS", 0);
@@ -427,10 +413,13 @@ hipError_t resid_gemm(int kind, const PanelPlan* plans, GemmArgs& g, void* ws, c
     return panel_gemm(EPI_RESID, plans[kind], g, ws, L, s, n_ss);
 }
 
-// The LM head of up to 16 rows with at least four column tiles per CU runs on the normed multi-tile kernel where that
-// divides the reduction (both sides measured at that kernel; 64 tiles: 13.1 against 5.7 us).
-bool lm_normed(int M, int n_tiles, int ksteps, int* ks, int* waves) {
-    return n_tiles >= 4 * device_cus() && plan_norm(M, ksteps, ks, waves);
+// The LM head of up to 16 rows on the normed multi-tile GEMM: where the reduction is a full operand slice for each of
+// its 8 wavefronts, and there are at least four column tiles per CU.  At 9496 tiles, 16 rows and logits, it and the panel
+// GEMM take 200 and 216 us (hidden 4096), and with fewer or shorter slices, or longer ones that do not fit the
+// registers, 125 and 61 (1024), 138 and 111 (2048), 161 and 159 (3072), 305 and 262 us (5120); at 1100 tiles and
+// hidden 4096 30.4 and 30.8, at 64 13.1 and 5.7 us.  NLD_NO_NORM_GEMM: never.
+bool lm_normed(int M, int n_tiles, int ksteps) {
+    return M <= 16 && ksteps == gemm_norm_ksteps() && n_tiles >= 4 * device_cus() && !env_int("NLD_NO_NORM_GEMM", 0);
 }
 
 // One projection whose operand is RMSNorm(x) (QKV, gate/up, LM head): the panel GEMM, or for the LM head the normed
@@ -438,10 +427,9 @@ bool lm_normed(int M, int n_tiles, int ksteps, int* ks, int* waves) {
 hipError_t normed_gemm(int kind, int epi, const PanelPlan* plans, GemmArgs g, void* ws, const Layout& L, hipStream_t s) {
     g.A = at<uint16_t>(ws, L.xg);
     g.part_ss = at<float>(ws, L.part_ss);
-    int ks = 0, waves = 0;
-    if (kind == PROJ_LM && lm_normed(g.M, g.n_tiles, g.ksteps, &ks, &waves)) {
+    if (kind == PROJ_LM && lm_normed(g.M, g.n_tiles, g.ksteps)) {
         g.n_parts = device_cus();   // tiles beyond the first one per workgroup are handed out dynamically
-        return launch_gemm_norm(ks, waves, g.n_parts, g, s);
+        return launch_gemm_norm(g.n_parts, g, s);
     }
     return panel_gemm(epi, plans[kind], g, ws, L, s, nullptr);
 }
@@ -484,8 +472,7 @@ nld_status run_pass(const nld_model* mdl, const nld_kv_cache* kv, int batch, int
     // before the first launch, which the others need not hold up.
     PanelPlan plans[N_PROJ];   // the same for every layer
     plans[PROJ_LM] = plan_panel(PROJ_LM, M, L.lm_tiles, c.hidden, L);
-    int ks_lm = 0, waves_lm = 0;
-    const bool normed = lm_normed(M, L.lm_tiles, cdiv(c.hidden, 32), &ks_lm, &waves_lm);
+    const bool normed = lm_normed(M, L.lm_tiles, cdiv(c.hidden, 32));
     const int parts = normed ? device_cus() : panel_groups(plans[PROJ_LM], L.lm_tiles);
     const int n_keys = normed ? parts : std::min(parts, KEY_SLOTS);
     e.keys = n_keys < parts && !io.kv_only ? at<unsigned long long>(ws, L.keys) : nullptr;

@@ -185,20 +185,19 @@ __device__ __forceinline__ void rms_scales(const GemmArgs& a, int m0, int rows, 
 // register buffer: the load of the next tile's step s is issued as soon as step s of the current tile has
 // been multiplied, so one tile's worth of loads is in flight throughout.  Per tile the NW partial products
 // meet in LDS and one group of wavefronts (rotating) runs the epilogue.  Against the panel GEMM it has no
-// prologue per tile and no uneven last round: 198 against 203 us for 9496 tiles (vocab 151936, hidden 4096),
-// 27.5 against 28.6 us for 1055; for a projection with few tiles per CU the panel GEMM is faster.
+// prologue per tile and no uneven last round, but only a full workgroup of full slices streams as fast: the rule of
+// its dispatch has both sides' times.
 // =====================================================================================
-template <int KS>
-__global__ void __launch_bounds__(KS >= 16 ? 512 : 1024) gemm_norm_kernel(GemmArgs a) {
-    __shared__ f32x4_t red[2][16][64];
+template <int NW, int KS>
+__global__ void __launch_bounds__(NW * 64) gemm_norm_kernel(GemmArgs a) {
+    __shared__ f32x4_t red[2][NW][64];
     __shared__ float inv_s[16];
-    __shared__ unsigned long long key_s[16][16];
-    __shared__ float2 lse_s[16][16];
+    __shared__ unsigned long long key_s[NW][16];
+    __shared__ float2 lse_s[NW][16];
     __shared__ int next_s[2];
 
     NLD_TS(TL_LM, 0);
-    const int NW = blockDim.x >> 6;
-    if (threadIdx.x < 256) {
+    if (threadIdx.x < NW * 16) {
         key_s[threadIdx.x >> 4][threadIdx.x & 15] = 0ull;
         lse_s[threadIdx.x >> 4][threadIdx.x & 15] = float2{-INFINITY, 0.f};
     }
@@ -236,10 +235,9 @@ __global__ void __launch_bounds__(KS >= 16 ? 512 : 1024) gemm_norm_kernel(GemmAr
     if (threadIdx.x == 0) next_s[0] = G < T ? min(G + (int)grab, T) : T;
     __syncthreads();
 
-    // A tile is finished by FIN wavefronts (wavefront i of the group takes rows 4g + i,
-    // 4g + i + FIN, ...); the groups take the tiles in turn.
+    // A tile is finished by FIN wavefronts (wavefront i of the group takes rows 4g + i); the groups take the tiles in turn.
     NLD_TS(TL_LM, 1);   // operand, first tile and row statistics in
-    const int FIN = NW < 4 ? NW : 4, groups = NW / FIN;
+    constexpr int FIN = 4, groups = NW / FIN;
     for (int it = 0; cur < T; ++it) {
         const int t = cur;
         const int nxt = next_s[it & 1];   // its weights stream in while tile t is multiplied
@@ -260,16 +258,15 @@ __global__ void __launch_bounds__(KS >= 16 ? 512 : 1024) gemm_norm_kernel(GemmAr
         cur = nxt;
         if (wave / FIN == it % groups) {
             const float* rp = (const float*)&red[parity][0][lane];
-            for (int i = wave % FIN; i < 4; i += FIN) {
-                float v = rp[i];
-                for (int w = 1; w < NW; ++w) v += rp[w * 256 + i];   // fixed order over the K-slices
-                const int m = 4 * g + i;
-                float2 tl;
-                const unsigned long long key = epi_lmhead(a, v * inv_s[m], m, t, lane, &tl);
-                if (r == 0) {
-                    key_s[wave][m] = umax64(key_s[wave][m], key);
-                    if (a.part_lse) lse_s[wave][m] = lse_merge(lse_s[wave][m], tl);
-                }
+            const int i = wave % FIN, m = 4 * g + i;
+            float v = rp[i];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) v += rp[w * 256 + i];   // fixed order over the K-slices
+            float2 tl;
+            const unsigned long long key = epi_lmhead(a, v * inv_s[m], m, t, lane, &tl);
+            if (r == 0) {
+                key_s[wave][m] = umax64(key_s[wave][m], key);
+                if (a.part_lse) lse_s[wave][m] = lse_merge(lse_s[wave][m], tl);
             }
         }
     }
@@ -289,19 +286,12 @@ __global__ void __launch_bounds__(KS >= 16 ? 512 : 1024) gemm_norm_kernel(GemmAr
     }
 }
 
-bool gemm_norm_supported(int ks) { return ks == 4 || ks == 8 || ks == 16 || ks == 20; }
+constexpr int NORM_NW = 8, NORM_KS = 16;
+int gemm_norm_ksteps() { return NORM_NW * NORM_KS; }
 
-int gemm_norm_max_waves(int ks) { return ks >= 16 ? 8 : 16; }
-
-hipError_t launch_gemm_norm(int ks, int waves, int grid, const GemmArgs& a, hipStream_t s) {
-    if (waves < 1 || waves > gemm_norm_max_waves(ks)) return hipErrorInvalidValue;
-    switch (ks) {
-        case 4: launch(gemm_norm_kernel<4>, dim3(grid), dim3(waves * 64), s, a); break;
-        case 8: launch(gemm_norm_kernel<8>, dim3(grid), dim3(waves * 64), s, a); break;
-        case 16: launch(gemm_norm_kernel<16>, dim3(grid), dim3(waves * 64), s, a); break;
-        case 20: launch(gemm_norm_kernel<20>, dim3(grid), dim3(waves * 64), s, a); break;
-        default: return hipErrorInvalidValue;
-    }
+hipError_t launch_gemm_norm(int grid, const GemmArgs& a, hipStream_t s) {
+    if (a.M > 16 || a.ksteps != NORM_NW * NORM_KS) return hipErrorInvalidValue;
+    launch(gemm_norm_kernel<NORM_NW, NORM_KS>, dim3(grid), dim3(NORM_NW * 64), s, a);
     return hipGetLastError();
 }
 

@@ -297,10 +297,9 @@ hipError_t launch_pack(const PackArgs& a, hipStream_t s);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_copy_u32(const uint32_t* src, uint32_t* dst, hipStream_t s);   // *dst = *src (one word)
 hipError_t launch_embed(const EmbedArgs& a, hipStream_t s);
-// Normed multi-tile GEMM (LM head, M <= 16).  ks = k-steps per wavefront (ksteps = ks * waves); grid = workgroups.
-bool gemm_norm_supported(int ks);
-int gemm_norm_max_waves(int ks);
-hipError_t launch_gemm_norm(int ks, int waves, int grid, const GemmArgs& a, hipStream_t s);
+// Normed multi-tile GEMM (LM head, M <= 16, ksteps = gemm_norm_ksteps()); grid = workgroups.
+int gemm_norm_ksteps();
+hipError_t launch_gemm_norm(int grid, const GemmArgs& a, hipStream_t s);
 // Streamed GEMM (EPI_RESID, M <= 16): one column tile per workgroup, nw (8 or 16) wavefronts split K.  With
 // a.W2 set the reduction continues over the second source.
 hipError_t launch_gemm_stream(int nw, const GemmArgs& a, hipStream_t s);
