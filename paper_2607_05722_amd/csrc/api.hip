@@ -312,12 +312,15 @@ enum ProjKind { PROJ_O = 0, PROJ_DOWN = 1, PROJ_QKV = 2, PROJ_GU = 3, PROJ_LM = 
 
 // Split-K plan of a residual projection with at most 16 rows: ct column tiles per workgroup and ksplit K
 // slices, so that column groups x slices is at most one workgroup per CU, with every wavefront (8 per
-// workgroup) getting at least two k-steps.  Default: the down projection of up to 8 rows, 2 tiles (O runs
-// streamed, 11.3 against 12.9 us).  Environment overrides: NLD_SPLITK_<O|DOWN> = "ct,ksplit" ("ct,0": ksplit
+// workgroup) getting at least two k-steps.  Default: the down projection of up to 8 rows, 2 tiles, where its groups
+// are few enough for two slices.  Split-K and panel GEMM in the middle of a pass: 21.8 and 21.7 us at 1 row of the 8B
+// shapes (128 groups, 2 slices), 22.0 and 21.8 at 8; whole passes of a model of hidden 256 69.8 and 70.8 us, of
+// hidden 2080 232.3 and 234.2; but 39.6 and 34.9 us per launch at hidden 5120 (160 groups, one slice, 96 CUs
+// idle).  (O runs streamed: 10.8 against 11.4 us at 16 rows.)  Environment overrides: NLD_SPLITK_<O|DOWN> = "ct,ksplit" ("ct,0": ksplit
 // from the rule; "0": off), NLD_SPLITK / NLD_SPLITK_CT for both at once, NLD_NO_SPLITK = 1: off.
 bool plan_splitk(int kind, const GemmArgs& g, const Layout& L, int* ct, int* ksplit) {
     if (g.W2 || env_int("NLD_NO_SPLITK", 0)) return false;
-    int c = kind == PROJ_DOWN && g.M <= 8 ? 2 : 0, ks = 0;
+    int c = kind == PROJ_DOWN && g.M <= 8 && 2 * cdiv(g.n_tiles, 2) <= device_cus() ? 2 : 0, ks = 0;
     const char* v = getenv(kind == PROJ_O ? "NLD_SPLITK_O" : "NLD_SPLITK_DOWN");
     if (v && *v) {
         c = atoi(v);
@@ -401,8 +404,8 @@ hipError_t panel_gemm(int epi, const PanelPlan& p, GemmArgs& g, void* ws, const 
     return launch_gemm_panel(epi, p.shape, g, p.ksplit, at<float>(ws, L.part), at<unsigned>(ws, L.tile_ctr) + CTR0, s);
 }
 
-// Residual projections (O, down).  Up to 16 rows O runs streamed and, up to 8, down on the split-K kernel (at
-// those kernels: both sides measured); the rest on the panel GEMM.  n_ss: sums of squares per row the
+// Residual projections (O, down).  Up to 16 rows O runs streamed and, up to 8, down on the split-K kernel (both sides
+// measured at the streamed kernel and at plan_splitk); the rest on the panel GEMM.  n_ss: sums of squares per row the
 // projection writes for the next RMSNorm.
 hipError_t resid_gemm(int kind, const PanelPlan* plans, GemmArgs& g, void* ws, const Layout& L, hipStream_t s, int* n_ss) {
     *n_ss = g.n_tiles;

@@ -298,11 +298,11 @@ hipError_t launch_gemm_norm(int grid, const GemmArgs& a, hipStream_t s) {
 // =====================================================================================
 // Streamed GEMM: the O projection of up to 16 rows.  A workgroup takes one column tile; its NW wavefronts
 // split the reduction, each streaming its slice of the weights and of the split activations with one batch
-// in flight ahead of the MFMAs (two per weight operand).  No slices meet and rows past M are not read: 8.2 us
-// at 8 rows of the 8B shapes against 10.6 us for the panel GEMM, 8.0 against 11.0 at 16.  XK: the reduction
-// continues over a second source (the LoRA up-projection): 9.3 us with rank 128 at 16 rows of the 8B shapes.  The
+// in flight ahead of the MFMAs (two per weight operand).  No slices meet and rows past M are not read: in the middle of a
+// pass 8.6 us at 1 and 8 rows of the 8B shapes against 11.9 us for the panel GEMM, 10.8 against 12.3 at 16.  XK: the reduction
+// continues over a second source (the LoRA up-projection): 11.1 us with rank 128 at 16 rows of the 8B shapes.  The
 // zeros past the ends are written as values: a conditional between a named zero quad and a loaded one chooses an
-// address, and the quad then lives in private memory (13.5 us).
+// address, and the quad then lives in private memory (16.9 us).
 // =====================================================================================
 // Operand and weight registers of one batch: U k-steps of CT column tiles.
 template <int CT, int U>
@@ -415,14 +415,14 @@ hipError_t launch_gemm_stream(int nw, const GemmArgs& a, hipStream_t s) {
 }
 
 // =====================================================================================
-// Split-K GEMM: the down projection of up to 8 rows.  (Rows past M are not read: 19.5 us at 1 row of the
-// 8B shapes against 20.9 us for the panel GEMM, 20.9 against 21.1 at 8 rows, 24.7 against 21.3 at 16.)
+// Split-K GEMM: the down projection of up to 8 rows, where two K slices per column group fit the CUs (rows past M are
+// not read; both sides' times stand at the rule, plan_splitk).
 // Workgroup (column group cg,
 // K slice ks) multiplies its slice of the operand against CT column tiles, so the
 // operand is read once per CT tiles and K slice instead of once per tile (the split
 // operand is twice as large as the weights it multiplies in these projections).  The
 // NW wavefronts cut the slice further and meet in LDS.  With ksplit > 1 the workgroup's
-// partial [16*MT rows][16*CT columns] goes to the workspace with agent-scope stores
+// partial [16 rows][16*CT columns] goes to the workspace with agent-scope stores
 // (written through to memory, so that every XCD sees them); once every lane's stores
 // are acknowledged, one atomic on the group's counter counts the workgroup in.  The
 // workgroup that arrives last reads the other partials with agent-scope loads (which
