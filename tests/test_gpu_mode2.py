@@ -238,7 +238,7 @@ def test_8b_layer_denoising_and_refresh(R, layer8b2, batch):
     assert R.read_device_status(ws) == 0
 
 
-@pytest.mark.parametrize("vocab,k", [(15, 8), (1000, 24), (16400, 64), (70000, 32)])
+@pytest.mark.parametrize("vocab,k", [(15, 8), (20000, 8), (1000, 24), (16400, 64), (70000, 32)])
 def test_finish_over_any_number_of_partials(R, monkeypatch, vocab, k):
     """The finish reads a row's LM-head partials sixteen loads at a time: 1 to 1094 of them (column groups of 64), with
     remainders.  Confidences and commit of a denoising step and the drafts of a draft pass, against the device's own

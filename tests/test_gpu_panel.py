@@ -80,6 +80,14 @@ def test_planned(R, model, batch, k):
         assert run(R, model, batch, k, mode) <= TOL
 
 
+@pytest.mark.parametrize("batch,k", [(1, 1), (3, 2), (1, 8)])
+def test_down_of_few_rows(R, model, monkeypatch, batch, k):
+    """Down of up to 8 rows on the panel GEMM, as where the split-K kernel's groups leave no room for two slices."""
+    monkeypatch.setenv("NLD_NO_SPLITK", "1")
+    for mode in (O.VERIFY, O.DRAFT):
+        assert run(R, model, batch, k, mode) <= TOL
+
+
 def bf16_parts(v):
     """v as a sum of three bf16 values (bits)."""
     parts, rest = [], np.float64(v)
