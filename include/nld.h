@@ -376,7 +376,7 @@ nld_status nld_read_device_status(void* workspace, uint32_t* host_bits, void* st
  * threads) race and must be serialized by the caller.
  * Errors as nld_verify_accept; NLD_ERR_CAPACITY when the scratch this batch,
  * k and max_len need (nld_workspace_bytes) exceeds NLD_NOALLOC_SCRATCH_BYTES
- * (it holds batch 1 at k <= 16 for the 8B and 14B shapes). */
+ * (it holds batch 1 at k <= 64 for the 8B and 14B shapes). */
 #define NLD_NOALLOC_SCRATCH_BYTES (64u << 20)
 nld_status nld_verify_accept_noalloc(const nld_model* m, const nld_kv_cache* kv, const int32_t* anchor,
                                      const int32_t* draft, int32_t batch, int32_t k, int32_t* accept_len,

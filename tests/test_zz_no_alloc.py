@@ -85,3 +85,32 @@ def test_noalloc_verify_equals_workspace_verify():
         if want_status:
             assert int(cb.lengths.cpu().max()) <= max_len
     model.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("k", [17, 32, 64])
+def test_noalloc_verify_of_many_rows(k):
+    """The scratch also holds one sequence of 17 to 64 rows of the 8B shapes (one layer of them here), whose K slices'
+    partials are most of it: the same results as with a workspace."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2607_05722_amd import runtime as R
+    wl = WORKLOADS["8b_layer"]
+    shape, max_len = wl.shape, 4608
+    model = R.DeviceModel(shape, LazyWeights(shape, wl.seed))
+    ws = R.Workspace(model, 1, k, max_len)
+    assert ws.nbytes <= C.NLD_NOALLOC_SCRATCH_BYTES
+    anchor = torch.from_numpy(synth_tokens(shape, wl.seed, "noalloc.anchor", (1,))).cuda()
+    drafts = torch.from_numpy(synth_tokens(shape, wl.seed, "noalloc.drafts", (1, k - 1))).cuda()
+    out = []
+    for alloc in (True, False):
+        cache = R.DeviceCache(shape, 1, max_len)
+        cache.set_lengths([700])
+        if alloc:
+            out.append(R.verify_accept(model, cache, ws, anchor.clone(), drafts, k, want_logits=True))
+            assert R.read_device_status(ws) == 0
+        else:
+            out.append(R.verify_accept_noalloc(model, cache, anchor.clone(), drafts, k, want_logits=True))
+    for name in ("logits", "accept_len", "committed", "next_anchor"):
+        assert torch.equal(out[0][name], out[1][name]), name
+    model.close()
